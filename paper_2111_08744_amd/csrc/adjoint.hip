@@ -172,18 +172,18 @@ struct RayCtx {
     double xobs[3];
 };
 
-// Trilinear coefficients (component-major: c[8 q + k]) of a stencil, read
+// Trilinear coefficients (component-major: c[8 q + k], gx, gy, gz) of a stencil, read
 // from the dual table.  (The lane's LDS copy holds only the stencil of the
 // replay's last stage; choosing between the two per lane made a wave wait
 // for the table whenever any of its lanes missed, and the records of a
 // step's stencils are in the caches after its replay.)
-__device__ __forceinline__ void stencil_coefs(const GridDev& g, int base, float c[32])
+__device__ __forceinline__ void stencil_coefs(const GridDev& g, int base, float c[24])
 {
     const float4* rec = g.dual + 8 * (int64_t)base;
 #pragma unroll
-    for (int o = 0; o < 8; ++o) {
+    for (int o = 0; o < 6; ++o) {
         const float4 q = rec[o];
-        c[o] = q.x; c[8 + o] = q.y; c[16 + o] = q.z; c[24 + o] = q.w;
+        c[4 * o] = q.x; c[4 * o + 1] = q.y; c[4 * o + 2] = q.z; c[4 * o + 3] = q.w;
     }
 }
 
@@ -244,13 +244,13 @@ __device__ __forceinline__ void jet_from_stage(const AdjointArgs& A, const RayCt
 // t-derivatives of the trilinear interpolant (Eq. W_CIC) times 2^lvl / h0.
 __device__ __forceinline__ void jet_gradient(const GridDev& g, const StageData& d, Jet32& J)
 {
-    float c[32];
+    float c[24];
     stencil_coefs(g, d.base, c);
     const float tx = d.t[0], ty = d.t[1], tz = d.t[2];
     const float scale = (float)((double)(1 << d.lvl) * g.inv_h0);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const float* k = c + 8 * (j + 1);
+        const float* k = c + 8 * j;
         J.JG[j][0] = (k[1] + ty * k[4] + tz * k[5] + ty * tz * k[7]) * scale;
         J.JG[j][1] = (k[2] + tx * k[4] + tz * k[6] + tx * tz * k[7]) * scale;
         J.JG[j][2] = (k[3] + tx * k[5] + ty * k[6] + tx * ty * k[7]) * scale;
@@ -536,12 +536,10 @@ __device__ __forceinline__ bool plan_step(const CastArgs& a, FieldCache<AMR>& F,
     double v[3];
     grid_coords(g, geo, y.eta, y.dx, v);
     int L;
-    s0.phi = s0.G[0] = s0.G[1] = s0.G[2] = s0.tv = 0.0f;
-    s0.l = 0;
-    s0.bad = F.eval(g, v, s0.phi, s0.G, L, s0.l);
+    s0.bad = F.eval(g, v, s0.G, L, s0.l);
     if (L < 0) return false;
     ds = step_length(a, L);
-    dl = ds / y.K;
+    dl = quotient(ds, y.K);
     landing = fma(-y.K, dl, y.eta) < eta_s;
     return true;
 }
@@ -561,7 +559,7 @@ __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>&
     ds_out = ds;
     if (__builtin_expect(!landing, 1)) {
         // the recorder of stage 0 sees the lane's cache as plan_step left it
-        if (rk4_step<FieldCache<AMR>, Rec, true>(a.grid, a.cosmo, F, geo, y, dl, yn, h, rec, record, &s0))
+        if (rk4_step<FieldCache<AMR>, Rec, false>(a.grid, a.cosmo, F, geo, y, dl, yn, h, rec, record, &s0))
             return false;
         dl_taken = dl;
         return true;
@@ -572,7 +570,7 @@ __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>&
     double dlx = (y.eta - eta_s) / y.K;
     for (int k = 0; k < 3; ++k) {
         const bool rec_pass = record && k == 2;
-        if (rk4_step<FieldCache<AMR>, Rec, true>(a.grid, a.cosmo, F, geo, y, dlx, yn, h, rec, rec_pass,
+        if (rk4_step<FieldCache<AMR>, Rec, false>(a.grid, a.cosmo, F, geo, y, dlx, yn, h, rec, rec_pass,
                                                  rec_pass ? nullptr : &s0))
             return false;
         if (k < 2) dlx = dlx + (yn.eta - eta_s) / yn.K;
@@ -725,11 +723,12 @@ __device__ __forceinline__ void point_jet(const AdjointArgs& A, const RayCtx& R,
     const GridDev& g = A.c.grid;
     stage_offsets(g, R, ys, lvl, P.t);
     const float4* rec = g.dual + 8 * (int64_t)base;
-    double c[4][8];
+    double c[4][8];             // phi, gx, gy, gz
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
         const float4 q = rec[o];
-        c[0][o] = q.x; c[1][o] = q.y; c[2][o] = q.z; c[3][o] = q.w;
+        double* k = c[(o / 2 + 1) & 3] + 4 * (o & 1);
+        k[0] = q.x; k[1] = q.y; k[2] = q.z; k[3] = q.w;
     }
     const double scale = (double)(1 << lvl) * g.inv_h0;
     double fx, fy, fz;
@@ -765,11 +764,10 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
 {
     constexpr bool HAS_JAC = W >= 3;
     const GridDev& g = A.c.grid;
-    float ph_f, Gt[3];
-    int ll, lv;
+    int ll;
     double vf[3];
     grid_coords(g, R.geo, yf.eta, yf.dx, vf);
-    F.eval(g, vf, ph_f, Gt, ll, lv);
+    F.locate(g, vf, ll);
     HubbleCubic Hf;
     Hf.init(A.c.cosmo, yf.eta);
     PointJet Jf;
@@ -859,12 +857,12 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
 template <bool AMR, int W, bool SCATTER>
 __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
 {
-    // LDS: [32][kBlock] stencil coefficients, [4 * 18][kBlock] stage records,
+    // LDS: [24][kBlock] stencil coefficients, [4 * 18][kBlock] stage records,
     // [33][kBlock] pending scatter sums, then one table per wave
     extern __shared__ float lds[];
     WaveTable T;
     if (SCATTER) {
-        T.bind(lds + (32 + 4 * StageRecord::kWords + kPendWords) * kBlock + (threadIdx.x >> 6) * kTabWords);
+        T.bind(lds + (FieldCache<AMR>::kFloats + 4 * StageRecord::kWords + kPendWords) * kBlock + (threadIdx.x >> 6) * kTabWords);
         T.clear(threadIdx.x & 63);
     }
     const int64_t ray = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
@@ -890,15 +888,14 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
     }
     const double eta_s = a.ray_stop ? a.ray_stop[ray].x : ob.eta_s;
     FieldCache<AMR> F;
-    F.bind(lds + threadIdx.x);
+    F.bind(lds);
     F.reset();
 
     // potential at the observer and the initial |k| (as in the forward)
-    float phio_f, Gt[3];
-    int ll, lv;
-    F.eval(g, R.geo.vo, phio_f, Gt, ll, lv);
+    int ll;
+    F.locate(g, R.geo.vo, ll);
     const int obs_base = F.base, obs_lvl = F.lvl;
-    const double phio = (double)phio_f;
+    const double phio = (double)F.phi(g);
     const double kmag = sqrt((1.0 + 2.0 * phio) / (1.0 - 2.0 * phio));
 
     const int K = a.ckpt_every;
@@ -912,7 +909,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
     for (int c = 0; c < W; ++c) lc[c] = 0.0f;
     double phio_bar = 0.0;
     Scatter<AMR> S;
-    S.init(lds + (32 + 4 * StageRecord::kWords) * kBlock + threadIdx.x);
+    S.init(lds + (FieldCache<AMR>::kFloats + 4 * StageRecord::kWords) * kBlock + threadIdx.x);
 
     // Segments from the source back to the observer.  Each is traversed
     // forwards from its checkpoint (storing the state before every step in
@@ -959,7 +956,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
                 if (jl > 0) pre = A.tape[(int64_t)(jl - 1) * a.n_rays + ray];
             }
             StageRecord rec;
-            rec.p = lds + 32 * kBlock + threadIdx.x;
+            rec.p = lds + FieldCache<AMR>::kFloats * kBlock + threadIdx.x;
             GeoState yn;
             double dl, ds;
             bool landing;
@@ -1066,7 +1063,7 @@ hipError_t launch_adjoint(const AdjointArgs& A, int columns, hipStream_t s)
     const int64_t n = A.c.n_rays;
     if (n == 0) return hipSuccess;
     const dim3 grid((unsigned)((n + kBlock - 1) / kBlock)), block(kBlock);
-    const size_t lds_cache = (size_t)(32 + 4 * StageRecord::kWords) * kBlock * sizeof(float);
+    const size_t lds_cache = (size_t)(FieldCache<true>::kFloats + 4 * StageRecord::kWords) * kBlock * sizeof(float);
     const size_t lds = lds_cache + (columns == 3 ? 0 : ((size_t)kPendWords * kBlock + (size_t)(kBlock / 64) * kTabWords) *
                                                           sizeof(float));
     const bool amr = A.c.grid.max_level > 0;

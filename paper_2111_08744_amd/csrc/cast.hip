@@ -79,10 +79,9 @@ struct RayRun {
         if constexpr (DP::kDiff) dp.dl_prev = 0.0;
         float G[3];
         int leafl, l;
-        if (F.eval(a.grid, geo.vo, phi_o, G, leafl, l)) {
-            status = MPATH_RAY_LEFT_DOMAIN;
-            phi_o = __builtin_nanf("");
-        }
+        phi_o = __builtin_nanf("");
+        if (F.eval(a.grid, geo.vo, G, leafl, l)) status = MPATH_RAY_LEFT_DOMAIN;
+        else phi_o = F.phi(a.grid);
         // k0 = -1 (backward in time); |k| from the null condition
         const double po = (double)phi_o;
         const double kmag = sqrt((1.0 + 2.0 * po) / (1.0 - 2.0 * po));
@@ -104,9 +103,10 @@ struct RayRun {
     {
         if (status >= 0) return true;
         const GridDev& g = a.grid;
-        // plain casts peel stage 0 (the step start's field evaluation serves
-        // it); the sampling casts keep the shorter code of the plain loop
+        // plain casts give the step start's field evaluation to stage 0 and
+        // unroll the stages; the sampling casts keep shorter code
         constexpr bool kPeel = std::is_same<Smp, NoSample>::value;
+        const int max_steps = (int)a.max_steps;     // at most 2^31 - 1
         int it = 0;
         for (;;) {
             // the field at the step start (stage 0 of the step, and of every
@@ -115,7 +115,7 @@ struct RayRun {
             // regular steps up to the one that would cross the stop surface
             for (;; ++it) {
                 if (it >= max_iter) return false;
-                if (n_steps >= a.max_steps) { status = MPATH_RAY_MAX_STEPS; return true; }
+                if (n_steps >= max_steps) { status = MPATH_RAY_MAX_STEPS; return true; }
                 if (CKPT && n_steps % a.ckpt_every == 0)
                     a.ckpt[(n_steps / a.ckpt_every) * a.n_rays + ray] = y;
                 // leaf level at the step start sets the step length (N steps
@@ -124,23 +124,19 @@ struct RayRun {
                 grid_coords(g, geo, y.eta, y.dx, v);
                 int L;
                 if constexpr (kPeel) {
-                    s0.phi = s0.G[0] = s0.G[1] = s0.G[2] = 0.0f;
-                    s0.l = 0;
-                    s0.bad = F.eval(g, v, s0.phi, s0.G, L, s0.l);
+                    s0.bad = F.eval(g, v, s0.G, L, s0.l);
+                    if constexpr (DP::kDiff) s0.phi = F.phi(g);
                     if constexpr (FC::kTime) s0.tv = F.tv;
                 } else {
-                    int I[3];
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) I[d] = (int)floor(v[d]);
-                    L = F.leaf(g, I);
+                    L = F.leaf(g, v);
                 }
                 if (L < 0) { status = MPATH_RAY_LEFT_DOMAIN; return true; }
                 hash = fnv(hash, (uint32_t)L);
                 smp.at_step(a, geo, y, L);
-                const double dl = step_length(a, L) / y.K;
+                const double dl = quotient(step_length(a, L), y.K);
                 if (fma(-y.K, dl, y.eta) < eta_s) break;
                 GeoState yn;
-                if (rk4_step_dp<FC, DP, kPeel>(g, a.cosmo, F, geo, y, dl, yn, hash, dp, &s0)) {
+                if (rk4_step_dp<FC, DP, kPeel>(g, a.cosmo, F, geo, y, dl, yn, hash, dp, kPeel ? &s0 : nullptr)) {
                     status = MPATH_RAY_LEFT_DOMAIN;
                     return true;
                 }
@@ -158,8 +154,9 @@ struct RayRun {
             // with derivative -K at the trial end, two iterations, then the step
             double dlx = (y.eta - eta_s) / y.K;
             GeoState yn;
+#pragma unroll 1
             for (int k = 0; k < 3; ++k) {
-                if (rk4_step_dp<FC, DP, kPeel>(g, a.cosmo, F, geo, y, dlx, yn, hash, dp, &s0)) {
+                if (rk4_step_dp<FC, DP, false>(g, a.cosmo, F, geo, y, dlx, yn, hash, dp, kPeel ? &s0 : nullptr)) {
                     status = MPATH_RAY_LEFT_DOMAIN;
                     return true;
                 }
@@ -199,9 +196,10 @@ struct RayRun {
         } else {
             double v[3];
             grid_coords(a.grid, geo, s.eta, s.dx, v);
-            float phi, G[3];
+            float G[3];
             int leafl, l;
-            if (F.eval(a.grid, v, phi, G, leafl, l)) return false;
+            if (F.eval(a.grid, v, G, leafl, l)) return false;
+            const float phi = F.phi(a.grid);
             const double sa = scale_factor(a.cosmo, s.eta);
             p = log(sa * s.K * (1.0 + (double)phi) / (1.0 + (double)phi_o));
             HubbleCubic Hc;
@@ -233,13 +231,10 @@ struct RayRun {
             if (n_steps >= a.max_steps) { status = MPATH_RAY_MAX_STEPS; return; }
             double v[3];
             grid_coords(g, geo, y.eta, y.dx, v);
-            int I[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) I[d] = (int)floor(v[d]);
-            const int L = F.leaf(g, I);
+            const int L = F.leaf(g, v);
             if (L < 0) { status = MPATH_RAY_LEFT_DOMAIN; return; }
             hash = fnv(hash, (uint32_t)L);
-            const double dl = step_length(a, L) / y.K;
+            const double dl = quotient(step_length(a, L), y.K);
             GeoState yn;
             if constexpr (SURF == MPATH_SURFACE_LAMBDA) {
                 if (lam + dl >= p_s) {
@@ -318,17 +313,14 @@ struct RayRun {
             if (n_steps >= a.max_steps) { status = MPATH_RAY_MAX_STEPS; return; }
             double v[3];
             grid_coords(g, geo, y.eta, y.dx, v);
-            int I[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) I[d] = (int)floor(v[d]);
-            const int L = F.leaf(g, I);
+            const int L = F.leaf(g, v);
             if (L < 0) { status = MPATH_RAY_LEFT_DOMAIN; return; }
             hash = fnv(hash, (uint32_t)L);
-            const double dl = step_length(a, L) / y.K;
+            const double dl = quotient(step_length(a, L), y.K);
             if (fma(-y.K, dl, y.eta) < eta_s) break;
             GeoState yn;
             T.begin_step(y, dl, true);
-            if (rk4_core<FC, Tan, ChainRule, true>(g, a.cosmo, F, geo, y, dl, yn, hash, T, true, cr)) {
+            if (rk4_core<FC, Tan, ChainRule, false>(g, a.cosmo, F, geo, y, dl, yn, hash, T, true, cr)) {
                 status = MPATH_RAY_LEFT_DOMAIN;
                 return;
             }
@@ -342,7 +334,7 @@ struct RayRun {
         GeoState yn;
         for (int k = 0; k < 3; ++k) {
             if (k == 2) T.begin_step(y, dlx, false);
-            if (rk4_core<FC, Tan, ChainRule, true>(g, a.cosmo, F, geo, y, dlx, yn, hash, T, k == 2, cr)) {
+            if (rk4_core<FC, Tan, ChainRule, false>(g, a.cosmo, F, geo, y, dlx, yn, hash, T, k == 2, cr)) {
                 status = MPATH_RAY_LEFT_DOMAIN;
                 return;
             }
@@ -386,7 +378,7 @@ struct RayRun {
         grid_coords(a.grid, geo, y.eta, y.dx, v);
         float phi_s = __builtin_nanf(""), G[3];
         int leafl, l;
-        if (F.eval(a.grid, v, phi_s, G, leafl, l)) phi_s = __builtin_nanf("");
+        if (!F.eval(a.grid, v, G, leafl, l)) phi_s = F.phi(a.grid);
         const OutDev& o = a.out;
         if (o.z5)
             o.z5[slot] = ok ? a_s * y.K * (1.0 + (double)phi_s) / (1.0 + (double)phi_o) - 1.0 : __builtin_nan("");
@@ -477,7 +469,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_static_kernel(C
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR, FieldCache<AMR, TIME>> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.start(a, r);
     R.advance(a, 0x7fffffff);
     R.finish(a);
@@ -491,7 +483,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_ckpt_kernel(Cas
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.start(a, r);
     R.template advance<true>(a, 0x7fffffff);
     R.finish(a);
@@ -503,7 +495,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_persistent_kern
     extern __shared__ float coef_lds[];
     const int lane = threadIdx.x & (kWave - 1);
     RayRun<AMR, FieldCache<AMR, TIME>> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.ray = -1;
     bool exhausted = false;
     for (;;) {
@@ -543,7 +535,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_persistent_kern
 // cache so that the integration's own cache is left in place.
 template <bool AMR>
 struct InfBeam {
-    FieldCache<AMR, false, false> P;
+    FieldCache<AMR> P;
     double chi_p, Tp[3];         // previous sample (T11, T12, T22)
     double J1[3], J2[3];         // trapezoid sums of chi T and chi^2 T
     int n;
@@ -582,9 +574,9 @@ struct InfBeam {
             double vp[3] = {v[0], v[1], v[2]}, vm[3] = {v[0], v[1], v[2]};
             vp[i] += hf;
             vm[i] -= hf;
-            float php, phm, gp[3], gm[3];
+            float gp[3], gm[3];
             int l0, l1;
-            const bool bad = P.eval(g, vp, php, gp, l0, l1) != 0 || P.eval(g, vm, phm, gm, l0, l1) != 0;
+            const bool bad = P.eval(g, vp, gp, l0, l1) != 0 || P.eval(g, vm, gm, l0, l1) != 0;
 #pragma unroll
             for (int j = 0; j < 3; ++j) H[i][j] = bad ? 0.0 : ((double)gp[j] - (double)gm[j]) / (2.0 * h);
         }
@@ -649,9 +641,9 @@ __global__ __launch_bounds__(kBlock, 2) void cast_infbeam_kernel(CastArgs a, flo
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     InfBeam<AMR> B;
-    B.init(coef_lds + 32 * kBlock + threadIdx.x);
+    B.init(coef_lds + FieldCache<AMR>::kFloats * kBlock);
     R.start(a, r);
     R.template advance<false, InfBeam<AMR>>(a, 0x7fffffff, B);
     const bool reached = R.status == MPATH_RAY_REACHED;
@@ -659,9 +651,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_infbeam_kernel(CastArgs a, flo
         // end-point sample: leaf level of the end point
         double v[3];
         grid_coords(a.grid, R.geo, R.y.eta, R.y.dx, v);
-        float ph, G[3];
-        int L, l;
-        B.P.eval(a.grid, v, ph, G, L, l);       // sets L (-1 outside a non-periodic box)
+        const int L = B.P.leaf(a.grid, v);       // -1 outside a non-periodic box
         B.at_step(a, R.geo, R.y, L < 0 ? 0 : L);
     }
     B.write(A + 4 * r, reached);
@@ -676,8 +666,8 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_diff_kernel(Cas
     extern __shared__ float coef_lds[];
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
-    RayRun<AMR, FieldCache<AMR>, StepDifference> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    RayRun<AMR, FieldCache<AMR, false, true>, StepDifference> R;
+    R.F.bind(coef_lds);
     R.start(a, r);
     R.advance(a, 0x7fffffff);
     R.finish(a);
@@ -691,7 +681,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_stop_kernel(Cas
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.start(a, r);
     int j = a.n_obs - 1;
     while (j > 0 && a.obs[j].ray_first > r) --j;
@@ -731,7 +721,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_surfaces_kernel(CastArgs a, Su
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.start(a, r);
     int j = a.n_obs - 1;
     while (j > 0 && a.obs[j].ray_first > r) --j;
@@ -771,9 +761,7 @@ __global__ __launch_bounds__(kBlock, 2) void born_beam_kernel(CastArgs a, float*
     const double eta_s = a.ray_stop ? a.ray_stop[r].x : ob.eta_s;
     const double chis = a.cosmo_eta0 - eta_s;
     InfBeam<AMR> B;
-    B.init(born_lds + threadIdx.x);
-    FieldCache<AMR> F;          // leaf lookups only (no stencil, no LDS)
-    F.reset();
+    B.init(born_lds);
     GeoState y;
     y.K = 1.0;
 #pragma unroll
@@ -787,7 +775,8 @@ __global__ __launch_bounds__(kBlock, 2) void born_beam_kernel(CastArgs a, float*
         int I[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) I[d] = (int)floor(v[d]);
-        const int L = F.leaf(g, I);
+        int id;
+        const int L = walk_to_leaf<AMR>(g, I, id);
         if (L < 0) { status = MPATH_RAY_LEFT_DOMAIN; break; }
         B.at_step(a, geo, y, L);
         if (chi >= chis) { status = MPATH_RAY_REACHED; break; }
@@ -808,7 +797,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_order_kernel(CastArgs a)
     if (r >= a.n_rays) return;
     using FC = typename std::conditional<ORDER == 0, NgpCache<AMR>, TscCache<AMR>>::type;
     RayRun<AMR, FC> R;
-    R.F.bind(order_lds + threadIdx.x);
+    R.F.bind(order_lds);
     R.start(a, r);
     R.advance(a, 0x7fffffff);
     R.finish(a);
@@ -936,10 +925,8 @@ struct TangentPair {
         float JG[3][3];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const float* q = F.c + 8 * (j + 1) * FC::cstride;
-            const float c1 = q[FC::cstride], c2 = q[2 * FC::cstride], c3 = q[3 * FC::cstride];
-            const float c4 = q[4 * FC::cstride], c5 = q[5 * FC::cstride], c6 = q[6 * FC::cstride];
-            const float c7 = q[7 * FC::cstride];
+            const float4 lo = F.quad(j, 0), hi = F.quad(j, 1);
+            const float c1 = lo.y, c2 = lo.z, c3 = lo.w, c4 = hi.x, c5 = hi.y, c6 = hi.z, c7 = hi.w;
             JG[j][0] = (c1 + ty * c4 + tz * c5 + ty * tz * c7) * sc;
             JG[j][1] = (c2 + tx * c4 + tz * c6 + tx * tz * c7) * sc;
             JG[j][2] = (c3 + tx * c5 + ty * c6 + tx * ty * c7) * sc;
@@ -1014,7 +1001,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, Tan
     const int64_t r = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (r >= a.n_rays) return;
     RayRun<AMR> R;
-    R.F.bind(coef_lds + threadIdx.x);
+    R.F.bind(coef_lds);
     R.start(a, r);
     TangentPair T;
     T.init(a, R.geo, R.phi_o);
@@ -1102,11 +1089,12 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
         t[d] = u - floor(u);
     }
     const float4* rec = g.dual + 8 * (int64_t)T.base;
-    double cf[4][8];
+    double cf[4][8];             // phi, gx, gy, gz
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
         const float4 c4 = rec[o];
-        cf[0][o] = c4.x; cf[1][o] = c4.y; cf[2][o] = c4.z; cf[3][o] = c4.w;
+        double* q = cf[(o / 2 + 1) & 3] + 4 * (o & 1);
+        q[0] = c4.x; q[1] = c4.y; q[2] = c4.z; q[3] = c4.w;
     }
     auto tri = [&](const double* c, double& f, double& fx, double& fy, double& fz) {
         const double tx = t[0], ty = t[1], tz = t[2];
@@ -1176,7 +1164,7 @@ hipError_t launch_cast_checkpointed(const CastArgs& a, hipStream_t s)
 {
     if (a.n_rays == 0) return hipSuccess;
     const int64_t blocks = (a.n_rays + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)32 * kBlock * sizeof(float);
+    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
         hipLaunchKernelGGL(cast_ckpt_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), lds, s, a);
     else
@@ -1188,7 +1176,7 @@ hipError_t launch_cast_infbeam(const CastArgs& a, float* A, hipStream_t s)
 {
     if (a.n_rays == 0) return hipSuccess;
     const int64_t blocks = (a.n_rays + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)64 * kBlock * sizeof(float);
+    const size_t lds = (size_t)2 * FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
         hipLaunchKernelGGL(cast_infbeam_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), lds, s, a, A);
     else
@@ -1200,7 +1188,7 @@ hipError_t launch_cast_tangent(const CastArgs& a, TanEnd* te, hipStream_t s)
 {
     if (a.n_rays == 0) return hipSuccess;
     const int64_t blocks = (a.n_rays + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)32 * kBlock * sizeof(float);
+    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
         hipLaunchKernelGGL(cast_tangent_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), lds, s, a, te);
     else
@@ -1238,7 +1226,7 @@ hipError_t launch_born_beam(const CastArgs& a, float* A, int32_t* status, hipStr
 {
     if (a.n_rays == 0) return hipSuccess;
     const int64_t blocks = (a.n_rays + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)32 * kBlock * sizeof(float);
+    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
         hipLaunchKernelGGL(born_beam_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), lds, s, a, A, status);
     else
@@ -1250,7 +1238,7 @@ hipError_t launch_cast_surfaces(const CastArgs& a, const double2* surf, int n_ex
 {
     if (a.n_rays == 0) return hipSuccess;
     const int64_t blocks = (a.n_rays + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)32 * kBlock * sizeof(float);
+    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     Surfaces S;
     S.surf = surf;
     S.n_extra = n_extra;
@@ -1291,7 +1279,7 @@ hipError_t launch_cast_diff(const CastArgs& a, hipStream_t s)
 {
     if (a.n_rays == 0) return hipSuccess;
     const dim3 grid((unsigned)((a.n_rays + kBlock - 1) / kBlock)), blk(kBlock);
-    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
+    const size_t lds = (size_t)FieldCache<true, false, true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0) hipLaunchKernelGGL(cast_diff_kernel<true>, grid, blk, lds, s, a);
     else hipLaunchKernelGGL(cast_diff_kernel<false>, grid, blk, lds, s, a);
     return hipGetLastError();

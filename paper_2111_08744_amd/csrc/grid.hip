@@ -14,26 +14,28 @@ namespace {
 // The build kernels take the positions of the cells [c0, c0 + m) as a chunk
 // pos[0 .. m) = (i, j, k, level) staged by the host.
 
-__device__ __forceinline__ void dual_record(const GridDev& g, int l, int i, int j, int k, float4* __restrict__ out)
-{
-    float4 v[8], coef[8];
-#pragma unroll
-    for (int o = 0; o < 8; ++o) {
-        const int id = lookup_cell(g, l, i + (o & 1), j + ((o >> 1) & 1), k + (o >> 2));
-        v[o] = id >= 0 ? g.payload[id] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    trilinear_coefficients(v, coef);
-#pragma unroll
-    for (int o = 0; o < 8; ++o) out[o] = coef[o];
-}
-
+// The record of every cell, and the mark kWholeLeaf in the child link of a
+// cell whose record's 8 cells are all leaves (of its own level).  Other
+// threads may read that link meanwhile; -1 and the mark are both negative,
+// and only the sign is read here.
 __global__ void build_dual_kernel(GridDev g, const int4* __restrict__ pos, int64_t c0, int64_t m,
-                                  float4* __restrict__ dual)
+                                  float4* __restrict__ dual, int32_t* child)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= m) return;
     const int4 p = pos[t];
-    dual_record(g, p.w, p.x, p.y, p.z, dual + 8 * (c0 + t));
+    float4 v[8], rec[8];
+    bool whole = true;
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        const int id = lookup_cell(g, p.w, p.x + (o & 1), p.y + ((o >> 1) & 1), p.z + (o >> 2));
+        v[o] = id >= 0 ? g.payload[id] : make_float4(0.f, 0.f, 0.f, 0.f);
+        whole = whole && id >= 0 && g.child[id] < 0;
+    }
+    stencil_record(v, rec);
+#pragma unroll
+    for (int o = 0; o < 8; ++o) dual[8 * (c0 + t) + o] = rec[o];
+    if (whole) child[c0 + t] = kWholeLeaf;
 }
 
 // The same record from the stored cell ids of each stencil (ids[8 c + o],
@@ -43,15 +45,15 @@ __global__ void rebuild_dual_kernel(GridDev g, const int32_t* __restrict__ ids, 
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
-    float4 v[8], coef[8];
+    float4 v[8], rec[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
         const int id = ids[8 * c + o];
         v[o] = id >= 0 ? g.payload[id] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    trilinear_coefficients(v, coef);
+    stencil_record(v, rec);
 #pragma unroll
-    for (int o = 0; o < 8; ++o) dual[8 * c + o] = coef[o];
+    for (int o = 0; o < 8; ++o) dual[8 * c + o] = rec[o];
 }
 
 // The same record for dPhi/deta (a time-dependent potential): the 8
@@ -63,15 +65,15 @@ __global__ void build_tdual_kernel(GridDev g, const int4* __restrict__ pos, int6
     if (t >= m) return;
     const int64_t c = c0 + t;
     const int4 p = pos[t];
-    float4 v[8], coef[8];
+    float4 v[8], rec[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
         const int id = lookup_cell(g, p.w, p.x + (o & 1), p.y + ((o >> 1) & 1), p.z + (o >> 2));
         v[o] = make_float4(id >= 0 ? tpay[id] : 0.f, 0.f, 0.f, 0.f);
     }
-    trilinear_coefficients(v, coef);
-    tdual[2 * c] = make_float4(coef[0].x, coef[1].x, coef[2].x, coef[3].x);
-    tdual[2 * c + 1] = make_float4(coef[4].x, coef[5].x, coef[6].x, coef[7].x);
+    stencil_record(v, rec);
+    tdual[2 * c] = rec[6];
+    tdual[2 * c + 1] = rec[7];
 }
 
 // Stencil of every half-cell of the refined cells (level >= 1; row
@@ -131,10 +133,11 @@ hipError_t launch_build_dual_ids(const GridDev& g, const int4* pos, int64_t c0, 
     return hipGetLastError();
 }
 
-hipError_t launch_build_dual(const GridDev& g, const int4* pos, int64_t c0, int64_t m, float4* dual, hipStream_t s)
+hipError_t launch_build_dual(const GridDev& g, const int4* pos, int64_t c0, int64_t m, float4* dual, int32_t* child,
+                             hipStream_t s)
 {
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(build_dual_kernel, blocks_for(m), dim3(256), 0, s, g, pos, c0, m, dual);
+    hipLaunchKernelGGL(build_dual_kernel, blocks_for(m), dim3(256), 0, s, g, pos, c0, m, dual, child);
     return hipGetLastError();
 }
 

@@ -30,7 +30,8 @@ struct ObsDev {
 // Two derived tables make a stencil one 128-byte read:
 //   dual[c]      the trilinear coefficients c0..c7 (see device.h) of the
 //                payloads of the 8 cells (l, ijk(c) + {0,1}^3) of c's level
-//                (zeros where such a cell does not exist);
+//                (zeros where such a cell does not exist), component by
+//                component (gx, gy, gz, phi);
 //   leafinfo[c - level_start[1]]  for a leaf c of level L >= 1 and each
 //                half-cell q of it (the
 //                8 sub-octants, q = qx + 2 qy + 4 qz), the id of the lowest
@@ -41,7 +42,7 @@ constexpr int kMaxLevels = 11;
 
 struct GridDev {
     const float4* payload;    // (phi, gx, gy, gz) per cell
-    const int32_t* child;     // first child id, -1 for a leaf
+    const int32_t* child;     // first child id, negative for a leaf (-1, or kWholeLeaf of device.h)
     const float4* dual;       // [n][8]
     const int32_t* leafinfo;  // [n - level_start[1]][8]: rows of the refined cells only
     const int32_t* dual_ids;  // [n][8] ids of the 8 cells of dual[c] (-1: missing); null
@@ -58,13 +59,14 @@ struct GridDev {
     int32_t level_start[kMaxLevels + 1];
 };
 
-// Conformal Hubble rate a'/a tabulated with its eta-derivative on a uniform
-// eta grid, for cubic Hermite interpolation.
+// Conformal Hubble rate a'/a (cubic Hermite interpolation on a uniform eta
+// grid, tabulated as each interval's coefficients) and scale factor (nodes).
 struct CosmoDev {
-    const double2* table;     // (H, dH/deta) at eta_lo + i * deta
-    const double2* atable;    // (a, da/deta) at the same nodes
+    const double2* cubic;     // [n - 1][2]: coefficients c0..c3 of H on interval i (see HubbleCubic)
+    const double2* atable;    // (a, da/deta) at the nodes eta_lo + i * deta
     double eta_lo;
     double inv_deta;
+    double eta_off;           // -eta_lo / deta: position in the table = eta inv_deta + eta_off
     double deta;
     int32_t n;
     int32_t is_static;
@@ -176,7 +178,8 @@ hipError_t launch_permute_values(float4* payload, const int64_t* perm, const flo
                                  int64_t n, hipStream_t s);
 // Derived tables (defined in grid.hip), built for the cells [c0, c0 + m)
 // from their positions pos[0 .. m) = (i, j, k, level) (a staged chunk).
-hipError_t launch_build_dual(const GridDev& g, const int4* pos, int64_t c0, int64_t m, float4* dual, hipStream_t s);
+hipError_t launch_build_dual(const GridDev& g, const int4* pos, int64_t c0, int64_t m, float4* dual, int32_t* child,
+                             hipStream_t s);
 hipError_t launch_rebuild_dual(const GridDev& g, const int32_t* ids, float4* dual, int64_t n, hipStream_t s);
 hipError_t launch_build_tdual(const GridDev& g, const int4* pos, int64_t c0, int64_t m, const float* tpay,
                               float4* tdual, hipStream_t s);

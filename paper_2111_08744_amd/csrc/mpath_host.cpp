@@ -165,8 +165,8 @@ struct mpath_grid {
     int32_t* leafinfo = nullptr;  // rows of the refined cells (ids >= level_start[1])
     int64_t* perm = nullptr;      // auxiliary tables (null without them)
     int32_t* dual_ids = nullptr;
-    double2* table = nullptr;
-    double2* atable = nullptr;    // (a, da/deta) on the nodes of table
+    double2* cubic = nullptr;     // a'/a: cubic coefficients per interval of the eta table
+    double2* atable = nullptr;    // (a, da/deta) on its nodes
     float phi_max = INFINITY;     // largest payload phi (+inf after set_values)
     float* tpay = nullptr;        // dPhi/deta per cell (time-dependent potential), else null
     float4* tdual = nullptr;      // its 8 trilinear coefficients per stencil base
@@ -200,7 +200,7 @@ GridLayout grid_layout(int64_t n, int64_t n_coarse, bool time_dep)
     L.off_dual = align_up(L.off_child + (size_t)n * 4, 256);
     L.off_leafinfo = align_up(L.off_dual + (size_t)n * 128, 256);
     L.off_table = align_up(L.off_leafinfo + (size_t)n_ref * 32, 256);
-    L.off_atable = align_up(L.off_table + (size_t)kTableN * 16, 256);
+    L.off_atable = align_up(L.off_table + (size_t)kTableN * 32, 256);
     L.off_tpay = align_up(L.off_atable + (size_t)kTableN * 16, 256);
     L.off_tdual = align_up(L.off_tpay + (time_dep ? (size_t)n * 4 : 0), 256);
     L.off_stage = align_up(L.off_tdual + (time_dep ? (size_t)n * 32 : 0), 256);
@@ -521,19 +521,27 @@ int mpath_grid_build_with_aux(const mpath_grid_desc* d, const mpath_cosmo* cosmo
     for (int64_t i = 0; i < n; ++i) G->phi_max = std::max(G->phi_max, payload[i].x);
     G->bg.init(cosmo->omega_m, cosmo->omega_l);
     G->eta0 = G->bg.is_static ? 0.0 : G->bg.eta0();
-    std::vector<double2> table(kTableN, make_double2(0.0, 0.0));
+    std::vector<double2> cubic(2 * kTableN, make_double2(0.0, 0.0));
     std::vector<double2> atable(kTableN, make_double2(1.0, 0.0));
     if (!G->bg.is_static) {
         const double lo = G->bg.eta_of_a(1.0 / (1.0 + kZMaxTable)) - 50.0;
         const double hi = G->eta0 + 50.0;
         G->table_eta_lo = lo;
         G->table_deta = (hi - lo) / (kTableN - 1);
+        std::vector<double2> node(kTableN);     // (H, dH/deta)
         for (int i = 0; i < kTableN; ++i) {
             const double a = G->bg.a_of_eta(lo + i * G->table_deta);
             double H, dH;
             G->bg.hubble(a, H, dH);
-            table[i] = make_double2(H, dH);
+            node[i] = make_double2(H, dH);
             atable[i] = make_double2(a, a * H);
+        }
+        // Hermite cubic on each interval, in the position tau in it
+        for (int i = 0; i + 1 < kTableN; ++i) {
+            const double d = G->table_deta, dy = node[i + 1].x - node[i].x;
+            const double s0 = node[i].y, s1 = node[i + 1].y;
+            cubic[2 * i] = make_double2(node[i].x, d * s0);
+            cubic[2 * i + 1] = make_double2(3.0 * dy - d * (2.0 * s0 + s1), d * (s0 + s1) - 2.0 * dy);
         }
     }
     // ---- upload ----
@@ -555,7 +563,7 @@ int mpath_grid_build_with_aux(const mpath_grid_desc* d, const mpath_cosmo* cosmo
     G->child = (int32_t*)(G->ws + lay.off_child);
     G->dual = (float4*)(G->ws + lay.off_dual);
     G->leafinfo = (int32_t*)(G->ws + lay.off_leafinfo);
-    G->table = (double2*)(G->ws + lay.off_table);
+    G->cubic = (double2*)(G->ws + lay.off_table);
     G->atable = (double2*)(G->ws + lay.off_atable);
     if (time_dep) {
         G->tpay = (float*)(G->ws + lay.off_tpay);
@@ -572,7 +580,7 @@ int mpath_grid_build_with_aux(const mpath_grid_desc* d, const mpath_cosmo* cosmo
     if ((e = hipMemcpyAsync(G->payload, payload.data(), (size_t)n * 16, hipMemcpyHostToDevice, s)) ||
         (e = hipMemcpyAsync(G->child, child.data(), (size_t)n * 4, hipMemcpyHostToDevice, s)) ||
         (aux && (e = hipMemcpyAsync(G->perm, perm.data(), (size_t)n * 8, hipMemcpyHostToDevice, s))) ||
-        (e = hipMemcpyAsync(G->table, table.data(), (size_t)kTableN * 16, hipMemcpyHostToDevice, s)) ||
+        (e = hipMemcpyAsync(G->cubic, cubic.data(), (size_t)kTableN * 32, hipMemcpyHostToDevice, s)) ||
         (e = hipMemcpyAsync(G->atable, atable.data(), (size_t)kTableN * 16, hipMemcpyHostToDevice, s)) ||
         (time_dep && (e = hipMemcpyAsync(G->tpay, tpay.data(), (size_t)n * 4, hipMemcpyHostToDevice, s)))) {
         delete G;
@@ -584,7 +592,7 @@ int mpath_grid_build_with_aux(const mpath_grid_desc* d, const mpath_cosmo* cosmo
         const int64_t m = std::min(lay.stage_cells, n - c0);
         const int64_t r0 = std::max(c0, nc);      // first refined cell of the chunk
         (void)((e = hipMemcpyAsync(stage, cellpos.data() + c0, (size_t)m * 16, hipMemcpyHostToDevice, s)) ||
-               (e = launch_build_dual(gd, stage, c0, m, G->dual, s)) ||
+               (e = launch_build_dual(gd, stage, c0, m, G->dual, G->child, s)) ||
                (r0 < c0 + m && (e = launch_build_leafinfo(gd, stage + (r0 - c0), r0, c0 + m - r0, G->leafinfo, s))) ||
                (aux && (e = launch_build_dual_ids(gd, stage, c0, m, G->dual_ids, s))) ||
                (time_dep && (e = launch_build_tdual(gd, stage, c0, m, G->tpay, G->tdual, s))));
@@ -824,12 +832,13 @@ CastArgs make_cast_args(const mpath_grid* g, const mpath_cast_desc* d, const Cas
     CastArgs a;
     std::memset(&a, 0, sizeof a);
     a.grid = make_griddev(g);
-    a.cosmo.table = g->table;
+    a.cosmo.cubic = g->cubic;
     a.cosmo.atable = g->atable;
     a.surface = d->stop_surface;
     a.cosmo.eta_lo = g->table_eta_lo;
     a.cosmo.deta = g->table_deta;
     a.cosmo.inv_deta = g->table_deta > 0 ? 1.0 / g->table_deta : 0.0;
+    a.cosmo.eta_off = -g->table_eta_lo * a.cosmo.inv_deta;
     a.cosmo.n = kTableN;
     a.cosmo.is_static = g->bg.is_static ? 1 : 0;
     a.cosmo_eta0 = g->eta0;
