@@ -28,6 +28,22 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nblocks)
     return x < r ? x * (q + 1) + idx : r * (q + 1) + (x - r) * q + idx;
 }
 
+// Ray of this lane in the one-ray-per-lane launches: every wave takes a.lanes
+// (a power of two) consecutive rays; its other lanes, and those past the last
+// ray, run copies of them, which write the same values to the same places.
+// (A wave that masks them off instead, with 8 lanes or fewer active and the
+// SIMD to itself, was measured to run at half the speed.)  False for a wave
+// without rays.
+__device__ __forceinline__ bool lane_ray(const CastArgs& a, int64_t& r)
+{
+    const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    r = wave * a.lanes;
+    if (r >= a.n_rays) return false;
+    r += threadIdx.x & (a.lanes - 1);
+    if (r >= a.n_rays) r = a.n_rays - 1;
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // HEALPix NESTED pixel centre (Gorski et al. 2005; Sect. 2.4 starts one photon
 // at every pixel centre).  Within base face f the nested index interleaves

@@ -129,6 +129,8 @@ struct CastArgs {
                                       // kernels read it through step_length()
     int64_t max_steps;
     int64_t n_rays;
+    int32_t simds;               // SIMDs of the GPU
+    int32_t lanes;               // rays per wave of a launch (set by its launcher; see spread_rays)
     OutDev out;
     unsigned long long* queue;   // persistent schedule: next ray to hand out
     int32_t batch;               // steps between queue refills
@@ -163,7 +165,7 @@ inline int64_t grad_accumulator_floats(int64_t n) { return 4 * (((n + 7) >> 3) <
 // Kernel launchers (defined in cast.hip).
 hipError_t launch_cast_stop(const CastArgs& a, hipStream_t s);
 hipError_t launch_cast_diff(const CastArgs& a, hipStream_t s);
-hipError_t launch_cast_static(const CastArgs& a, int block, hipStream_t s);
+hipError_t launch_cast_static(const CastArgs& a, hipStream_t s);
 hipError_t launch_cast_persistent(const CastArgs& a, int block, int blocks, hipStream_t s);
 hipError_t launch_observables(const CastArgs& a, hipStream_t s);
 hipError_t launch_ray_dirs(const CastArgs& a, hipStream_t s);

@@ -851,6 +851,8 @@ CastArgs make_cast_args(const mpath_grid* g, const mpath_cast_desc* d, const Cas
         a.ds_level[l] = (g->box / g->n0) / (double)(1 << (a.adaptive ? l : 0)) / (double)d->steps_per_cell;
     a.max_steps = std::min<int64_t>(d->max_steps, INT32_MAX);   // steps are counted in 32 bits
     a.n_rays = n_rays;
+    a.simds = 4 * (g->num_cus > 0 ? g->num_cus : 256);
+    a.lanes = 64;
     a.queue = (unsigned long long*)(ws + lay.off_queue);
     a.ends = (RayEnd*)(ws + lay.off_ends);
     a.dirs = (double*)(ws + lay.off_dirs);
@@ -1055,7 +1057,7 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
         if (sched == MPATH_SCHED_AUTO) sched = d->n_obs > 1 ? MPATH_SCHED_PERSISTENT : MPATH_SCHED_STATIC;
         const int block = d->block_size ? d->block_size : 256;
         if (sched == MPATH_SCHED_STATIC) {
-            e = launch_cast_static(a, block, s);
+            e = launch_cast_static(a, s);
         } else {
             int wpc = d->waves_per_cu;
             if (wpc <= 0)
