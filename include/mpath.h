@@ -532,10 +532,11 @@ int mpath_infinitesimal_beam(const mpath_grid* grid, const mpath_cast_desc* desc
  * (e1, e2) = (e_phi, -e_theta) and normalised.  The first identity_iters
  * iterations take A = I (plain casts, as the paper does), later ones the
  * exact distortion matrix of mpath_adjoint (a checkpointed cast and a
- * Jacobian sweep).  A source stops iterating when the angle between beta_i
- * and beta is below tol.  At the end every source is cast once more along
- * its theta (checkpointed) and, when requested, its exact A and dz5/dtheta
- * are computed there. */
+ * Jacobian sweep over the sources that have to move).  A source stops
+ * iterating when the angle between beta_i and beta is below tol.  At the end
+ * every source is cast once more along its theta and, when requested, its
+ * exact A and dz5/dtheta there come from that cast's tangents
+ * (mpath_cast_jacobian). */
 typedef struct {
     const double* obs_pos;      /* HOST [3] observer position                            */
     int64_t n_src;
@@ -580,8 +581,8 @@ typedef struct {
     double* z1;                 /* z0 + (1 + z0)(Phi_o - Phi_s)                                      */
 } mpath_finder_out;
 
-/* Workspace: the checkpointed cast and Jacobian sweep of n_src rays plus
- * per-source tables (88 bytes per source). */
+/* Workspace: the checkpointed cast, Jacobian sweep and tangents (80 bytes per
+ * source) of n_src rays plus per-source tables (80 bytes per source). */
 int mpath_find_geodesics_workspace_bytes(const mpath_grid* grid, const mpath_finder_desc* desc, size_t* bytes);
 /* Synchronises the stream once per iteration and grid round (the count of
  * sources still iterating decides whether to continue).  Errors:

@@ -865,9 +865,10 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
         T.bind(lds + (FieldCache<AMR>::kFloats + 4 * StageRecord::kWords + kPendWords) * kBlock + (threadIdx.x >> 6) * kTabWords);
         T.clear(threadIdx.x & 63);
     }
-    const int64_t ray = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    const int64_t at = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const CastArgs& a = A.c;
-    if (ray >= a.n_rays) return;
+    if (at >= A.n_list) return;
+    const int64_t ray = A.list ? A.list[at] : at;
     constexpr bool HAS_JAC = W >= 3;
     const int N = A.n_steps[ray];
     if (A.status[ray] != MPATH_RAY_REACHED || N <= 0) {
@@ -1060,7 +1061,7 @@ __global__ void central_transpose_kernel(const float* __restrict__ g_lib, const 
 
 hipError_t launch_adjoint(const AdjointArgs& A, int columns, hipStream_t s)
 {
-    const int64_t n = A.c.n_rays;
+    const int64_t n = A.n_list;
     if (n == 0) return hipSuccess;
     const dim3 grid((unsigned)((n + kBlock - 1) / kBlock)), block(kBlock);
     const size_t lds_cache = (size_t)(FieldCache<true>::kFloats + 4 * StageRecord::kWords) * kBlock * sizeof(float);

@@ -38,6 +38,24 @@ __device__ inline double end_direction(const RayEnd& e, const double th[3], doub
     return atan2(sqrt(dot3(c, c)), dot3(b, t));
 }
 
+// The sources that finder_update_kernel will move: their rays' indices to
+// list (in any order) and their number to *active.
+__global__ __launch_bounds__(256) void finder_list_kernel(int64_t n, const RayEnd* __restrict__ ends,
+                                                          const double* __restrict__ target,
+                                                          const int32_t* __restrict__ status, double eta0, double tol,
+                                                          const double* __restrict__ theta,
+                                                          const int32_t* __restrict__ n_iter,
+                                                          int32_t* __restrict__ list,
+                                                          unsigned int* __restrict__ active)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n || n_iter[i] != -1 || status[i] != MPATH_RAY_REACHED) return;
+    const double t[3] = {target[3 * i], target[3 * i + 1], target[3 * i + 2]};
+    const double th[3] = {theta[3 * i], theta[3 * i + 1], theta[3 * i + 2]};
+    double b[3];
+    if (!(end_direction(ends[i], th, eta0, t, b) < tol)) list[atomicAdd(active, 1u)] = (int32_t)i;
+}
+
 // One Newton step for every source still iterating (n_iter == -1): a ray
 // that did not reach its source stops the iteration (-2); a ray within tol
 // of its target converges at iteration it; the others move theta and are
@@ -195,6 +213,17 @@ __global__ void zero_u32_kernel(unsigned int* p) { *p = 0u; }
 inline dim3 blocks_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
 }  // namespace
+
+hipError_t launch_finder_list(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
+                              double tol, const double* theta, const int32_t* n_iter, int32_t* list,
+                              unsigned int* active, hipStream_t s)
+{
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(1), 0, s, active);
+    hipLaunchKernelGGL(finder_list_kernel, blocks_for(n), dim3(256), 0, s, n, ends, target, status, eta0, tol, theta,
+                       n_iter, list, active);
+    return hipGetLastError();
+}
 
 hipError_t launch_finder_update(int64_t n, const RayEnd* ends, const double* target, const int32_t* status,
                                 const float* jac, double eta0, double tol, int it, double* theta, int32_t* n_iter,

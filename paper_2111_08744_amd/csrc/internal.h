@@ -148,6 +148,8 @@ struct CastArgs {
 struct AdjointArgs {
     CastArgs c;                  // the cast that stored the checkpoints
     GeoState* tape;              // [ckpt_every][n_rays] step states of one segment
+    const int32_t* list;         // the rays to sweep, or NULL: all
+    int64_t n_list;              // their number
     const int32_t* n_steps;      // forward outputs
     const int32_t* status;
     const float* dL_dalpha;      // [n_rays][2] or NULL
@@ -211,6 +213,9 @@ hipError_t launch_beam_dirs(const BeamObs* obs, int n_obs, int nside, const doub
 hipError_t launch_finite_beam(const BeamObs* obs, int n_obs, const RayEnd* ends, const double* dirs5,
                               const int32_t* status5, double eta0, double tan_eps, int64_t n_rays, float* A,
                               int32_t* status, hipStream_t s);
+hipError_t launch_finder_list(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
+                              double tol, const double* theta, const int32_t* n_iter, int32_t* list,
+                              unsigned int* active, hipStream_t s);
 hipError_t launch_finder_update(int64_t n, const RayEnd* ends, const double* target, const int32_t* status,
                                 const float* jac, double eta0, double tol, int it, double* theta, int32_t* n_iter,
                                 double* sep, unsigned int* active, hipStream_t s);

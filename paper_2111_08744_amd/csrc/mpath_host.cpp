@@ -10,6 +10,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -127,12 +128,13 @@ struct Background {
     double a_of_eta(double eta) const
     {
         if (is_static) return 1.0;
-        // matter-dominated start: eta = 2 y / (H0 sqrt(Om))
+        // matter-dominated start: eta = 2 y / (H0 sqrt(Om)).  The iteration
+        // converges quadratically: the step after one below 1e-9 is rounding.
         double y = 0.5 * kH0 * std::sqrt(om) * eta;
         for (int it = 0; it < 60; ++it) {
             const double dy = (eta_of_y(y) - eta) / deta_dy(y);
             y -= dy;
-            if (std::fabs(dy) <= 1e-16 * y) break;
+            if (std::fabs(dy) <= 1e-9 * y) break;
         }
         return y * y;
     }
@@ -240,9 +242,14 @@ void parallel_ranges(int64_t n, F fn, int64_t min_per_thread = (int64_t)1 << 16)
         return;
     }
     std::vector<std::thread> th;
+    th.reserve(T);
     for (int t = 0; t < T; ++t) {
         const int64_t a = n * t / T, b = n * (t + 1) / T;
-        th.emplace_back([=, &fn] { fn(a, b); });
+        try {
+            th.emplace_back([=, &fn] { fn(a, b); });
+        } catch (const std::system_error&) {    // no thread to be had: the range runs here
+            fn(a, b);
+        }
     }
     for (auto& x : th) x.join();
 }
@@ -1233,7 +1240,8 @@ namespace {
 
 int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_observables* fwd,
                  const void* cast_ws, size_t cast_ws_bytes, const mpath_adjoint_desc* ad, void* dev_ws,
-                 size_t ws_bytes, void* stream, const double2* ray_stop)
+                 size_t ws_bytes, void* stream, const double2* ray_stop = nullptr, const int32_t* list = nullptr,
+                 int64_t n_list = 0)
 {
     int64_t n_rays;
     std::vector<ObsDev> obs;
@@ -1263,6 +1271,8 @@ int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obse
     std::memset(&A, 0, sizeof A);
     A.c = make_cast_args(g, d, lay, (char*)cast_ws, n_rays);
     A.c.ray_stop = ray_stop;
+    A.list = list;
+    A.n_list = list ? n_list : n_rays;
     A.tape = (GeoState*)(ws + al.off_tape);
     A.n_steps = fwd->n_steps;
     A.status = fwd->status;
@@ -1293,7 +1303,7 @@ int mpath_adjoint(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obs
                   const void* cast_ws, size_t cast_ws_bytes, const mpath_adjoint_desc* ad, void* dev_ws,
                   size_t ws_bytes, void* stream)
 {
-    return adjoint_impl(g, d, fwd, cast_ws, cast_ws_bytes, ad, dev_ws, ws_bytes, stream, nullptr);
+    return adjoint_impl(g, d, fwd, cast_ws, cast_ws_bytes, ad, dev_ws, ws_bytes, stream);
 }
 
 }  // extern "C"
@@ -1541,7 +1551,8 @@ struct FinderPlan {
     int64_t count = 0;
     mpath_cast_desc cd;
     size_t off_stop = 0, off_target = 0, off_iter = 0, off_status = 0, off_sep = 0, off_jac = 0, off_nsteps = 0,
-           off_active = 0, off_cast = 0, off_adj = 0, cast_bytes = 0, adj_bytes = 0, total = 0;
+           off_list = 0, off_active = 0, off_cast = 0, off_adj = 0, off_tan = 0, cast_bytes = 0, adj_bytes = 0,
+           total = 0;
     CastLayout lay;
     // grid search: at most m_max sources, g x g candidates each
     int64_t m_max = 0, gcount = 0;
@@ -1574,6 +1585,7 @@ int finder_plan(const mpath_grid* g, const mpath_finder_desc* f, FinderPlan& P, 
         P.stop.resize(P.n);
         P.target.resize(3 * P.n);
     }
+    std::vector<double> chi_of(tables ? P.n : 0);
     P.chi_max = 0.0;
     for (int64_t i = 0; i < P.n; ++i) {
         double r[3];
@@ -1584,10 +1596,19 @@ int finder_plan(const mpath_grid* g, const mpath_finder_desc* f, FinderPlan& P, 
         if (eta_s < eta_min) return fail(MPATH_ERR_UNSUPPORTED, "a source lies beyond the background table (z > 20)");
         P.chi_max = std::max(P.chi_max, chi);
         if (tables) {
-            P.stop[i] = make_double2(eta_s, g->bg.a_of_eta(eta_s));
+            chi_of[i] = chi;
             for (int k = 0; k < 3; ++k) P.target[3 * i + k] = r[k] / chi;
         }
     }
+    // the scale factor of every source's surface (a Newton iteration on a
+    // quadrature each)
+    if (tables)
+        parallel_ranges(P.n, [&](int64_t i0, int64_t i1) {
+            for (int64_t i = i0; i < i1; ++i) {
+                const double eta_s = g->eta0 - chi_of[i];
+                P.stop[i] = make_double2(eta_s, g->bg.a_of_eta(eta_s));
+            }
+        }, 256);
     P.count = P.n;
     std::memset(&P.cd, 0, sizeof P.cd);
     P.cd.n_obs = 1;
@@ -1615,12 +1636,14 @@ int finder_plan(const mpath_grid* g, const mpath_finder_desc* f, FinderPlan& P, 
     P.off_sep = align_up(P.off_status + n * 4, 256);
     P.off_jac = align_up(P.off_sep + n * 8, 256);
     P.off_nsteps = align_up(P.off_jac + n * 16, 256);
-    P.off_active = align_up(P.off_nsteps + n * 4, 256);
+    P.off_list = align_up(P.off_nsteps + n * 4, 256);
+    P.off_active = align_up(P.off_list + n * 4, 256);
     P.off_cast = align_up(P.off_active + 256, 256);
     P.cast_bytes = P.lay.total;
     P.off_adj = align_up(P.off_cast + P.cast_bytes, 256);
     P.adj_bytes = adjoint_layout(g, &P.cd, P.n).total;
-    P.total = P.off_adj + P.adj_bytes;
+    P.off_tan = align_up(P.off_adj + P.adj_bytes, 256);
+    P.total = P.off_tan + n * sizeof(TanEnd);
     if (f->grid_rounds > 0 && P.n > 0) {
         P.g = f->grid_n;
         P.m_max = f->grid_max > 0 ? std::min<int64_t>(f->grid_max, P.n) : P.n;
@@ -1676,8 +1699,9 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
     int32_t* status = reinterpret_cast<int32_t*>(ws + P.off_status);
     double* sep = reinterpret_cast<double*>(ws + P.off_sep);
     float* jac = reinterpret_cast<float*>(ws + P.off_jac);
-    int32_t* nsteps = reinterpret_cast<int32_t*>(ws + P.off_nsteps);
     unsigned int* active = reinterpret_cast<unsigned int*>(ws + P.off_active);
+    int32_t* nsteps = reinterpret_cast<int32_t*>(ws + P.off_nsteps);
+    int32_t* list = reinterpret_cast<int32_t*>(ws + P.off_list);
     char* cws = ws + P.off_cast;
     char* aws = ws + P.off_adj;
     double* theta = out->theta;
@@ -1690,28 +1714,38 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
     if (e) return hip_fail_drain(e, s, "finder set-up");
     P.cd.dirs = theta;
     const RayEnd* ends = reinterpret_cast<const RayEnd*>(cws + P.lay.off_ends);
-    const int K = f->checkpoint_every;
+    // Every iteration casts all sources along their current theta.  From the
+    // first exact iteration on, the Jacobian sweep runs over the sources that
+    // still have to move, and only if there are any.
+    mpath_observables fo;
+    std::memset(&fo, 0, sizeof fo);
+    fo.status = status;
+    fo.n_steps = nsteps;
     for (int it = 0; it < f->max_iter; ++it) {
         const bool exact = it >= f->identity_iters;
-        P.cd.checkpoint_every = exact ? K : 0;
-        mpath_observables fo;
-        std::memset(&fo, 0, sizeof fo);
-        fo.status = status;
-        fo.n_steps = nsteps;
+        P.cd.checkpoint_every = exact ? f->checkpoint_every : 0;
         rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop);
         if (rc) return rc;
+        unsigned int left = 0;
         if (exact) {
-            mpath_adjoint_desc ad;
-            std::memset(&ad, 0, sizeof ad);
-            ad.jac = jac;
-            rc = adjoint_impl(g, &P.cd, &fo, cws, P.cast_bytes, &ad, aws, P.adj_bytes, stream, stop);
-            if (rc) return rc;
+            e = launch_finder_list(P.n, ends, target, status, g->eta0, f->tol, theta, n_iter, list, active, s);
+            if (!e) e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
+            if (!e) e = hipStreamSynchronize(s);
+            if (e) return hip_fail(e, "finder iteration");
+            if (left > 0) {
+                mpath_adjoint_desc ad;
+                std::memset(&ad, 0, sizeof ad);
+                ad.jac = jac;
+                rc = adjoint_impl(g, &P.cd, &fo, cws, P.cast_bytes, &ad, aws, P.adj_bytes, stream, stop, list, left);
+                if (rc) return rc;
+            }
         }
         e = launch_finder_update(P.n, ends, target, status, exact ? jac : nullptr, g->eta0, f->tol, it, theta,
                                  n_iter, sep, active, s);
-        unsigned int left = 0;
-        if (!e) e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
-        if (!e) e = hipStreamSynchronize(s);
+        if (!e && !exact) {
+            e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
+            if (!e) e = hipStreamSynchronize(s);
+        }
         if (e) return hip_fail(e, "finder iteration");
         if (left == 0) break;
     }
@@ -1764,26 +1798,19 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
             }
         }
     }
-    // final cast along theta, checkpointed for the distortion matrix there
-    P.cd.checkpoint_every = K;
-    mpath_observables fo;
-    std::memset(&fo, 0, sizeof fo);
-    fo.status = status;
-    fo.n_steps = nsteps;
+    // final cast along theta, with its tangents for the distortion matrix there
+    P.cd.checkpoint_every = 0;
     fo.z5 = out->z5;
     fo.z0 = out->z0;
     fo.z1 = out->z1;
     fo.phi_src = out->phi_src;
-    rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop);
+    TangentOut tg;
+    tg.ends = reinterpret_cast<TanEnd*>(ws + P.off_tan);
+    tg.jac = out->A;
+    tg.dz_dtheta = out->dz_dtheta;
+    rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop,
+                   out->A || out->dz_dtheta ? &tg : nullptr);
     if (rc) return rc;
-    if (out->A || out->dz_dtheta) {
-        mpath_adjoint_desc ad;
-        std::memset(&ad, 0, sizeof ad);
-        ad.jac = out->A;
-        ad.dz_dtheta = out->dz_dtheta;
-        rc = adjoint_impl(g, &P.cd, &fo, cws, P.cast_bytes, &ad, aws, P.adj_bytes, stream, stop);
-        if (rc) return rc;
-    }
     e = launch_finder_sep(P.n, ends, target, theta, status, g->eta0, out->sep ? out->sep : sep, s);
     if (!e && out->n_iter) e = hipMemcpyAsync(out->n_iter, n_iter, n * 4, hipMemcpyDeviceToDevice, s);
     if (!e && out->status) e = hipMemcpyAsync(out->status, status, n * 4, hipMemcpyDeviceToDevice, s);
