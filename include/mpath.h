@@ -387,11 +387,13 @@ int mpath_cast_jacobian(const mpath_grid* grid, const mpath_cast_desc* desc, mpa
 /* ---- reverse mode ----
  * The derivative of the discrete map that mpath_cast computes (RK4 on the
  * geodesic equations of Sect. 2.2 with CIC interpolation and the AMR level
- * fallback, step length h_leaf / N, landing on the iso-eta surface), by one
- * reverse sweep per ray over the checkpointed forward path: each segment of
- * K steps is recomputed from its checkpoint, then traversed backwards.  The
- * discrete decisions (leaf levels, stencils, landing) are those of the
- * forward cast and carry no derivative.
+ * fallback, step length h_leaf / N, landing on the iso-eta surface): the cell
+ * outputs by one reverse sweep per ray over the checkpointed forward path
+ * (each segment of K steps is recomputed from its checkpoint, then traversed
+ * backwards), the per-ray outputs by the tangents of mpath_cast_jacobian
+ * carried through the same cast once more.  The discrete decisions (leaf
+ * levels, stencils, landing) are those of the forward cast and carry no
+ * derivative.
  *
  * Per-ray outputs (DEVICE, length n_rays; NaN for rays whose status is not
  * MPATH_RAY_REACHED):
@@ -427,11 +429,11 @@ typedef struct {
 } mpath_adjoint_desc;
 
 /* Device workspace of mpath_adjoint for this desc (which needs
- * checkpoint_every > 0): K states per ray (40 B each) and 16 B per cell
- * (rounded up to a multiple of 8 cells). */
+ * checkpoint_every > 0): K states per ray (40 B each), 104 B per ray, and
+ * 16 B per cell (rounded up to a multiple of 8 cells). */
 int mpath_adjoint_workspace_bytes(const mpath_grid* grid, const mpath_cast_desc* desc, size_t* bytes);
 
-/* Reverse sweep after a checkpointed mpath_cast with the same grid (whose
+/* Derivatives after a checkpointed mpath_cast with the same grid (whose
  * values must not have changed since), the same desc and its workspace
  * cast_ws; fwd gives that cast's n_steps and status arrays (the other
  * fields are not read).  Asynchronous on the stream; cast_ws and the forward

@@ -305,9 +305,9 @@ def jacobian(grid: Grid, cfg: CastConfig, out=None, ws=None):
 
 def adjoint(grid: Grid, cfg: CastConfig, fwd, dL_dalpha=None, dL_dz=None, jacobian=False, cells=False,
             phi_total=False, ws=None):
-    """mpath_adjoint: reverse sweep over the checkpointed cast ``fwd`` (the
-    dict returned by ``cast`` with cfg.checkpoint_every > 0, on the same grid
-    values).
+    """mpath_adjoint: derivatives of the checkpointed cast ``fwd`` (the dict
+    returned by ``cast`` with cfg.checkpoint_every > 0, on the same grid
+    values): per ray by tangents, per cell by the reverse sweep.
 
     jacobian: return ``jac`` [n_rays, 2, 2] (A_ab = d beta_a / d theta_b) and
     ``dz_dtheta`` [n_rays, 2].  cells: return ``dL_dvalues`` [n_cells, 4],

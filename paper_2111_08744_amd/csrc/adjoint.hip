@@ -1,12 +1,12 @@
 // adjoint.hip -- reverse-mode derivative of the ray-casting map on gfx950.
 //
 // The forward cast (with checkpoints) stores every ray's state before steps
-// 0, K, 2K, ...  The adjoint kernel then runs, per ray, one reverse sweep:
-// segment by segment from the source back to the observer it recomputes the
-// steps of the segment from its checkpoint (the same code as the forward, so
-// every leaf level, stencil and landing decision is replayed exactly) into a
-// per-ray tape, and for every step in reverse order re-records the four RK4
-// stages and applies the transposed Jacobian of the step.
+// 0, K, 2K, ...  The reverse sweep then runs, per ray, segment by segment from
+// the source back to the observer: it recomputes the steps of the segment from
+// its checkpoint (the same code as the forward, so every leaf level, stencil
+// and landing decision is replayed exactly) into a per-ray tape, and for every
+// step in reverse order re-records the four RK4 stages and applies the
+// transposed Jacobian of the step.
 //
 // The derivative is that of the discrete map: classical RK4 on the null
 // geodesic equations of Sect. 2.2 with CIC interpolation (piecewise
@@ -19,16 +19,22 @@
 // per-stage products (stage Jacobians applied to small cotangent increments)
 // run in single precision, like the stage arithmetic of the forward.
 //
-// Cotangent columns (one reverse sweep carries all of them):
-//   beta_1, beta_2   e~_a(beta) . x / |x_s - x_obs|: their values at the
-//                    observer, contracted with d k / d theta_b, give the
-//                    distortion matrix A_ab = d beta_a / d theta_b (Sect. 2.3)
-//   z                the observed redshift z5 (Sect. 2.5): d z5 / d theta_b
-//   L                a scalar loss through the per-ray cotangents
-//                    (dL/dalpha, dL/dz5); its cotangents of the interpolated
-//                    (Phi, grad Phi) at every sub-step are scattered to the
-//                    cells with the CIC weights (dL/d cell values).
+// Cotangent columns:
+//   L                adjoint_loss_kernel: a scalar loss through the per-ray
+//                    cotangents (dL/dalpha, dL/dz5); its cotangents of the
+//                    interpolated (Phi, grad Phi) at every sub-step are
+//                    scattered to the cells with the CIC weights (dL/d cell
+//                    values)
+//   beta_1, beta_2, z   adjoint_kernel: e~_a(beta) . x / |x_s - x_obs| and the
+//                    redshift z5 (Sect. 2.5); their values at the observer,
+//                    contracted with d k / d theta_b, give the distortion
+//                    matrix A_ab = d beta_a / d theta_b (Sect. 2.3) and
+//                    d z5 / d theta_b.  Only the finder's Newton steps take
+//                    them so: three reverse columns cost ten forwards, the
+//                    two tangents of cast_tangent_kernel two.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "device.h"
 
@@ -85,11 +91,24 @@ struct StageData {
     int base, lvl;
 };
 
-// The four stages of one RK4 step, kept in this lane's LDS slots (the
-// forward's stage loop is not unrolled, so the stage index is a run-time
-// value, and the replay must run that same loop to reproduce the forward's
-// rounding bit for bit).  Word w of stage i is at p[(i * kWords + w) kBlock].
-struct StageRecord {
+struct RayCtx {
+    RayGeom geo;
+    double xobs[3];
+};
+
+// What the transposed stage Jacobian needs at one stage (single precision).
+struct Jet32 {
+    float k0, k[3];
+    float G[3];
+    float JG[3][3];     // dG_j / dx_l of the trilinear interpolant
+    float H, dH;        // a'/a and its eta-derivative
+    float t[3];         // CIC offsets (weights) at the stencil level
+    int base, lvl;
+};
+
+// The four stages of one RK4 step for the Jacobian sweep (three columns),
+// kept in this lane's LDS slots.  Word w of stage i is at p[(i * kWords + w) kBlock].
+struct LdsRecord {
     static constexpr int kWords = 18;
     float* p;
 
@@ -125,28 +144,6 @@ struct StageRecord {
         put(q, 17, __int_as_float(F.lvl));
     }
 
-    // After a stage's transposed Jacobian its gradient words are free: they
-    // take the loss cotangent of the interpolated gradient at that stage.
-    template <int I>
-    __device__ __forceinline__ void put_gbar(const float g[3]) const
-    {
-        float* q = p + I * kWords * kBlock;
-        put(q, 10, g[0]);
-        put(q, 11, g[1]);
-        put(q, 12, g[2]);
-    }
-    // stage i (run-time index): stencil base, offsets and the loss cotangent
-    __device__ __forceinline__ void scatter_data(int i, int& base, float t[3], float g[3]) const
-    {
-        const float* q = p + i * kWords * kBlock;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            g[k] = q[(10 + k) * kBlock];
-            t[k] = q[(13 + k) * kBlock];
-        }
-        base = __float_as_int(q[16 * kBlock]);
-    }
-
     template <int I>
     __device__ __forceinline__ StageData get() const
     {
@@ -165,11 +162,74 @@ struct StageRecord {
         d.lvl = __float_as_int(q[17 * kBlock]);
         return d;
     }
+
+    // the stage's jet, without the gradient's derivatives
+    template <int I>
+    __device__ __forceinline__ void jet(const CosmoDev& cz, const RayCtx& R, const HubbleCubic& Hc, Jet32& J) const
+    {
+        const StageData d = get<I>();
+        const float K = (float)d.y.K;
+        J.k0 = -K;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            J.k[i] = K * ((float)R.geo.n[i] + d.y.d[i]);
+            J.G[i] = d.G[i];
+            J.t[i] = d.t[i];
+        }
+        J.H = (float)Hc(cz, d.y.eta);
+        J.dH = (float)Hc.deriv(cz, d.y.eta);
+        J.base = d.base;
+        J.lvl = d.lvl;
+    }
 };
 
-struct RayCtx {
-    RayGeom geo;
-    double xobs[3];
+// The same for the loss sweep (one column), kept in registers: 13 or 14 words
+// a stage.  With the stages unrolled every index is a constant; without the
+// records in LDS two waves fit a SIMD.
+struct RegRecord {
+    float K[4], H[4], dH[4], k[4][3], G[4][3], t[4][3];
+    int base[4], lvl[4];
+
+    template <class FC>
+    __device__ __forceinline__ void stage(int i, const GeoState& y, const GeoState& yi, const FC& F, const float* g,
+                                          const HubbleCubic& Hc, const CosmoDev& cz)
+    {
+        K[i] = (float)yi.K;
+        H[i] = (float)Hc(cz, yi.eta);
+        dH[i] = (float)Hc.deriv(cz, yi.eta);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            k[i][q] = yi.d[q];
+            G[i][q] = g[q];
+            t[i][q] = F.t[q];
+        }
+        base[i] = F.base;
+        lvl[i] = FC::kUniform ? 0 : F.lvl;
+    }
+
+    template <int I>
+    __device__ __forceinline__ void jet(const RayCtx& R, Jet32& J) const
+    {
+        J.k0 = -K[I];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            J.k[i] = K[I] * ((float)R.geo.n[i] + k[I][i]);
+            J.G[i] = G[I][i];
+            J.t[i] = t[I][i];
+        }
+        J.H = H[I];
+        J.dH = dH[I];
+        J.base = base[I];
+        J.lvl = lvl[I];
+    }
+
+    // After a stage's transposed Jacobian its gradient's place takes the loss
+    // cotangent of the interpolated gradient at that stage.
+    template <int I>
+    __device__ __forceinline__ void put_gbar(const float g[3])
+    {
+        G[I][0] = g[0]; G[I][1] = g[1]; G[I][2] = g[2];
+    }
 };
 
 // Trilinear coefficients (component-major: c[8 q + k], gx, gy, gz) of a stencil, read
@@ -213,41 +273,14 @@ __device__ __forceinline__ void trilinear_jet(const T c[8], T tx, T ty, T tz, T&
     fz = c[3] + tx * c[5] + ty * c[6] + tx * ty * c[7];
 }
 
-// What the transposed stage Jacobian needs at one stage (single precision).
-struct Jet32 {
-    float k0, k[3];
-    float G[3];
-    float JG[3][3];     // dG_j / dx_l of the trilinear interpolant
-    float H, dH;        // a'/a and its eta-derivative
-    float t[3];         // CIC offsets (weights) at the stencil level
-    int base;
-};
-
-// Stage quantities that need no stencil coefficients.
-__device__ __forceinline__ void jet_from_stage(const AdjointArgs& A, const RayCtx& R, const StageData& d,
-                                               const HubbleCubic& Hc, Jet32& J)
-{
-    const float K = (float)d.y.K;
-    J.k0 = -K;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        J.k[i] = K * ((float)R.geo.n[i] + d.y.d[i]);
-        J.G[i] = d.G[i];
-        J.t[i] = d.t[i];
-    }
-    J.H = (float)Hc(A.c.cosmo, d.y.eta);
-    J.dH = (float)Hc.deriv(A.c.cosmo, d.y.eta);
-    J.base = d.base;
-}
-
 // Spatial derivatives of the interpolated gradient at the stage: the
 // t-derivatives of the trilinear interpolant (Eq. W_CIC) times 2^lvl / h0.
-__device__ __forceinline__ void jet_gradient(const GridDev& g, const StageData& d, Jet32& J)
+__device__ __forceinline__ void jet_gradient(const GridDev& g, Jet32& J)
 {
     float c[24];
-    stencil_coefs(g, d.base, c);
-    const float tx = d.t[0], ty = d.t[1], tz = d.t[2];
-    const float scale = (float)((double)(1 << d.lvl) * g.inv_h0);
+    stencil_coefs(g, J.base, c);
+    const float tx = J.t[0], ty = J.t[1], tz = J.t[2];
+    const float scale = (float)((double)(1 << J.lvl) * g.inv_h0);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         const float* k = c + 8 * j;
@@ -274,8 +307,10 @@ __device__ __forceinline__ Phys32 rhs32(const Jet32& J)
 }
 
 // Transposed Jacobian of the right-hand side at a stage applied to v:
-// Yb = (dF/dY)^T v and the cotangent Gb of the interpolated grad Phi.
+// Yb = (dF/dY)^T v (Yb.x only with X) and the cotangent Gb of the interpolated
+// grad Phi.
 //   F = (k0, k, -2 H k0^2 - 2 psi k0, -2 H k0 k + 2 psi k - 2 G k0^2), psi = G.k
+template <bool X = true>
 __device__ __forceinline__ void rhs_vjp32(const Jet32& J, const Phys32& v, Phys32& Yb, float Gb[3])
 {
     const float k0 = J.k0;
@@ -290,8 +325,10 @@ __device__ __forceinline__ void rhs_vjp32(const Jet32& J, const Phys32& v, Phys3
 #pragma unroll
     for (int j = 0; j < 3; ++j)
         Yb.k[j] = v.x[j] - 2.0f * k0 * a * J.G[j] + (-2.0f * J.H * k0 + 2.0f * psi) * v.k[j] + 2.0f * J.G[j] * bk;
+    if constexpr (X) {
 #pragma unroll
-    for (int l = 0; l < 3; ++l) Yb.x[l] = J.JG[0][l] * Gb[0] + J.JG[1][l] * Gb[1] + J.JG[2][l] * Gb[2];
+        for (int l = 0; l < 3; ++l) Yb.x[l] = J.JG[0][l] * Gb[0] + J.JG[1][l] * Gb[1] + J.JG[2][l] * Gb[2];
+    }
 }
 
 __device__ __forceinline__ void cic_weights(const float t[3], float w[8])
@@ -417,97 +454,86 @@ struct WaveTable {
 };
 static_assert(kTab == 256, "the slot hash takes the top 8 bits");
 
-// Per-lane accumulator (registers) of the gradient cotangents of the 8 cells
-// of the current stencil.  When the stencil changes the sums move to a
-// pending slot in LDS, and pending slots enter the wave's table once per
-// step, so that a wave runs the table insertion about once per step rather
-// than at every stage where one of its lanes changes stencil.  The cell ids
-// of a stencil are loaded when it becomes current, long before they are
-// needed.
-constexpr int kPendWords = 33;          // 24 sums, 8 cell ids, spare
+// Per-lane accumulator of the gradient cotangents of the 8 cells of the
+// current stencil: 24 words in LDS (component q of corner o is word 8 q + o;
+// quad k at sum[64 k] of the wave's part), to which a step's stages are added
+// once per step, and which enters the wave's table when the lane's stencil
+// changes.  Only the lane itself touches its words: they are read, added to
+// and written back (LDS float atomics on them cost 50 cycles each).
+constexpr int kSumWords = 24;
 
-template <bool AMR>
 struct Scatter {
-    float acc[8][3];
-    int ids[8];
-    int cur;
-    bool pending;
-    float* pend;        // this lane's pending slot: word w at pend[w * kBlock]
+    float4* sum;
+    int cur;            // the stencil's lowest corner, -1: none
 
-    __device__ __forceinline__ void init(float* slot)
+    // lds: kSumWords * kBlock floats of the block
+    __device__ __forceinline__ void init(float* lds)
     {
-        pend = slot;
-        pending = false;
+        sum = reinterpret_cast<float4*>(lds) + (threadIdx.x >> 6) * (64 * kSumWords / 4) + (threadIdx.x & 63);
         cur = -1;
 #pragma unroll
-        for (int o = 0; o < 8; ++o) {
-            ids[o] = -1;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) acc[o][q] = 0.0f;
-        }
+        for (int k = 0; k < kSumWords / 4; ++k) sum[64 * k] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 
-    __device__ __forceinline__ void flush_pending(const AdjointArgs& A, WaveTable& T)
-    {
-        float pa[8][3];
-        int pi[8];
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) pa[o][q] = pend[(3 * o + q) * kBlock];
-            pi[o] = __float_as_int(pend[(24 + o) * kBlock]);
-        }
-        T.add8(A, pi, pa);
-        pending = false;
-    }
-
-    // move the current sums to the pending slot (inserting an older pending
-    // slot first)
-    __device__ __forceinline__ void stash(const AdjointArgs& A, WaveTable& T)
-    {
-        if (cur < 0) return;
-        if (pending) flush_pending(A, T);
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                pend[(3 * o + q) * kBlock] = acc[o][q];
-                acc[o][q] = 0.0f;
-            }
-            pend[(24 + o) * kBlock] = __int_as_float(ids[o]);
-        }
-        pending = true;
-        cur = -1;
-    }
-
-    __device__ __forceinline__ void end_step(const AdjointArgs& A, WaveTable& T)
-    {
-        if (pending) flush_pending(A, T);
-    }
-
+    // the sums to the table, the accumulator empty
     __device__ __forceinline__ void flush(const AdjointArgs& A, WaveTable& T)
     {
-        stash(A, T);
-        end_step(A, T);
+        if (cur < 0) return;
+        const int4* p = reinterpret_cast<const int4*>(A.c.grid.dual_ids + 8 * (int64_t)cur);
+        const int4 a = p[0], b = p[1];
+        const int ids[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        float acc[8][3];
+#pragma unroll
+        for (int k = 0; k < kSumWords / 4; ++k) {
+            const float4 v = sum[64 * k];
+            const int o = 4 * (k & 1), q = k >> 1;
+            acc[o][q] = v.x; acc[o + 1][q] = v.y; acc[o + 2][q] = v.z; acc[o + 3][q] = v.w;
+            sum[64 * k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        T.add8(A, ids, acc);
+        cur = -1;
     }
 
-    __device__ __forceinline__ void add(const AdjointArgs& A, WaveTable& T, int base, const float t[3],
-                                        const float Gb[3])
+    // The stages' cotangents G of the interpolated gradient at offsets t in
+    // the stencils base, last stage first.  A pass adds every lane's leading
+    // stages that share its current stencil; the lanes with stages left
+    // flush, take the next stage's stencil and go round again, which a wave
+    // does once in most steps (a lane's stages rarely meet three stencils).
+    __device__ __forceinline__ void add(const AdjointArgs& A, WaveTable& T, const int (&base)[4],
+                                        const float (&t)[4][3], const float (&G)[4][3])
     {
-        if (base != cur) {
-            stash(A, T);
-            cur = base;
-            const int4* p = reinterpret_cast<const int4*>(A.c.grid.dual_ids + 8 * (int64_t)base);
-            const int4 a = p[0], b = p[1];
-            ids[0] = a.x; ids[1] = a.y; ids[2] = a.z; ids[3] = a.w;
-            ids[4] = b.x; ids[5] = b.y; ids[6] = b.z; ids[7] = b.w;
+        int next = 3;           // first stage not yet added
+        while (next >= 0) {
+            const int b = next == 3 ? base[3] : next == 2 ? base[2] : next == 1 ? base[1] : base[0];
+            if (b != cur) {
+                flush(A, T);
+                cur = b;
+            }
+            float acc[3][8];
+#pragma unroll
+            for (int k = 0; k < kSumWords / 4; ++k) {
+                const float4 v = sum[64 * k];
+                float* c = acc[k >> 1] + 4 * (k & 1);
+                c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
+            }
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                if (next == i && base[i] == b) {
+                    float w[8];
+                    cic_weights(t[i], w);
+#pragma unroll
+                    for (int o = 0; o < 8; ++o)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) acc[q][o] = fmaf(w[o], G[i][q], acc[q][o]);
+                    next = i - 1;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kSumWords / 4; ++k) {
+                const float* c = acc[k >> 1] + 4 * (k & 1);
+                sum[64 * k] = make_float4(c[0], c[1], c[2], c[3]);
+            }
         }
-        float w[8];
-        cic_weights(t, w);
-#pragma unroll
-        for (int o = 0; o < 8; ++o)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) acc[o][q] += w[o] * Gb[q];
     }
 };
 
@@ -547,7 +573,7 @@ __device__ __forceinline__ bool plan_step(const CastArgs& a, FieldCache<AMR>& F,
 // One forward step (regular or landing) from y, as in the forward kernels;
 // records the stages of the final RK4 pass into rec when record is set.  Returns the
 // affine length of the step taken through dl_taken.
-template <bool AMR, class Rec>
+template <bool AMR, class Rec, bool UNROLL>
 __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>& F, const RayGeom& geo,
                                              const GeoState& y, double eta_s, GeoState& yn, Rec& rec, bool record,
                                              double& dl_taken, double& ds_out, bool& landing)
@@ -559,7 +585,7 @@ __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>&
     ds_out = ds;
     if (__builtin_expect(!landing, 1)) {
         // the recorder of stage 0 sees the lane's cache as plan_step left it
-        if (rk4_step<FieldCache<AMR>, Rec, false>(a.grid, a.cosmo, F, geo, y, dl, yn, h, rec, record, &s0))
+        if (rk4_step<FieldCache<AMR>, Rec, UNROLL>(a.grid, a.cosmo, F, geo, y, dl, yn, h, rec, record, &s0))
             return false;
         dl_taken = dl;
         return true;
@@ -568,10 +594,11 @@ __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>&
     // recorded pass evaluates its stage 0 again, since the passes before it
     // moved the lane's cache)
     double dlx = (y.eta - eta_s) / y.K;
+#pragma unroll 1
     for (int k = 0; k < 3; ++k) {
         const bool rec_pass = record && k == 2;
-        if (rk4_step<FieldCache<AMR>, Rec, false>(a.grid, a.cosmo, F, geo, y, dlx, yn, h, rec, rec_pass,
-                                                 rec_pass ? nullptr : &s0))
+        if (rk4_step<FieldCache<AMR>, Rec, UNROLL>(a.grid, a.cosmo, F, geo, y, dlx, yn, h, rec,
+                                                   UNROLL ? record : rec_pass, rec_pass ? nullptr : &s0))
             return false;
         if (k < 2) dlx = dlx + (yn.eta - eta_s) / yn.K;
     }
@@ -579,40 +606,35 @@ __device__ __forceinline__ bool forward_step(const CastArgs& a, FieldCache<AMR>&
     return true;
 }
 
-// Reverse of one RK4 step for all W cotangent columns: the four stages are
-// visited last to first; the jet of a stage is formed once and applied to
-// every column.  For y' = y + dl/6 (F1 + 2 F2 + 2 F3 + F4) with
+// Reverse of one RK4 step for the W cotangent columns of the Jacobian: the
+// four stages are visited last to first; the jet of a stage is formed once and
+// applied to every column.  For y' = y + dl/6 (F1 + 2 F2 + 2 F3 + F4) with
 // Y_i = y + c_i dl F_{i-1} (c = 1/2, 1/2, 1):
 //   Fbar_4 = dl/6 v,  Ybar_i = J_i^T Fbar_i,
 //   Fbar_{i-1} = w_{i-1}/6 dl v + c_i dl Ybar_i,  ybar = v + sum_i Ybar_i,
 //   dlbar = sum_i (w_i/6) v.F_i + sum_{i>1} c_i Ybar_i.F_{i-1}.
 // Stage I (0-based) is handled with J holding its jet; the recursion moves
 // to stage I - 1.
-template <int I, bool AMR, int W, bool SCATTER>
-__device__ __forceinline__ void reverse_stage(const AdjointArgs& A, const RayCtx& R, const StageRecord& rec,
+template <int I, int W>
+__device__ __forceinline__ void reverse_stage(const AdjointArgs& A, const RayCtx& R, const LdsRecord& rec,
                                               const HubbleCubic& Hc, float dlf, Jet32& J,
                                               const Phys32 (&v)[W], Phys32 (&Fb)[W], float (&dlbar)[W],
-                                              Phys32 (&dy)[W], const float (&lc)[W], Scatter<AMR>& S, WaveTable& T)
+                                              Phys32 (&dy)[W])
 {
     Jet32 P;
     Phys32 FP;
     if constexpr (I > 0) {
-        jet_from_stage(A, R, rec.template get<I - 1>(), Hc, P);
+        rec.template jet<I - 1>(A.c.cosmo, R, Hc, P);
         FP = rhs32(P);
     }
     constexpr float ci = (I == 3) ? 1.0f : 0.5f;
     constexpr float wprev = (I == 1) ? 1.0f : 2.0f;
-    float gL[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int c = 0; c < W; ++c) {
         Phys32 Yb;
         float Gb[3];
         rhs_vjp32(J, Fb[c], Yb, Gb);
         phys_axpy(dy[c], 1.0f, Yb);
-        if (SCATTER) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) gL[q] = fmaf(lc[c], Gb[q], gL[q]);
-        }
         if constexpr (I > 0) {
             dlbar[c] += ci * phys_dot(Yb, FP) + (wprev * (1.0f / 6.0f)) * phys_dot(v[c], FP);
             phys_zero(Fb[c]);
@@ -620,32 +642,24 @@ __device__ __forceinline__ void reverse_stage(const AdjointArgs& A, const RayCtx
             phys_axpy(Fb[c], ci * dlf, Yb);
         }
     }
-    if (SCATTER) rec.template put_gbar<I>(gL);
     if constexpr (I > 0) {
         J = P;
-        jet_gradient(A.c.grid, rec.template get<I - 1>(), J);
-        reverse_stage<I - 1, AMR, W, SCATTER>(A, R, rec, Hc, dlf, J, v, Fb, dlbar, dy, lc, S, T);
+        jet_gradient(A.c.grid, J);
+        reverse_stage<I - 1, W>(A, R, rec, Hc, dlf, J, v, Fb, dlbar, dy);
     }
 }
 
-// The loss column is a fixed linear combination of the others when the
-// Jacobian columns are carried (its end-point cotangent is
-// lc_0 beta_1 + lc_1 beta_2 + lc_2 z, and the sweep is linear), so it is
-// not propagated separately: its gradient cotangents are that combination of
-// the columns' ones.  Alone (W = 1) it is the only column, with lc_0 = 1.
-template <bool AMR, int W, bool SCATTER>
-__device__ __forceinline__ void reverse_step(const AdjointArgs& A, const RayCtx& R, const StageRecord& rec,
+template <int W>
+__device__ __forceinline__ void reverse_step(const AdjointArgs& A, const RayCtx& R, const LdsRecord& rec,
                                              const HubbleCubic& Hc, double dl,
-                                             double ds_reg, double k0_step, Phys (&yb)[W], const float (&lc)[W],
-                                             Scatter<AMR>& S, WaveTable& T)
+                                             double ds_reg, double k0_step, Phys (&yb)[W])
 {
     const float dlf = (float)dl;
     Phys32 v[W], Fb[W], dy[W];
     float dlbar[W];
     Jet32 J;
-    const StageData d3 = rec.template get<3>();
-    jet_from_stage(A, R, d3, Hc, J);
-    jet_gradient(A.c.grid, d3, J);
+    rec.template jet<3>(A.c.cosmo, R, Hc, J);
+    jet_gradient(A.c.grid, J);
     {
         const Phys32 F4 = rhs32(J);
 #pragma unroll
@@ -657,19 +671,7 @@ __device__ __forceinline__ void reverse_step(const AdjointArgs& A, const RayCtx&
             phys_zero(dy[c]);
         }
     }
-    reverse_stage<3, AMR, W, SCATTER>(A, R, rec, Hc, dlf, J, v, Fb, dlbar, dy, lc, S, T);
-    if (SCATTER) {
-        // the stages' gradient cotangents to the cells, last stage first (one
-        // copy of the accumulate-and-flush code)
-#pragma unroll 1
-        for (int i = 3; i >= 0; --i) {
-            int base;
-            float t[3], g[3];
-            rec.scatter_data(i, base, t, g);
-            S.add(A, T, base, t, g);
-        }
-        S.end_step(A, T);
-    }
+    reverse_stage<3, W>(A, R, rec, Hc, dlf, J, v, Fb, dlbar, dy);
     // the four stage increments, summed in single precision, enter the
     // double-precision cotangent once per step
 #pragma unroll
@@ -680,6 +682,72 @@ __device__ __forceinline__ void reverse_step(const AdjointArgs& A, const RayCtx&
 #pragma unroll
         for (int c = 0; c < W; ++c) yb[c].k0 += (double)dlbar[c] * f;
     }
+}
+
+// Spatial part of the transposed stage Jacobian for one column: the gradient's
+// cotangent contracted with the stencil's coefficients (one trilinear scalar),
+// then its derivatives, in place of the nine derivatives of the gradient.
+__device__ __forceinline__ void gradient_vjp(const GridDev& g, int base, int lvl, const float t[3], const float Gb[3],
+                                             float x[3])
+{
+    float c[24], k[8];
+    stencil_coefs(g, base, c);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) k[i] = fmaf(Gb[2], c[16 + i], fmaf(Gb[1], c[8 + i], Gb[0] * c[i]));
+    const float scale = ldexpf((float)g.inv_h0, lvl);
+    const float tx = t[0], ty = t[1], tz = t[2];
+    x[0] = scale * fmaf(tz, fmaf(ty, k[7], k[5]), fmaf(ty, k[4], k[1]));
+    x[1] = scale * fmaf(tz, fmaf(tx, k[7], k[6]), fmaf(tx, k[4], k[2]));
+    x[2] = scale * fmaf(ty, fmaf(tx, k[7], k[6]), fmaf(tx, k[5], k[3]));
+}
+
+// The same for the loss's single column.  As Fbar_i = dl times the bracket of
+// F_i in dlbar, dlbar = sum_i F_i.Fbar_i / dl.
+template <int I>
+__device__ __forceinline__ void reverse_loss_stage(const AdjointArgs& A, const RayCtx& R, RegRecord& rec, float dlf,
+                                                   const Phys32& v6, Phys32& Fb, float& dlbar, Phys32& dy)
+{
+    Jet32 J;
+    rec.template jet<I>(R, J);
+    dlbar += phys_dot(Fb, rhs32(J));
+    Phys32 Yb;
+    float Gb[3];
+    rhs_vjp32<false>(J, Fb, Yb, Gb);
+    float x[3];
+    gradient_vjp(A.c.grid, J.base, J.lvl, J.t, Gb, x);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) Yb.x[l] = x[l];
+    rec.template put_gbar<I>(Gb);
+    phys_axpy(dy, 1.0f, Yb);
+    if constexpr (I > 0) {
+        constexpr float wprev = (I == 1) ? 1.0f : 2.0f;
+        const float cdl = (I == 3) ? dlf : 0.5f * dlf;
+        Fb.eta = fmaf(cdl, Yb.eta, wprev * v6.eta);
+        Fb.k0 = fmaf(cdl, Yb.k0, wprev * v6.k0);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            Fb.x[i] = fmaf(cdl, Yb.x[i], wprev * v6.x[i]);
+            Fb.k[i] = fmaf(cdl, Yb.k[i], wprev * v6.k[i]);
+        }
+        reverse_loss_stage<I - 1>(A, R, rec, dlf, v6, Fb, dlbar, dy);
+    }
+}
+
+__device__ __forceinline__ void reverse_loss_step(const AdjointArgs& A, const RayCtx& R, RegRecord& rec, double dl,
+                                                  double ds_reg, double K, Phys& yb)
+{
+    const float dlf = (float)dl;
+    Phys32 v6, dy;
+    phys_zero(v6);
+    phys_axpy(v6, dlf * (1.0f / 6.0f), to32(yb));
+    phys_zero(dy);
+    Phys32 Fb = v6;
+    float dlbar = 0.0f;
+    reverse_loss_stage<3>(A, R, rec, dlf, v6, Fb, dlbar, dy);
+    phys_axpy(yb, 1.0, dy);
+    // a regular step has dl = ds / |k0| with ds fixed by the leaf level:
+    // k0bar += dlbar ds / k0^2 = (dlbar dl) / |k0|
+    if (ds_reg > 0.0) yb.k0 += (double)(dlbar * __builtin_amdgcn_rcpf((float)K));
 }
 
 // Rays without a derivative (not stopped on the source surface, or a replay
@@ -758,9 +826,9 @@ __device__ __forceinline__ void point_jet(const AdjointArgs& A, const RayCtx& R,
 // eta(y_f) = eta_s, so the cotangent along the flow F(y_f) is removed.
 template <bool AMR, int W, bool SCATTER>
 __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCtx& R, FieldCache<AMR>& F,
-                                               const ObsDev& ob, int64_t ray, const GeoState& yf, double phio,
+                                               const ObsDev& ob, int64_t ray, bool owner, const GeoState& yf, double phio,
                                                const double e1[3], const double e2[3], Phys (&yb)[W],
-                                               float (&lc)[W], double& phio_bar)
+                                               double& phio_bar)
 {
     constexpr bool HAS_JAC = W >= 3;
     const GridDev& g = A.c.grid;
@@ -833,85 +901,80 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
                 cb[bb] += ga[aa] * (-fs * ee + fps * et * ne);
             }
         }
-        if constexpr (W == 1) {
-            Phys& L = yb[0];
+        Phys& L = yb[0];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) L.x[i] = (cb[0] * f1[i] + cb[1] * f2[i]) / chi + gz * dz_dphis * Jf.gphi[i];
-            L.k0 = -gz * dz_dK;
-            lc[0] = 1.0f;
-        } else {
-            lc[0] = (float)cb[0];
-            lc[1] = (float)cb[1];
-            lc[2] = (float)gz;
-        }
-        scatter_phi(A, end_base, Jf.t, gz * dz_dphis);
+        for (int i = 0; i < 3; ++i) L.x[i] = (cb[0] * f1[i] + cb[1] * f2[i]) / chi + gz * dz_dphis * Jf.gphi[i];
+        L.k0 = -gz * dz_dK;
+        if (owner) scatter_phi(A, end_base, Jf.t, gz * dz_dphis);
         phio_bar = gz * dz_dphio;
     }
 #pragma unroll
     for (int c = 0; c < W; ++c) yb[c].eta -= phys_dot(yb[c], Jf.F) / Jf.F.eta;
 }
 
-// W cotangent columns: W = 3 (beta_1, beta_2, z) or 1 (the loss L).
-// SCATTER: the cell cotangents of L are kept (with W = 3, L is the
-// combination lc of the three columns).
-template <bool AMR, int W, bool SCATTER>
+// A ray's sweep: its observer, stop surface and start.
+template <bool AMR>
+struct Sweep {
+    RayCtx R;
+    FieldCache<AMR> F;
+    const ObsDev* ob;
+    double eta_s, phio, kmag, e1[3], e2[3];
+    int obs_base, obs_lvl, N, nseg;
+
+    __device__ __forceinline__ void start(const AdjointArgs& A, int64_t ray, int n_steps, float* lds)
+    {
+        const CastArgs& a = A.c;
+        int j = a.n_obs - 1;
+        while (j > 0 && a.obs[j].ray_first > ray) --j;
+        ob = a.obs + j;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            R.geo.vo[i] = ldexp(ob->x[i] / a.grid.h0, a.grid.max_level + 1);
+            R.geo.n[i] = a.dirs[3 * ray + i];
+        }
+        eta_s = a.ray_stop ? a.ray_stop[ray].x : ob->eta_s;
+        F.bind(lds);
+        F.reset();
+        // potential at the observer and the initial |k| (as in the forward)
+        int ll;
+        F.locate(a.grid, R.geo.vo, ll);
+        obs_base = F.base;
+        obs_lvl = F.lvl;
+        phio = (double)F.phi(a.grid);
+        kmag = sqrt((1.0 + 2.0 * phio) / (1.0 - 2.0 * phio));
+        screen_basis(R.geo.n, e1, e2);
+        N = n_steps;
+        nseg = (N + a.ckpt_every - 1) / a.ckpt_every;
+    }
+};
+
+// The replay must end where the forward cast ended, bit for bit.
+__device__ __forceinline__ bool retraced(const RayEnd& e, const GeoState& y)
+{
+    return y.eta == e.eta && y.dx[0] == e.dx[0] && y.dx[1] == e.dx[1] && y.dx[2] == e.dx[2];
+}
+
+// The distortion matrix by the reverse sweep: the three columns beta_1,
+// beta_2 and z of the rays A.list (the finder's Newton steps; the other
+// products take the tangents of cast_tangent_kernel).
+template <bool AMR>
 __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
 {
-    // LDS: [24][kBlock] stencil coefficients, [4 * 18][kBlock] stage records,
-    // [33][kBlock] pending scatter sums, then one table per wave
+    // LDS: stencil coefficients, then the stage records
     extern __shared__ float lds[];
-    WaveTable T;
-    if (SCATTER) {
-        T.bind(lds + (FieldCache<AMR>::kFloats + 4 * StageRecord::kWords + kPendWords) * kBlock + (threadIdx.x >> 6) * kTabWords);
-        T.clear(threadIdx.x & 63);
-    }
-    const int64_t at = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const CastArgs& a = A.c;
-    if (at >= A.n_list) return;
-    const int64_t ray = A.list ? A.list[at] : at;
-    constexpr bool HAS_JAC = W >= 3;
-    const int N = A.n_steps[ray];
-    if (A.status[ray] != MPATH_RAY_REACHED || N <= 0) {
-        if (HAS_JAC) write_nan_jacobian(A, ray);
-        if (A.ray_status) A.ray_status[ray] = 1;
+    int64_t at;
+    if (!lane_ray(a, A.n_list, at)) return;
+    const int64_t ray = A.list[at];
+    constexpr int W = 3;
+    if (A.status[ray] != MPATH_RAY_REACHED || A.n_steps[ray] <= 0) {
+        write_nan_jacobian(A, ray);
         return;
     }
-    const GridDev& g = a.grid;
-    int j = a.n_obs - 1;
-    while (j > 0 && a.obs[j].ray_first > ray) --j;
-    const ObsDev& ob = a.obs[j];
-    RayCtx R;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        R.xobs[i] = ob.x[i];
-        R.geo.vo[i] = ldexp(ob.x[i] / g.h0, g.max_level + 1);
-        R.geo.n[i] = a.dirs[3 * ray + i];
-    }
-    const double eta_s = a.ray_stop ? a.ray_stop[ray].x : ob.eta_s;
-    FieldCache<AMR> F;
-    F.bind(lds);
-    F.reset();
-
-    // potential at the observer and the initial |k| (as in the forward)
-    int ll;
-    F.locate(g, R.geo.vo, ll);
-    const int obs_base = F.base, obs_lvl = F.lvl;
-    const double phio = (double)F.phi(g);
-    const double kmag = sqrt((1.0 + 2.0 * phio) / (1.0 - 2.0 * phio));
-
+    Sweep<AMR> w;
+    w.start(A, ray, A.n_steps[ray], lds);
     const int K = a.ckpt_every;
-    const int nseg = (N + K - 1) / K;
-    const double* n = R.geo.n;
-    double e1[3], e2[3];
-    screen_basis(n, e1, e2);
     Phys yb[W];
-    float lc[W];
-#pragma unroll
-    for (int c = 0; c < W; ++c) lc[c] = 0.0f;
-    double phio_bar = 0.0;
-    Scatter<AMR> S;
-    S.init(lds + (FieldCache<AMR>::kFloats + 4 * StageRecord::kWords) * kBlock + threadIdx.x);
-
     // Segments from the source back to the observer.  Each is traversed
     // forwards from its checkpoint (storing the state before every step in
     // the tape; the last step of a segment other than the final one is not
@@ -921,29 +984,26 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
     bool ok = true;
     // the tape entry of the next reverse step and the next segment's
     // checkpoint are loaded one iteration ahead of their use
-    GeoState pre, ck = a.ckpt[(int64_t)(nseg - 1) * a.n_rays + ray];
-    for (int seg = nseg - 1; seg >= 0 && ok; --seg) {
-        const bool last = seg == nseg - 1;
+    GeoState pre, ck = a.ckpt[(int64_t)(w.nseg - 1) * a.n_rays + ray];
+    for (int seg = w.nseg - 1; seg >= 0 && ok; --seg) {
+        const bool last = seg == w.nseg - 1;
         const int j0 = seg * K;
-        const int len = min(N, j0 + K) - j0;
+        const int len = min(w.N, j0 + K) - j0;
         const int nf = last ? len : len - 1;
         GeoState y = ck, yin = ck;
         for (int it = 0; it < nf + len; ++it) {
             const bool fwd = it < nf;
-            // the lanes still iterating empty the table when it is a quarter full
-            if (SCATTER && *T.count > kTab / 4) T.evict(A);
             if (it == nf) {
                 // the state before the segment's last step is in registers
                 pre = last ? yin : y;
                 if (seg > 0) ck = a.ckpt[(int64_t)(seg - 1) * a.n_rays + ray];
                 if (last) {
-                    // the replay must end where the forward cast ended, bit for bit
-                    const RayEnd e = a.ends[ray];
-                    if (y.eta != e.eta || y.dx[0] != e.dx[0] || y.dx[1] != e.dx[1] || y.dx[2] != e.dx[2]) {
+                    if (!retraced(a.ends[ray], y)) {
                         ok = false;
                         break;
                     }
-                    end_cotangents<AMR, W, SCATTER>(A, R, F, ob, ray, y, phio, e1, e2, yb, lc, phio_bar);
+                    double none;
+                    end_cotangents<AMR, W, false>(A, w.R, w.F, *w.ob, ray, false, y, w.phio, w.e1, w.e2, yb, none);
                 }
             }
             const int jl = fwd ? it : len - 1 - (it - nf);
@@ -956,12 +1016,12 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
                 ys = pre;
                 if (jl > 0) pre = A.tape[(int64_t)(jl - 1) * a.n_rays + ray];
             }
-            StageRecord rec;
+            LdsRecord rec;
             rec.p = lds + FieldCache<AMR>::kFloats * kBlock + threadIdx.x;
             GeoState yn;
             double dl, ds;
             bool landing;
-            if (!forward_step<AMR, StageRecord>(a, F, R.geo, ys, eta_s, yn, rec, !fwd, dl, ds, landing)) {
+            if (!forward_step<AMR, LdsRecord, false>(a, w.F, w.R.geo, ys, w.eta_s, yn, rec, !fwd, dl, ds, landing)) {
                 ok = false;
                 break;
             }
@@ -970,51 +1030,155 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
             } else {
                 HubbleCubic Hc;
                 Hc.init(a.cosmo, ys.eta);
-                const double ds_reg = landing ? 0.0 : ds;
-                reverse_step<AMR, W, SCATTER>(A, R, rec, Hc, dl, ds_reg, -ys.K, yb, lc, S, T);
+                reverse_step<W>(A, w.R, rec, Hc, dl, landing ? 0.0 : ds, -ys.K, yb);
             }
         }
     }
+    if (!ok) {
+        write_nan_jacobian(A, ray);
+        return;
+    }
+    // the initial state: k = kmag(Phi_o) n (theta), k0 = -1
+    const double* eb[2] = {w.e1, w.e2};
+#pragma unroll
+    for (int bb = 0; bb < 2; ++bb) {
+        const double db0 = w.kmag * (yb[0].k[0] * eb[bb][0] + yb[0].k[1] * eb[bb][1] + yb[0].k[2] * eb[bb][2]);
+        const double db1 = w.kmag * (yb[1].k[0] * eb[bb][0] + yb[1].k[1] * eb[bb][1] + yb[1].k[2] * eb[bb][2]);
+        const double dz = w.kmag * (yb[2].k[0] * eb[bb][0] + yb[2].k[1] * eb[bb][1] + yb[2].k[2] * eb[bb][2]);
+        if (A.jac) {
+            A.jac[4 * ray + bb] = (float)db0;          // row beta_1
+            A.jac[4 * ray + 2 + bb] = (float)db1;      // row beta_2
+        }
+        if (A.dz_dtheta) A.dz_dtheta[2 * ray + bb] = (float)dz;
+    }
+}
 
-    // ---- the initial state: k = kmag(Phi_o) n (theta), k0 = -1 ----
-    if (HAS_JAC && !ok) write_nan_jacobian(A, ray);
-    if (A.ray_status) A.ray_status[ray] = ok ? 0 : 2;
-    if (HAS_JAC && ok) {
-        const double* eb[2] = {e1, e2};
-#pragma unroll
-        for (int bb = 0; bb < 2; ++bb) {
-            const double db0 = kmag * (yb[0].k[0] * eb[bb][0] + yb[0].k[1] * eb[bb][1] + yb[0].k[2] * eb[bb][2]);
-            const double db1 = kmag * (yb[1].k[0] * eb[bb][0] + yb[1].k[1] * eb[bb][1] + yb[1].k[2] * eb[bb][2]);
-            const double dz = kmag * (yb[2].k[0] * eb[bb][0] + yb[2].k[1] * eb[bb][1] + yb[2].k[2] * eb[bb][2]);
-            if (A.jac) {
-                A.jac[4 * ray + bb] = (float)db0;          // row beta_1
-                A.jac[4 * ray + 2 + bb] = (float)db1;      // row beta_2
+// The cell cotangents of the loss L by the reverse sweep of its one column.
+// One column's stage records fit in registers and the scatter sums take 96
+// bytes of LDS a lane, so that two waves fit a SIMD (one did with the records
+// in LDS and the Jacobian's columns alongside), which hides most of the gather
+// and table latency: 131,072 rays to z = 1 on a uniform 64^3 grid (3,000 steps)
+// 80.3 ms before, 34.6 now, 27 of them without the scatter; with the Jacobian
+// (15 ms of tangents) 80.5 and 49.6.  12,288 rays on 64^3 + 5 levels 18.1 and
+// 11.1.  SPREAD: waves of fewer than 64 rays (see lane_ray).
+template <bool AMR, bool SPREAD>
+__global__ __launch_bounds__(kBlock, 2) void adjoint_loss_kernel(AdjointArgs A)
+{
+    // LDS: stencil coefficients, scatter sums, one table per wave
+    extern __shared__ float lds[];
+    WaveTable T;
+    T.bind(lds + (FieldCache<AMR>::kFloats + kSumWords) * kBlock + (threadIdx.x >> 6) * kTabWords);
+    T.clear(threadIdx.x & 63);
+    const CastArgs& a = A.c;
+    int64_t ray = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    bool owner = true;          // the lanes that repeat another's ray add nothing to the cells
+    if constexpr (SPREAD) {
+        if (!lane_ray(a, a.n_rays, ray)) return;
+        owner = (int)(threadIdx.x & 63) < min((int64_t)a.lanes, a.n_rays - (ray & -(int64_t)a.lanes));
+    } else {
+        if (ray >= a.n_rays) return;
+    }
+    const int n_steps = A.n_steps[ray];
+    if (A.status[ray] != MPATH_RAY_REACHED || n_steps <= 0) {
+        write_nan_jacobian(A, ray);
+        if (A.ray_status) A.ray_status[ray] = 1;
+        return;
+    }
+    const GridDev& g = a.grid;
+    Sweep<AMR> w;
+    w.start(A, ray, n_steps, lds);
+    const int K = a.ckpt_every;
+    Phys yb[1];
+    double phio_bar = 0.0;
+    Scatter S;
+    S.init(lds + FieldCache<AMR>::kFloats * kBlock);
+    NoRecord none;
+    bool ok = true;
+    // segments from the source back to the observer: forwards from the
+    // checkpoint into the tape (the last step of a segment other than the
+    // final one is not needed), then backwards, re-recording every step
+    GeoState ck = a.ckpt[(int64_t)(w.nseg - 1) * a.n_rays + ray];
+    for (int seg = w.nseg - 1; seg >= 0 && ok; --seg) {
+        const bool last = seg == w.nseg - 1;
+        const int j0 = seg * K;
+        const int len = min(w.N, j0 + K) - j0;
+        GeoState y = ck, pre = ck;
+        double dl, ds;
+        bool landing;
+        for (int it = 0; it < len; ++it) {
+            pre = y;                      // the state before the segment's last step, in the end
+            if (it == len - 1 && !last) break;
+            A.tape[(int64_t)it * a.n_rays + ray] = y;
+            GeoState yn;
+            if (!forward_step<AMR, NoRecord, true>(a, w.F, w.R.geo, y, w.eta_s, yn, none, false, dl, ds, landing)) {
+                ok = false;
+                break;
             }
-            if (A.dz_dtheta) A.dz_dtheta[2 * ray + bb] = (float)dz;
+            y = yn;
+        }
+        if (!ok) break;
+        if (seg > 0) ck = a.ckpt[(int64_t)(seg - 1) * a.n_rays + ray];
+        if (last) {
+            if (!retraced(a.ends[ray], y)) {
+                ok = false;
+                break;
+            }
+            end_cotangents<AMR, 1, true>(A, w.R, w.F, *w.ob, ray, owner, y, w.phio, w.e1, w.e2, yb, phio_bar);
+        }
+        for (int jl = len - 1; jl >= 0; --jl) {
+            // the lanes still iterating empty the table when it is a quarter full
+            if (*T.count > kTab / 4) T.evict(A);
+            const GeoState ys = pre;
+            // the tape entry of the next step is loaded one step ahead of its use
+            if (jl > 0) pre = A.tape[(int64_t)(jl - 1) * a.n_rays + ray];
+            RegRecord rec;
+            GeoState yn;
+            if (!forward_step<AMR, RegRecord, true>(a, w.F, w.R.geo, ys, w.eta_s, yn, rec, true, dl, ds, landing)) {
+                ok = false;
+                break;
+            }
+            reverse_loss_step(A, w.R, rec, dl, landing ? 0.0 : ds, ys.K, yb[0]);
+            if (owner) S.add(A, T, rec.base, rec.t, rec.G);
         }
     }
-    if (SCATTER) {
-        if (ok) {
-            S.flush(A, T);
-            double Lk[3] = {0.0, 0.0, 0.0};
+    if (!ok) write_nan_jacobian(A, ray);
+    if (A.ray_status) A.ray_status[ray] = ok ? 0 : 2;
+    if (ok && owner) {
+        S.flush(A, T);
+        // the initial state: k = kmag(Phi_o) n (theta), k0 = -1
+        const double* n = w.R.geo.n;
+        const double dkmag = w.kmag * 2.0 / (1.0 - 4.0 * w.phio * w.phio);
+        phio_bar += (yb[0].k[0] * n[0] + yb[0].k[1] * n[1] + yb[0].k[2] * n[2]) * dkmag;
+        GeoState y0;
+        y0.eta = g.eta0;
+        y0.K = 1.0;
 #pragma unroll
-            for (int c = 0; c < W; ++c)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) Lk[i] += (double)lc[c] * yb[c].k[i];
-            const double dkmag = kmag * 2.0 / (1.0 - 4.0 * phio * phio);
-            phio_bar += (Lk[0] * n[0] + Lk[1] * n[1] + Lk[2] * n[2]) * dkmag;
-            GeoState y0;
-            y0.eta = g.eta0;
-            y0.K = 1.0;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) { y0.d[i] = 0.0f; y0.dx[i] = 0.0f; }
-            double t0[3];
-            stage_offsets(g, R, y0, obs_lvl, t0);
-            scatter_phi(A, obs_base, t0, phio_bar);
-        }
-        // every lane that took a ray arrives here together: empty the table
-        T.evict(A);
+        for (int i = 0; i < 3; ++i) { y0.d[i] = 0.0f; y0.dx[i] = 0.0f; }
+        double t0[3];
+        stage_offsets(g, w.R, y0, w.obs_lvl, t0);
+        scatter_phi(A, w.obs_base, t0, phio_bar);
     }
+    // every lane that took a ray arrives here together: empty the table
+    T.evict(A);
+}
+
+// The check of a Jacobian without a loss: `ends` are the end states of the
+// cast that carried the tangents.  A ray that did not reach the source has no
+// derivative; one that ended elsewhere than the forward cast is reported.
+__global__ __launch_bounds__(256) void retrace_kernel(AdjointArgs A, const RayEnd* __restrict__ ends)
+{
+    const int64_t ray = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (ray >= A.c.n_rays) return;
+    int st = 1;
+    if (A.status[ray] == MPATH_RAY_REACHED && A.n_steps[ray] > 0) {
+        GeoState y;
+        const RayEnd e = ends[ray];
+        y.eta = e.eta;
+        y.dx[0] = e.dx[0]; y.dx[1] = e.dx[1]; y.dx[2] = e.dx[2];
+        st = retraced(A.c.ends[ray], y) ? 0 : 2;
+    }
+    if (st) write_nan_jacobian(A, ray);
+    if (A.ray_status) A.ray_status[ray] = st;
 }
 
 __global__ void fill_zero_kernel(float* __restrict__ p, int64_t n)
@@ -1059,25 +1223,43 @@ __global__ void central_transpose_kernel(const float* __restrict__ g_lib, const 
 
 }  // namespace
 
-hipError_t launch_adjoint(const AdjointArgs& A, int columns, hipStream_t s)
+hipError_t launch_adjoint(const AdjointArgs& args, hipStream_t s)
 {
-    const int64_t n = A.n_list;
+    if (args.n_list == 0) return hipSuccess;
+    AdjointArgs A = args;
+    A.c = spread_rays(args.c, args.n_list, 1);
+    const dim3 grid = ray_grid(A.c, A.n_list), block(kBlock);
+    const size_t lds = (size_t)(FieldCache<true>::kFloats + 4 * LdsRecord::kWords) * kBlock * sizeof(float);
+    if (A.c.grid.max_level > 0) hipLaunchKernelGGL(adjoint_kernel<true>, grid, block, lds, s, A);
+    else hipLaunchKernelGGL(adjoint_kernel<false>, grid, block, lds, s, A);
+    return hipGetLastError();
+}
+
+hipError_t launch_adjoint_loss(const AdjointArgs& args, hipStream_t s)
+{
+    const int64_t n = args.c.n_rays;
     if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + kBlock - 1) / kBlock)), block(kBlock);
-    const size_t lds_cache = (size_t)(FieldCache<true>::kFloats + 4 * StageRecord::kWords) * kBlock * sizeof(float);
-    const size_t lds = lds_cache + (columns == 3 ? 0 : ((size_t)kPendWords * kBlock + (size_t)(kBlock / 64) * kTabWords) *
-                                                          sizeof(float));
+    AdjointArgs A = args;
+    A.c = spread_rays(args.c, n, 1);
+    const dim3 grid = ray_grid(A.c, n), block(kBlock);
+    const size_t lds = ((size_t)(FieldCache<true>::kFloats + kSumWords) * kBlock +
+                        (size_t)(kBlock / 64) * kTabWords) * sizeof(float);
     const bool amr = A.c.grid.max_level > 0;
-    if (columns == 4) {
-        if (amr) hipLaunchKernelGGL((adjoint_kernel<true, 3, true>), grid, block, lds, s, A);
-        else hipLaunchKernelGGL((adjoint_kernel<false, 3, true>), grid, block, lds, s, A);
-    } else if (columns == 3) {
-        if (amr) hipLaunchKernelGGL((adjoint_kernel<true, 3, false>), grid, block, lds, s, A);
-        else hipLaunchKernelGGL((adjoint_kernel<false, 3, false>), grid, block, lds, s, A);
+    if (A.c.lanes < 64) {
+        if (amr) hipLaunchKernelGGL((adjoint_loss_kernel<true, true>), grid, block, lds, s, A);
+        else hipLaunchKernelGGL((adjoint_loss_kernel<false, true>), grid, block, lds, s, A);
     } else {
-        if (amr) hipLaunchKernelGGL((adjoint_kernel<true, 1, true>), grid, block, lds, s, A);
-        else hipLaunchKernelGGL((adjoint_kernel<false, 1, true>), grid, block, lds, s, A);
+        if (amr) hipLaunchKernelGGL((adjoint_loss_kernel<true, false>), grid, block, lds, s, A);
+        else hipLaunchKernelGGL((adjoint_loss_kernel<false, false>), grid, block, lds, s, A);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_retrace(const AdjointArgs& A, const RayEnd* ends, hipStream_t s)
+{
+    const int64_t n = A.c.n_rays;
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(retrace_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A, ends);
     return hipGetLastError();
 }
 

@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_static_kernel(C
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR, FieldCache<AMR, TIME>> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_ckpt_kernel(Cas
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -639,7 +639,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_infbeam_kernel(CastArgs a, flo
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR> R;
     R.F.bind(coef_lds);
     InfBeam<AMR> B;
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_diff_kernel(Cas
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR, FieldCache<AMR, false, true>, StepDifference> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_stop_kernel(Cas
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -719,7 +719,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_surfaces_kernel(CastArgs a, Su
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kBlock, 2) void born_beam_kernel(CastArgs a, float*
 {
     extern __shared__ float born_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     const GridDev& g = a.grid;
     int j = a.n_obs - 1;
     while (j > 0 && a.obs[j].ray_first > r) --j;
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_order_kernel(CastArgs a)
 {
     extern __shared__ float order_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     using FC = typename std::conditional<ORDER == 0, NgpCache<AMR>, TscCache<AMR>>::type;
     RayRun<AMR, FC> R;
     R.F.bind(order_lds);
@@ -999,7 +999,7 @@ __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, Tan
 {
     extern __shared__ float coef_lds[];
     int64_t r;
-    if (!lane_ray(a, r)) return;
+    if (!lane_ray(a, a.n_rays, r)) return;
     RayRun<AMR> R;
     R.F.bind(coef_lds);
     R.start(a, r);
@@ -1142,41 +1142,14 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
 
 }  // namespace
 
-namespace {
-
-// The launch's rays per wave: 64, or fewer where that leaves SIMDs without a
-// wave: the smallest power of two that needs at most `waves` waves per SIMD.
-// A stage stalls the wave when any of its rays enters a new stencil, so waves
-// of fewer rays run a step sooner; beyond one wave per SIMD the additional
-// instructions cost more than that saves, except where the stalls are long (a
-// tree's walk, the 27 cells of TSC), which two waves per SIMD hide better.
-// Uniform 64^3, 3,072 rays to z = 0.3: 64 rays a wave 2.01 ms, 8 1.70, 4 (768
-// waves) 1.65, 2 (1,536) 2.01; 6,144 rays on 64^3 + 5 levels: 1.97, 1.73, 4
-// (1,536 waves) 1.57; TSC there 5.14, 4.19, 3.34.
-CastArgs spread_rays(const CastArgs& a, int waves)
-{
-    CastArgs c = a;
-    c.lanes = 64;
-    while (c.lanes > 1 && (a.n_rays + c.lanes / 2 - 1) / (c.lanes / 2) <= (int64_t)waves * a.simds) c.lanes /= 2;
-    return c;
-}
-
-dim3 ray_grid(const CastArgs& a)
-{
-    const int64_t per = (int64_t)(kBlock / 64) * a.lanes;
-    return dim3((unsigned)((a.n_rays + per - 1) / per));
-}
-
-}  // namespace
-
 hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
     const bool amr = args.grid.max_level > 0, td = args.grid.tdual != nullptr;
-    const CastArgs a = spread_rays(args, amr ? 2 : 1);
+    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1);
     const size_t lds = (size_t)(td ? FieldCache<true, true>::kFloats : FieldCache<true>::kFloats) * kBlock *
                        sizeof(float);
-    const dim3 grid = ray_grid(a), blk(kBlock);
+    const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     if (td) {
         if (amr) hipLaunchKernelGGL((cast_static_kernel<true, true>), grid, blk, lds, s, a);
         else hipLaunchKernelGGL((cast_static_kernel<false, true>), grid, blk, lds, s, a);
@@ -1190,36 +1163,36 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(cast_ckpt_kernel<true>, ray_grid(a), dim3(kBlock), lds, s, a);
+        hipLaunchKernelGGL(cast_ckpt_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a);
     else
-        hipLaunchKernelGGL(cast_ckpt_kernel<false>, ray_grid(a), dim3(kBlock), lds, s, a);
+        hipLaunchKernelGGL(cast_ckpt_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_cast_infbeam(const CastArgs& args, float* A, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)2 * FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(cast_infbeam_kernel<true>, ray_grid(a), dim3(kBlock), lds, s, a, A);
+        hipLaunchKernelGGL(cast_infbeam_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, A);
     else
-        hipLaunchKernelGGL(cast_infbeam_kernel<false>, ray_grid(a), dim3(kBlock), lds, s, a, A);
+        hipLaunchKernelGGL(cast_infbeam_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, A);
     return hipGetLastError();
 }
 
 hipError_t launch_cast_tangent(const CastArgs& args, TanEnd* te, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(cast_tangent_kernel<true>, ray_grid(a), dim3(kBlock), lds, s, a, te);
+        hipLaunchKernelGGL(cast_tangent_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, te);
     else
-        hipLaunchKernelGGL(cast_tangent_kernel<false>, ray_grid(a), dim3(kBlock), lds, s, a, te);
+        hipLaunchKernelGGL(cast_tangent_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, te);
     return hipGetLastError();
 }
 
@@ -1235,9 +1208,9 @@ hipError_t launch_tangent_observables(const CastArgs& a, const TanEnd* te, float
 hipError_t launch_cast_order(const CastArgs& args, int order, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.grid.max_level > 0 ? 2 : 1);
+    const CastArgs a = spread_rays(args, args.n_rays, args.grid.max_level > 0 ? 2 : 1);
     const size_t lds = 0;
-    const dim3 grid = ray_grid(a), block(kBlock);
+    const dim3 grid = ray_grid(a, a.n_rays), block(kBlock);
     const bool amr = a.grid.max_level > 0;
     if (order == 0) {
         if (amr) hipLaunchKernelGGL((cast_order_kernel<true, 0>), grid, block, lds, s, a);
@@ -1252,36 +1225,36 @@ hipError_t launch_cast_order(const CastArgs& args, int order, hipStream_t s)
 hipError_t launch_born_beam(const CastArgs& args, float* A, int32_t* status, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(born_beam_kernel<true>, ray_grid(a), dim3(kBlock), lds, s, a, A, status);
+        hipLaunchKernelGGL(born_beam_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, A, status);
     else
-        hipLaunchKernelGGL(born_beam_kernel<false>, ray_grid(a), dim3(kBlock), lds, s, a, A, status);
+        hipLaunchKernelGGL(born_beam_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, A, status);
     return hipGetLastError();
 }
 
 hipError_t launch_cast_surfaces(const CastArgs& args, const double2* surf, int n_extra, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     Surfaces S;
     S.surf = surf;
     S.n_extra = n_extra;
     S.k = 0;
     if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(cast_surfaces_kernel<true>, ray_grid(a), dim3(kBlock), lds, s, a, S);
+        hipLaunchKernelGGL(cast_surfaces_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, S);
     else
-        hipLaunchKernelGGL(cast_surfaces_kernel<false>, ray_grid(a), dim3(kBlock), lds, s, a, S);
+        hipLaunchKernelGGL(cast_surfaces_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, S);
     return hipGetLastError();
 }
 
 hipError_t launch_cast_stop(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
-    const dim3 grid = ray_grid(a), blk(kBlock);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     const bool amr = a.grid.max_level > 0;
     switch (a.surface) {
@@ -1306,8 +1279,8 @@ hipError_t launch_cast_stop(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_diff(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, 1);
-    const dim3 grid = ray_grid(a), blk(kBlock);
+    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     const size_t lds = (size_t)FieldCache<true, false, true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0) hipLaunchKernelGGL(cast_diff_kernel<true>, grid, blk, lds, s, a);
     else hipLaunchKernelGGL(cast_diff_kernel<false>, grid, blk, lds, s, a);

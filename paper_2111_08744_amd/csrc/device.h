@@ -28,19 +28,42 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nblocks)
     return x < r ? x * (q + 1) + idx : r * (q + 1) + (x - r) * q + idx;
 }
 
-// Ray of this lane in the one-ray-per-lane launches: every wave takes a.lanes
+// Rays per wave of a launch of n rays: 64, or fewer where that leaves SIMDs without a
+// wave: the smallest power of two that needs at most `waves` waves per SIMD.
+// A stage stalls the wave when any of its rays enters a new stencil, so waves
+// of fewer rays run a step sooner; beyond one wave per SIMD the additional
+// instructions cost more than that saves, except where the stalls are long (a
+// tree's walk, the 27 cells of TSC), which two waves per SIMD hide better.
+// Uniform 64^3, 3,072 rays to z = 0.3: 64 rays a wave 2.01 ms, 8 1.70, 4 (768
+// waves) 1.65, 2 (1,536) 2.01; 6,144 rays on 64^3 + 5 levels: 1.97, 1.73, 4
+// (1,536 waves) 1.57; TSC there 5.14, 4.19, 3.34.
+inline CastArgs spread_rays(const CastArgs& a, int64_t n, int waves)
+{
+    CastArgs c = a;
+    c.lanes = 64;
+    while (c.lanes > 1 && (n + c.lanes / 2 - 1) / (c.lanes / 2) <= (int64_t)waves * a.simds) c.lanes /= 2;
+    return c;
+}
+
+inline dim3 ray_grid(const CastArgs& a, int64_t n)
+{
+    const int64_t per = (int64_t)(kBlock / 64) * a.lanes;
+    return dim3((unsigned)((n + per - 1) / per));
+}
+
+// Ray (of n) of this lane in the one-ray-per-lane launches: every wave takes a.lanes
 // (a power of two) consecutive rays; its other lanes, and those past the last
 // ray, run copies of them, which write the same values to the same places.
 // (A wave that masks them off instead, with 8 lanes or fewer active and the
 // SIMD to itself, was measured to run at half the speed.)  False for a wave
 // without rays.
-__device__ __forceinline__ bool lane_ray(const CastArgs& a, int64_t& r)
+__device__ __forceinline__ bool lane_ray(const CastArgs& a, int64_t n, int64_t& r)
 {
     const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     r = wave * a.lanes;
-    if (r >= a.n_rays) return false;
+    if (r >= n) return false;
     r += threadIdx.x & (a.lanes - 1);
-    if (r >= a.n_rays) r = a.n_rays - 1;
+    if (r >= n) r = n - 1;
     return true;
 }
 

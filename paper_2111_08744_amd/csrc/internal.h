@@ -193,7 +193,9 @@ hipError_t launch_build_dual_ids(const GridDev& g, const int4* pos, int64_t c0, 
                                  hipStream_t s);
 // Adjoint (defined in adjoint.hip).
 hipError_t launch_cast_checkpointed(const CastArgs& a, hipStream_t s);
-hipError_t launch_adjoint(const AdjointArgs& a, int columns, hipStream_t s);
+hipError_t launch_adjoint(const AdjointArgs& a, hipStream_t s);
+hipError_t launch_adjoint_loss(const AdjointArgs& a, hipStream_t s);
+hipError_t launch_retrace(const AdjointArgs& a, const RayEnd* ends, hipStream_t s);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s);
 hipError_t launch_scatter_grad(const float* grad_lib, const int64_t* perm, float4* out_user, int64_t n,
                                hipStream_t s);

@@ -917,10 +917,10 @@ int make_surface_table(const mpath_grid* g, const mpath_cast_desc* d, const std:
     return MPATH_OK;
 }
 
-// Adjoint workspace: one segment of step states per ray and the cell
-// cotangents in library order.
+// Adjoint workspace: one segment of step states per ray, the cell cotangents
+// in library order, and the tangents and end states of the Jacobian's pass.
 struct AdjointLayout {
-    size_t off_tape, off_grad, total;
+    size_t off_tape, off_grad, off_tan, off_ends, total;
 };
 
 AdjointLayout adjoint_layout(const mpath_grid* g, const mpath_cast_desc* d, int64_t n_rays)
@@ -928,7 +928,9 @@ AdjointLayout adjoint_layout(const mpath_grid* g, const mpath_cast_desc* d, int6
     AdjointLayout L;
     L.off_tape = 0;
     L.off_grad = align_up((size_t)d->checkpoint_every * (size_t)n_rays * sizeof(GeoState), 256);
-    L.total = align_up(L.off_grad + (size_t)grad_accumulator_floats(g->n_cells) * 4, 256);
+    L.off_tan = align_up(L.off_grad + (size_t)grad_accumulator_floats(g->n_cells) * 4, 256);
+    L.off_ends = align_up(L.off_tan + (size_t)n_rays * sizeof(TanEnd), 256);
+    L.total = align_up(L.off_ends + (size_t)n_rays * sizeof(RayEnd), 256);
     return L;
 }
 
@@ -1285,8 +1287,27 @@ int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obse
     A.grad = loss ? grad : nullptr;
     A.n_cells = g->n_cells;
     hipError_t e = hipSuccess;
-    if (loss) e = launch_fill_zero(grad, grad_accumulator_floats(g->n_cells), s);
-    if (!e) e = launch_adjoint(A, jac && loss ? 4 : (jac ? 3 : 1), s);
+    if (list) {
+        // the finder's Newton steps: the three columns of the listed rays
+        e = launch_adjoint(A, s);
+    } else {
+        // The Jacobian comes from the forward-mode tangents of the same cast
+        // (about twice a forward, where three reverse columns take ten), the
+        // cell cotangents from the reverse sweep of the loss's one column;
+        // either finds out whether the rays retrace the forward's.
+        if (ad->jac || ad->dz_dtheta || !loss) {
+            CastArgs t = A.c;
+            t.ends = (RayEnd*)(ws + al.off_ends);
+            TanEnd* te = (TanEnd*)(ws + al.off_tan);
+            e = launch_cast_tangent(t, te, s);
+            if (!e) e = launch_tangent_observables(t, te, ad->jac, ad->dz_dtheta, s);
+            if (!e && !loss) e = launch_retrace(A, t.ends, s);
+        }
+        if (loss) {
+            if (!e) e = launch_fill_zero(grad, grad_accumulator_floats(g->n_cells), s);
+            if (!e) e = launch_adjoint_loss(A, s);
+        }
+    }
     if (!e && ad->dL_dvalues)
         e = launch_scatter_grad(grad, g->perm, (float4*)ad->dL_dvalues, g->n_cells, s);
     if (!e && ad->dL_dphi_total)
