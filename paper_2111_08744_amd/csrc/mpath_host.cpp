@@ -1062,10 +1062,15 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
     } else if (d->checkpoint_every > 0) {
         e = launch_cast_checkpointed(a, s);
     } else {
-        int sched = d->schedule;
-        if (sched == MPATH_SCHED_AUTO) sched = d->n_obs > 1 ? MPATH_SCHED_PERSISTENT : MPATH_SCHED_STATIC;
+        // AUTO is the static schedule: with many observers too, the hardware
+        // refills whole waves, and few rays are spread over the SIMDs.  Uniform
+        // 64^3, sources to z in [0.1, 2], static against persistent: 64 cones of
+        // 16,384 rays 47.3 ms and 48.7, of 64 rays 6.6 and 9.4; 4,096 observers
+        // of 3 rays (lanes of one wave ending at very different steps) 13.7 and
+        // 26.8; 64^3 + 5 levels 31.4 and 30.1, 4.6 and 6.2, 11.1 and 26.0.
+        const int sched = d->schedule;
         const int block = d->block_size ? d->block_size : 256;
-        if (sched == MPATH_SCHED_STATIC) {
+        if (sched != MPATH_SCHED_PERSISTENT) {
             e = launch_cast_static(a, s);
         } else {
             int wpc = d->waves_per_cu;
