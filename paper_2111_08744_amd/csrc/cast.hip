@@ -39,6 +39,7 @@ struct NoSample {
 // Everything one lane carries for its current ray (DP: the form of dPhi/dl).
 template <bool AMR, class FC = FieldCache<AMR>, class DP = ChainRule>
 struct RayRun {
+    static constexpr int C = FC::kComp;   // components of geo, y and the gradient that this lane holds
     int64_t ray;          // -1: no ray
     RayGeom geo;
     double eta_s;
@@ -68,10 +69,10 @@ struct RayRun {
         while (j > 0 && a.obs[j].ray_first > r) --j;
         const ObsDev& ob = a.obs[j];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) geo.vo[i] = ldexp(ob.x[i] / a.grid.h0, a.grid.max_level + 1);
-        geo.n[0] = a.dirs[3 * r];
-        geo.n[1] = a.dirs[3 * r + 1];
-        geo.n[2] = a.dirs[3 * r + 2];
+        for (int i = 0; i < C; ++i) {
+            geo.vo[i] = ldexp(ob.x[FC::own_axis(i)] / a.grid.h0, a.grid.max_level + 1);
+            geo.n[i] = a.dirs[3 * r + FC::own_axis(i)];
+        }
         eta_s = a.ray_stop ? a.ray_stop[r].x : ob.eta_s;
         F.reset();
         n_steps = 0;
@@ -79,7 +80,7 @@ struct RayRun {
         status = -1;
         isw = 0.0;
         if constexpr (DP::kDiff) dp.dl_prev = 0.0;
-        float G[3];
+        float G[C];
         int leafl, l;
         phi_o = __builtin_nanf("");
         if (F.eval(a.grid, geo.vo, G, leafl, l)) status = MPATH_RAY_LEFT_DOMAIN;
@@ -90,7 +91,7 @@ struct RayRun {
         y.eta = a.cosmo_eta0;
         y.K = 1.0;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < C; ++i) {
             y.d[i] = (float)(geo.n[i] * (kmag - 1.0));
             y.dx[i] = 0.0f;
         }
@@ -115,12 +116,17 @@ struct RayRun {
             for (;; ++it) {
                 if (it >= max_iter) return false;
                 if (n_steps >= max_steps) { status = MPATH_RAY_MAX_STEPS; return true; }
-                if (CKPT && n_steps % a.ckpt_every == 0)
-                    a.ckpt[(n_steps / a.ckpt_every) * a.n_rays + ray] = y;
+                if (CKPT && n_steps % a.ckpt_every == 0) {
+                    GeoState& k = a.ckpt[(n_steps / a.ckpt_every) * a.n_rays + ray];
+                    k.eta = y.eta;
+                    k.K = y.K;
+                    FC::whole_vector(y.dx, k.dx);
+                    FC::whole_vector(y.d, k.d);
+                }
                 // leaf level at the step start sets the step length (N steps
                 // per cell); the same evaluation gives stage 0's field
-                double v[3];
-                grid_coords(g, geo, y.eta, y.dx, v);
+                double v[C];
+                grid_coords<C>(g, geo, y.eta, y.dx, v);
                 int L;
                 s0.bad = F.eval(g, v, s0.G, L, s0.l);
                 if constexpr (DP::kDiff) s0.phi = F.phi(g);
@@ -136,7 +142,7 @@ struct RayRun {
                     return true;
                 }
                 if constexpr (FC::kTime) isw += (double)F.isw_step;
-                if (!finite_state(yn)) { status = MPATH_RAY_NONFINITE; return true; }
+                if (!finite_state<FC>(yn)) { status = MPATH_RAY_NONFINITE; return true; }
                 y = yn;
                 ++n_steps;
                 if constexpr (DP::kDiff) {
@@ -157,7 +163,7 @@ struct RayRun {
                 }
                 if (k < 2) dlx = dlx + (yn.eta - eta_s) / yn.K;
             }
-            const bool fin = finite_state(yn);
+            const bool fin = finite_state<FC>(yn);
             if constexpr (FC::kTime) isw += (double)F.isw_step;
             y = yn;
             ++n_steps;
@@ -369,9 +375,9 @@ struct RayRun {
                                                   int st)
     {
         const bool ok = st == MPATH_RAY_REACHED;
-        double v[3];
-        grid_coords(a.grid, geo, y.eta, y.dx, v);
-        float phi_s = __builtin_nanf(""), G[3];
+        double v[C];
+        grid_coords<C>(a.grid, geo, y.eta, y.dx, v);
+        float phi_s = __builtin_nanf(""), G[C];
         int leafl, l;
         if (!F.eval(a.grid, v, G, leafl, l)) phi_s = F.phi(a.grid);
         const OutDev& o = a.out;
@@ -389,7 +395,7 @@ struct RayRun {
         if (o.hash) o.hash[slot] = hash;
         RayEnd e;
         e.eta = y.eta;
-        e.dx[0] = y.dx[0]; e.dx[1] = y.dx[1]; e.dx[2] = y.dx[2];
+        FC::whole_vector(y.dx, e.dx);
         e.obs = j;
         a.ends[slot] = e;
     }
@@ -467,6 +473,21 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_static_kernel(C
     R.F.bind(coef_lds);
     R.start(a, r);
     R.advance(a, 0x7fffffff);
+    R.finish(a);
+}
+
+// Four lanes per ray (QuadRay), with CKPT checkpoints for the adjoint: for
+// casts that leave a SIMD no more than a wave or a few, where the length of a
+// step's instruction sequence decides and not the number of waves.  A step
+// takes about 390 vector instructions against 582 (uniform grid).
+template <bool AMR, bool CKPT>
+__global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_quad_kernel(CastArgs a)
+{
+    int64_t r;
+    if (!lane_ray<4>(a, a.n_rays, r)) return;
+    RayRun<AMR, QuadCache<AMR>> R;
+    R.start(a, r);
+    R.template advance<CKPT>(a, 0x7fffffff);
     R.finish(a);
 }
 
@@ -1232,10 +1253,36 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
 
 }  // namespace
 
+// Whether a cast's rays take four lanes each: where that needs at most two
+// waves per SIMD on a uniform grid, four on a tree.  A quad's wave issues two
+// thirds of the instructions of a step, and waits for no coefficients from
+// LDS, but carries a quarter of the rays; on a tree it also gathers and
+// diverges for 16 rays and not for 64.  One lane against four, uniform 64^3,
+// to z = 0.3: 3,072 rays 1.59 ms and 1.02, 12,288 1.86 and 1.21, 32,768 (two
+// waves) 2.02 and 1.66, 49,152 2.13 and 2.19; 64^3 + 5 levels: 3,072 1.44 and
+// 1.09, 32,768 2.33 and 1.76, 65,536 (four) 2.58 and 2.14, 98,304 2.51 and
+// 2.96.  With checkpoints the same.
+static bool by_quads(const CastArgs& a)
+{
+    return a.n_rays <= (int64_t)(kWave / 4) * a.simds * (a.grid.max_level > 0 ? 4 : 2);
+}
+
+template <bool CKPT>
+static hipError_t launch_cast_quad(const CastArgs& args, hipStream_t s)
+{
+    const bool amr = args.grid.max_level > 0;
+    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1, 16);
+    const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
+    if (amr) hipLaunchKernelGGL((cast_quad_kernel<true, CKPT>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((cast_quad_kernel<false, CKPT>), grid, blk, 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
     const bool amr = args.grid.max_level > 0, td = args.grid.tdual != nullptr;
+    if (!td && by_quads(args)) return launch_cast_quad<false>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1);
     const size_t lds = (size_t)(td ? FieldCache<true, true>::kFloats : FieldCache<true>::kFloats) * kBlock *
                        sizeof(float);
@@ -1253,6 +1300,7 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
+    if (by_quads(args)) return launch_cast_quad<true>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)

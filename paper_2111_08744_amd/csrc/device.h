@@ -37,10 +37,10 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nblocks)
 // Uniform 64^3, 3,072 rays to z = 0.3: 64 rays a wave 2.01 ms, 8 1.70, 4 (768
 // waves) 1.65, 2 (1,536) 2.01; 6,144 rays on 64^3 + 5 levels: 1.97, 1.73, 4
 // (1,536 waves) 1.57; TSC there 5.14, 4.19, 3.34.
-inline CastArgs spread_rays(const CastArgs& a, int64_t n, int waves)
+inline CastArgs spread_rays(const CastArgs& a, int64_t n, int waves, int most = 64)
 {
     CastArgs c = a;
-    c.lanes = 64;
+    c.lanes = most;
     while (c.lanes > 1 && (n + c.lanes / 2 - 1) / (c.lanes / 2) <= (int64_t)waves * a.simds) c.lanes /= 2;
     return c;
 }
@@ -57,12 +57,13 @@ inline dim3 ray_grid(const CastArgs& a, int64_t n)
 // (A wave that masks them off instead, with 8 lanes or fewer active and the
 // SIMD to itself, was measured to run at half the speed.)  False for a wave
 // without rays.
+template <int LANES = 1>
 __device__ __forceinline__ bool lane_ray(const CastArgs& a, int64_t n, int64_t& r)
 {
     const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     r = wave * a.lanes;
     if (r >= n) return false;
-    r += threadIdx.x & (a.lanes - 1);
+    r += threadIdx.x / LANES & (a.lanes - 1);
     if (r >= n) r = n - 1;
     return true;
 }
@@ -239,6 +240,55 @@ __device__ __forceinline__ float trilinear_eval(float c0, float c1, float c2, fl
     return fmaf(tz, c3, fmaf(ty, b, fmaf(tx, a, c0)));
 }
 
+// How the lanes carry a ray's vectors.  WholeRay: one lane, all three
+// components.  QuadRay: four lanes, one component each (the fourth repeats the
+// third), everything that is no vector in all four; the lanes of a quad take
+// every branch together, and a component reaches the others by a lane
+// permutation within the quad.
+struct WholeRay {
+    static constexpr int kComp = 3;     // components a lane holds
+    static __device__ __forceinline__ int own_axis(int i) { return i; }     // axis of its component i
+    static __device__ __forceinline__ float dot(const float m[3], const float G[3])
+    {
+        return fmaf(m[2], G[2], fmaf(m[1], G[1], m[0] * G[0]));
+    }
+    static __device__ __forceinline__ void whole_vector(const float v[3], float all[3])
+    {
+        all[0] = v[0]; all[1] = v[1]; all[2] = v[2];
+    }
+};
+
+struct QuadRay {
+    static constexpr int kComp = 1;
+    template <int P0, int P1, int P2, int P3>
+    static __device__ __forceinline__ uint32_t perm(uint32_t x)
+    {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, P0 | P1 << 2 | P2 << 4 | P3 << 6, 0xf, 0xf, true);
+    }
+    // the value of component K, of the next one and of the one after
+    template <int K>
+    static __device__ __forceinline__ uint32_t of(uint32_t x) { return perm<K, K, K, K>(x); }
+    template <int K>
+    static __device__ __forceinline__ float of(float x) { return __uint_as_float(of<K>(__float_as_uint(x))); }
+    static __device__ __forceinline__ uint32_t next(uint32_t x) { return perm<1, 2, 0, 0>(x); }
+    static __device__ __forceinline__ uint32_t after(uint32_t x) { return perm<2, 0, 1, 1>(x); }
+    static __device__ __forceinline__ uint32_t all_or(uint32_t x) { return x | next(x) | after(x); }
+
+    static __device__ __forceinline__ int own_axis(int)
+    {
+        const int c = threadIdx.x & 3;
+        return c < 2 ? c : 2;
+    }
+    static __device__ __forceinline__ float dot(const float m[1], const float G[1])
+    {
+        return fmaf(of<2>(m[0]), of<2>(G[0]), fmaf(of<1>(m[0]), of<1>(G[0]), of<0>(m[0]) * of<0>(G[0])));
+    }
+    static __device__ __forceinline__ void whole_vector(const float v[1], float all[3])
+    {
+        all[0] = of<0>(v[0]); all[1] = of<1>(v[0]); all[2] = of<2>(v[0]);
+    }
+};
+
 // Child link of a leaf whose stencil record (the 8 cells from it) consists of
 // leaves of its own level only; every other leaf has -1.  A point inside such
 // a dual cell is in a leaf of that level and takes that stencil, whichever of
@@ -280,7 +330,7 @@ constexpr int kWholeLeaf = -2;
 // coefficients of Phi are kept too (for a field evaluation whose Phi is
 // needed at every step; else phi() reads them from the record).
 template <bool AMR, bool TIME = false, bool PHI = false>
-struct FieldCache {
+struct FieldCache : WholeRay {
     static constexpr bool kTime = TIME;
     static constexpr bool kUniform = !AMR;
     static constexpr int kComps = PHI ? 4 : 3;
@@ -512,6 +562,143 @@ struct FieldCache {
     }
 };
 
+// FieldCache for a ray carried by four lanes: the same regions, look-ups and
+// arithmetic, component by component.  A lane evaluates one component of the
+// gradient, whose eight coefficients it keeps in registers.
+template <bool AMR>
+struct QuadCache : QuadRay {
+    static constexpr bool kTime = false;
+    static constexpr bool kUniform = !AMR;
+    int leafL, lvl, base;   // as in FieldCache
+    bool whole;
+    double kd, sc;
+    float t;                // this axis
+    float4 p, q;            // coefficients c0..c3, c4..c7 of this axis's component
+
+    __device__ __forceinline__ void reset()
+    {
+        leafL = -1;
+        lvl = 0;
+        base = 0;
+        whole = true;
+        sc = 0.0;
+        kd = __builtin_nan("");
+    }
+
+    __device__ __forceinline__ bool inside(double v, float& u) const
+    {
+        #pragma clang fp contract(off)
+        u = (float)(AMR ? fma(v, sc, -kd) : fma(v, 0.5, -kd));
+        uint32_t m = __float_as_uint(u);
+        const uint32_t n = next(m);
+        const uint32_t a = after(m);
+        m = n > m ? n : m;
+        m = a > m ? a : m;
+        return m < 0x3f800000u;
+    }
+
+    // Bit k of x at bit 3 k + axis, over the axes.
+    static __device__ __forceinline__ uint32_t interleave(uint32_t x)
+    {
+        return all_or((uint32_t)morton3(x, 0u, 0u) << own_axis(0));
+    }
+
+    __device__ __forceinline__ void load(const GridDev& g, int b)
+    {
+        const float4* src = g.dual + 8 * (int64_t)b + 2 * own_axis(0);
+        p = src[0];
+        q = src[1];
+    }
+
+    __device__ __forceinline__ bool find(const GridDev& g, double v, int& leaf)
+    {
+        #pragma clang fp contract(off)
+        const int Lm = AMR ? g.max_level : 0;
+        const int I = (int)floor(v);
+        const int M = g.n0;
+        const int bc = ((AMR ? I >> Lm : I) - 1) >> 1;
+        bool ok = true;
+        int L = 0, l = 0;
+        if (!g.periodic) {
+            ok = all_or((unsigned)bc < (unsigned)(M - 1) ? 0u : 1u) == 0u;
+            const int Mh = 2 * (M << Lm);
+            if (all_or((unsigned)I < (unsigned)Mh ? 0u : 1u)) L = -1;
+        }
+        int b = (int)interleave((uint32_t)(bc & (M - 1)));
+        load(g, b);
+        bool w = true;
+        if constexpr (AMR) w = ok && g.child[b] == kWholeLeaf;
+        if (AMR && !w && L >= 0) {
+            const int J = (I >> 1) & ((M << Lm) - 1);
+            int id = (int)interleave((uint32_t)(J >> Lm));
+            for (int m = Lm - 1; m >= 0; --m) {
+                const int ch = g.child[id];
+                if (ch < 0) break;
+                id = ch + (int)all_or((uint32_t)((J >> m) & 1) << own_axis(0));
+                ++L;
+            }
+            if (L > 0) {
+                b = g.leafinfo[8 * (int64_t)(id - g.level_start[1]) +
+                               all_or((uint32_t)((I >> (Lm - L)) & 1) << own_axis(0))];
+                ok = b >= 0;
+                if (ok) {
+                    l = level_of(g, b);
+                    w = l > 0 && g.child[b] == kWholeLeaf;
+                    load(g, b);
+                }
+            }
+        }
+        leaf = L;
+        if (!ok) {
+            p = q = make_float4(0.f, 0.f, 0.f, 0.f);
+            t = 0.0f;
+            reset();
+            return false;
+        }
+        if constexpr (AMR) {
+            const int sh = w ? Lm - l : Lm - L;
+            sc = ldexp(1.0, w ? -sh - 1 : -sh);
+            const int k = I >> sh;
+            kd = w ? (double)((k - 1) >> 1) + 0.5 : (double)k;
+            whole = w;
+        } else {
+            kd = (double)bc + 0.5;
+        }
+        leafL = L;
+        lvl = l;
+        base = b;
+        return true;
+    }
+
+    __device__ __forceinline__ int eval(const GridDev& g, const double v[1], float G[1], int& leaf_level,
+                                        int& stencil_level)
+    {
+        #pragma clang fp contract(off)
+        bool ok = true;
+        leaf_level = leafL;
+        if (!inside(v[0], t)) {
+            ok = find(g, v[0], leaf_level);
+            if (ok) (void)inside(v[0], t);
+            else t = 0.0f;
+        }
+        if constexpr (AMR) {
+            if (!whole) {
+                const double sl = ldexp(1.0, lvl - g.max_level - 1);
+                t = (float)(v[0] * sl - 0.5 - (double)((((int)kd >> (leafL - lvl)) - 1) >> 1));
+            }
+        }
+        stencil_level = AMR ? lvl : 0;
+        G[0] = trilinear_eval(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, of<0>(t), of<1>(t), of<2>(t));
+        return ok ? 0 : 1;
+    }
+
+    __device__ __forceinline__ float phi(const GridDev& g) const
+    {
+        const float4 u = g.dual[8 * (int64_t)base + 6], w = g.dual[8 * (int64_t)base + 7];
+        return trilinear_eval(u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w, of<0>(t), of<1>(t), of<2>(t));
+    }
+};
+
 // Leaf containing the point with unwrapped coordinates I at level
 // max_level + 1 (a walk from its coarse cell); its id in id.  Returns its
 // level, or -1 outside a non-periodic box.
@@ -542,7 +729,7 @@ __device__ __forceinline__ int walk_to_leaf(const GridDev& g, const int I[3], in
 // Field by nearest grid point (Sect. 2.2, W_NGP): the values of the deepest
 // cell containing the point.  The lane keeps the last leaf and its values.
 template <bool AMR>
-struct NgpCache {
+struct NgpCache : WholeRay {
     static constexpr bool kTime = false;
     static constexpr bool kUniform = !AMR;
     static constexpr int kFloats = 0;
@@ -606,7 +793,7 @@ struct NgpCache {
 // the position in the centre cell (in [0, 1)), the weights of the cells at
 // -1, 0, +1 are (1 - f)^2 / 2, 3/4 - (f - 1/2)^2 and f^2 / 2.
 template <bool AMR>
-struct TscCache {
+struct TscCache : WholeRay {
     static constexpr bool kTime = false;
     static constexpr bool kUniform = !AMR;
     static constexpr int kFloats = 0;
@@ -826,13 +1013,15 @@ __device__ __forceinline__ double step_length(const CastArgs& a, int L)
 // exactly with x / h_f, elsewhere to one rounding).  Scaling by the power of
 // two is exact, so v is 2^(max_level + 1) times the coarse-grid coordinates
 // computed the same way.
-__device__ __forceinline__ void grid_coords(const GridDev& g, const RayGeom& r, double eta, const float dx[3],
-                                            double v[3])
+// C: components the lane holds.
+template <int C = 3>
+__device__ __forceinline__ void grid_coords(const GridDev& g, const RayGeom& r, double eta, const float dx[C],
+                                            double v[C])
 {
     #pragma clang fp contract(off)
     const double s = g.eta0 - eta;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) v[i] = fma(fma(s, r.n[i], (double)dx[i]), g.inv_hf, r.vo[i]);
+    for (int i = 0; i < C; ++i) v[i] = fma(fma(s, r.n[i], (double)dx[i]), g.inv_hf, r.vo[i]);
 }
 
 // dPhi/dl in the spatial geodesic equation.  ChainRule: grad Phi . k
@@ -915,12 +1104,15 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
                                         const Stage0* s0 = nullptr)
 {
     #pragma clang fp contract(off)
-    const float nf[3] = {(float)r.n[0], (float)r.n[1], (float)r.n[2]};
+    constexpr int C = FC::kComp;
+    float nf[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) nf[i] = (float)r.n[i];
     const double half = 0.5 * dl;
     double acc_eta = 0.0, acc_K = 0.0;
-    float acc_dx[3] = {0.f, 0.f, 0.f}, acc_P[3] = {0.f, 0.f, 0.f};
+    float acc_dx[C] = {}, acc_P[C] = {};
     double f_K = 0.0, Kprev = y.K;
-    float f_dx[3] = {0.f, 0.f, 0.f}, f_P[3] = {0.f, 0.f, 0.f};
+    float f_dx[C] = {}, f_P[C] = {};
     float acc_I = 0.f;
     uint32_t h = hash;
     HubbleCubic Hc;
@@ -946,25 +1138,26 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
             const float rm1 = (float)(y.K - yi.K) * inv;
             const float cK = (cf + cf) * inv;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < C; ++i) {
                 yi.dx[i] = fmaf(cf, f_dx[i], y.dx[i]);
                 yi.d[i] = fmaf(cK, f_P[i], fmaf(rm1, y.d[i], y.d[i]));
             }
         }
-        float G[3];
+        float G[C];
         float phi = 0.0f;
         int l = 0;
         bool bad;
         if (z) {
             // stage 0 at the step start, evaluated by the caller
             phi = z->phi;
-            G[0] = z->G[0]; G[1] = z->G[1]; G[2] = z->G[2];
+#pragma unroll
+            for (int i = 0; i < C; ++i) G[i] = z->G[i];
             l = z->l;
             bad = z->bad != 0;
             if constexpr (FC::kTime) F.tv = z->tv;
         } else {
-            double u[3];
-            grid_coords(g, r, yi.eta, yi.dx, u);
+            double u[C];
+            grid_coords<C>(g, r, yi.eta, yi.dx, u);
             int leafl;
             bad = F.eval(g, u, G, leafl, l) != 0;
             if constexpr (DP::kDiff) {
@@ -974,8 +1167,10 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
         h = fnv(h, (uint32_t)l);
         if (record) rec.stage(st, y, yi, F, G, Hc, cz);
         const double H = Hc(cz, yi.eta);
-        const float m[3] = {nf[0] + yi.d[0], nf[1] + yi.d[1], nf[2] + yi.d[2]};
-        const float mG = fmaf(m[2], G[2], fmaf(m[1], G[1], m[0] * G[0]));
+        float m[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i) m[i] = nf[i] + yi.d[i];
+        const float mG = FC::dot(m, G);
         Kprev = yi.K;
         f_K = yi.K * yi.K * (H - (double)mG);
         const float Kf = (float)yi.K;
@@ -994,7 +1189,7 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
             cm = dp.D / Kf + mG;
         }
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < C; ++i) {
             f_dx[i] = Kf * yi.d[i];
             f_P[i] = K2 * fmaf(hm, yi.d[i], fmaf(cm, m[i], -G[i]));
         }
@@ -1003,7 +1198,7 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
             acc_eta = yi.K;
             acc_K = f_K;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { acc_dx[i] = f_dx[i]; acc_P[i] = f_P[i]; }
+            for (int i = 0; i < C; ++i) { acc_dx[i] = f_dx[i]; acc_P[i] = f_P[i]; }
         } else {
             const double w = st == 3 ? 1.0 : 2.0;
             const float wf = st == 3 ? 1.0f : 2.0f;
@@ -1011,14 +1206,15 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
             acc_eta = fma(w, yi.K, acc_eta);
             acc_K = fma(w, f_K, acc_K);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < C; ++i) {
                 acc_dx[i] = fmaf(wf, f_dx[i], acc_dx[i]);
                 acc_P[i] = fmaf(wf, f_P[i], acc_P[i]);
             }
             // the sums are taken here: the compiler would otherwise move them past
             // the test of the last stage and keep every stage's terms until then
-            asm volatile("" : "+v"(acc_eta), "+v"(acc_K), "+v"(acc_dx[0]), "+v"(acc_dx[1]), "+v"(acc_dx[2]),
-                         "+v"(acc_P[0]), "+v"(acc_P[1]), "+v"(acc_P[2]));
+            asm volatile("" : "+v"(acc_eta), "+v"(acc_K));
+#pragma unroll
+            for (int i = 0; i < C; ++i) asm volatile("" : "+v"(acc_dx[i]), "+v"(acc_P[i]));
         }
         return bad;
     };
@@ -1040,7 +1236,7 @@ __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC
     const float rm1 = (float)(y.K - out.K) * inv;
     const float cK = (h6f + h6f) * inv;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < C; ++i) {
         out.dx[i] = fmaf(h6f, acc_dx[i], y.dx[i]);
         out.d[i] = fmaf(cK, acc_P[i], fmaf(rm1, y.d[i], y.d[i]));
     }
@@ -1083,10 +1279,16 @@ __device__ __forceinline__ int rk4_step_dp(const GridDev& g, const CosmoDev& cz,
 // eta needs no test of its own: it is the start's minus a sum of the stages'
 // K, and a stage's K that is not finite makes its fK and with it the end's K
 // not finite.
+template <class Form = WholeRay>
 __device__ __forceinline__ bool finite_state(const GeoState& y)
 {
-    const float s = ((y.d[0] + y.d[1]) + (y.d[2] + y.dx[0])) + (y.dx[1] + y.dx[2]);
-    return isfinite(y.K) && isfinite(s);
+    if constexpr (Form::kComp == 1) {
+        const float s = y.d[0] + y.dx[0];
+        return isfinite(y.K) && Form::all_or(isfinite(s) ? 0u : 1u) == 0u;
+    } else {
+        const float s = ((y.d[0] + y.d[1]) + (y.d[2] + y.dx[0])) + (y.dx[1] + y.dx[2]);
+        return isfinite(y.K) && isfinite(s);
+    }
 }
 
 }  // namespace mpath

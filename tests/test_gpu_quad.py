@@ -1,0 +1,46 @@
+"""Casts whose rays take four lanes each (by_quads in cast.hip) against the
+persistent schedule, one lane per ray, bit for bit: rays that leave the box of
+a non-periodic grid through every face and edge, partly filled waves, and the
+numbers of rays on both sides of the rule's line."""
+import dataclasses
+
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+COSMO = (0.3, 0.7, 0.7)
+
+
+def _equal(M, grid, n, tag, **kw):
+    import torch
+    runs = [M.cast(grid, M.CastConfig(nside=128, pix_first=[0], pix_count=[n], schedule=s, **kw)) for s in (1, 2)]
+    for k, v in runs[0].items():
+        if not k.startswith("_"):
+            assert torch.equal(v.view(torch.uint8), runs[1][k].view(torch.uint8)), (tag, n, k)
+    return runs[0]
+
+
+@pytest.mark.parametrize("levels", [0, 3])
+@pytest.mark.parametrize("periodic", [True, False])
+def test_four_lanes_a_ray(levels, periodic):
+    import torch
+
+    import paper_2111_08744_amd as M
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    if levels:
+        cells = synth.random_amr_cells(16, 125.0, levels, seed=5, periodic=periodic)
+    else:
+        cells = dataclasses.replace(synth.make_cells("gauss32"), periodic=periodic)
+    grid = M.Grid(cells, COSMO)
+    for f in (0.47, 0.03):
+        kw = dict(obs=[f * cells.box, 0.5 * cells.box, 0.6 * cells.box], stop=0.7 * cells.box, stop_kind="chi", steps_per_cell=3,
+                  adaptive=levels > 0)
+        for n in (1, 15, 17, 1025, 16391):
+            print(levels, periodic, f, n, flush=True)
+            out = _equal(M, grid, n, (levels, periodic, f), **kw)
+        assert periodic or int((out["status"] != 0).sum()) > 0
+    line = 64 * torch.cuda.get_device_properties(0).multi_processor_count * (4 if levels else 2)
+    for n in (line, line + 1):
+        _equal(M, grid, n, "line", **{**kw, "stop": 0.05 * cells.box})
