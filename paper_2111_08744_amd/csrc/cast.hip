@@ -297,7 +297,6 @@ struct RayRun {
         }
     }
 
-    // Outputs at the end of advance_stop: the end point's own scale factor.
     // advance() for a plain cast (iso-eta stop, chain rule, static
     // potential) with a stage recorder T that also sees every step's start
     // and end: T.begin_step(y, dl, regular) before the RK4 pass it records
@@ -310,22 +309,25 @@ struct RayRun {
         if (status >= 0) return;
         const GridDev& g = a.grid;
         ChainRule cr;
+        constexpr bool kUnrolled = C == 1;
         for (;;) {
             if (n_steps >= a.max_steps) { status = MPATH_RAY_MAX_STEPS; return; }
-            double v[3];
-            grid_coords(g, geo, y.eta, y.dx, v);
-            const int L = F.leaf(g, v);
+            double v[C];
+            grid_coords<C>(g, geo, y.eta, y.dx, v);
+            int L;
+            Stage0 s0;                 // the field at the step start: stage 0
+            s0.bad = F.eval(g, v, s0.G, L, s0.l);
             if (L < 0) { status = MPATH_RAY_LEFT_DOMAIN; return; }
             hash = fnv(hash, (uint32_t)L);
             const double dl = quotient(step_length(a, L), y.K);
             if (fma(-y.K, dl, y.eta) < eta_s) break;
             GeoState yn;
             T.begin_step(y, dl, true);
-            if (rk4_core<FC, Tan, ChainRule, false>(g, a.cosmo, F, geo, y, dl, yn, hash, T, true, cr)) {
+            if (rk4_core<FC, Tan, ChainRule, kUnrolled>(g, a.cosmo, F, geo, y, dl, yn, hash, T, true, cr, &s0)) {
                 status = MPATH_RAY_LEFT_DOMAIN;
                 return;
             }
-            if (!finite_state(yn)) { status = MPATH_RAY_NONFINITE; return; }
+            if (!finite_state<FC>(yn)) { status = MPATH_RAY_NONFINITE; return; }
             T.end_step(y, yn);
             y = yn;
             ++n_steps;
@@ -341,13 +343,14 @@ struct RayRun {
             }
             if (k < 2) dlx = dlx + (yn.eta - eta_s) / yn.K;
         }
-        const bool fin = finite_state(yn);
+        const bool fin = finite_state<FC>(yn);
         T.end_step(y, yn);
         y = yn;
         ++n_steps;
         status = fin ? MPATH_RAY_REACHED : MPATH_RAY_NONFINITE;
     }
 
+    // Outputs at the end of advance_stop: the end point's own scale factor.
     __device__ __forceinline__ void finish_stop(const CastArgs& a)
     {
         int j = a.n_obs - 1;
@@ -947,22 +950,31 @@ __global__ void permute_values_kernel(float4* payload, const int64_t* perm, cons
 // source surface; its pass is differentiated at fixed length and the end
 // tangent projected along the flow afterwards (tangent_observables_kernel).
 // ---------------------------------------------------------------------------
+//
+// The kernels are bound by instruction issue, so a stage's factors common to
+// both tangents are formed once, the three scalar products in dpsi are one sum
+// over the axes, and the scale of JG goes onto the displacement it multiplies.
+// Every operation is written out (no contraction), so that one and four lanes
+// a ray (Form) give the same bits.
+template <class Form>
 struct TangentPair {
-    float n[3];                                   // initial direction
-    float e[2][3];                                // e_b
-    float dEta[2], dK[2], dX[2][3], dQ[2][3];     // tangents at the step start
-    float fEta[2], fK[2], fX[2][3], fQ[2][3];     // their derivative at the previous stage
-    float aEta[2], aK[2], aX[2][3], aQ[2][3];     // sum of w_i times it over the stages
+    static constexpr int C = Form::kComp;
+    float n[C];                                   // initial direction
+    float e[2][C];                                // e_b
+    float dEta[2], dK[2], dX[2][C], dQ[2][C];     // tangents at the step start
+    float fEta[2], fK[2], fX[2][C], fQ[2][C];     // their derivative at the previous stage
+    float aEta[2], aK[2], aX[2][C], aQ[2][C];     // sum of w_i times it over the stages
     float rho[2];                                  // d(dl)/dl of the recorded pass
     float dlf;                                     // its affine length
     double eta0;
     float inv_h0;
 
-    __device__ __forceinline__ void init(const CastArgs& a, const RayGeom& geo, float phi_o)
+    // v: the initial direction
+    __device__ __forceinline__ void init(const CastArgs& a, const double v[3], float phi_o)
     {
+        #pragma clang fp contract(off)
         eta0 = a.cosmo_eta0;
         inv_h0 = (float)a.grid.inv_h0;
-        const double* v = geo.n;
         const double rh = hypot(v[0], v[1]);
         const double cp = rh > 0.0 ? v[0] / rh : 1.0, sp = rh > 0.0 ? v[1] / rh : 0.0;
         const double ct = v[2], st = rh;
@@ -970,15 +982,19 @@ struct TangentPair {
         // k = kmag n at the observer, so dk = kmag e_b there and dQ = (kmag - 1) e_b
         const double po = (double)phi_o;
         const float km1 = (float)(sqrt((1.0 + 2.0 * po) / (1.0 - 2.0 * po)) - 1.0);
+        auto own = [&](const double* u, int i) {
+            const int ax = Form::own_axis(i);
+            return (float)(ax == 0 ? u[0] : ax == 1 ? u[1] : u[2]);
+        };
 #pragma unroll
-        for (int i = 0; i < 3; ++i) n[i] = (float)v[i];
+        for (int i = 0; i < C; ++i) n[i] = own(v, i);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             dEta[b] = 0.0f;
             dK[b] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                e[b][i] = (float)eb[b][i];
+            for (int i = 0; i < C; ++i) {
+                e[b][i] = own(eb[b], i);
                 dX[b][i] = 0.0f;
                 dQ[b][i] = km1 * e[b][i];
             }
@@ -995,19 +1011,20 @@ struct TangentPair {
             aEta[b] = 0.0f;
             aK[b] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { aX[b][i] = 0.0f; aQ[b][i] = 0.0f; }
+            for (int i = 0; i < C; ++i) { aX[b][i] = 0.0f; aQ[b][i] = 0.0f; }
         }
     }
 
     // Y - y in the physical variables: (eta, K, x, k) differences
-    __device__ __forceinline__ void diff(const GeoState& y, const GeoState& Y, float& De, float& DK, float Dx[3],
-                                         float Dk[3]) const
+    __device__ __forceinline__ void diff(const GeoState& y, const GeoState& Y, float& De, float& DK, float Dx[C],
+                                         float Dk[C]) const
     {
+        #pragma clang fp contract(off)
         De = (float)(Y.eta - y.eta);
         DK = (float)(Y.K - y.K);
         const float KY = (float)Y.K, Ky = (float)y.K;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < C; ++i) {
             Dx[i] = fmaf(-De, n[i], Y.dx[i] - y.dx[i]);
             Dk[i] = fmaf(DK, n[i], fmaf(KY, Y.d[i], -Ky * y.d[i]));
         }
@@ -1017,86 +1034,101 @@ struct TangentPair {
     __device__ __forceinline__ void stage(int st, const GeoState& y, const GeoState& yi, const FC& F,
                                           const float* G, const HubbleCubic& Hc, const CosmoDev& cz)
     {
+        #pragma clang fp contract(off)
         const float c = st == 0 ? 0.0f : (st == 3 ? 1.0f : 0.5f);
         const float cdl = c * dlf;
         const float w = (st == 0 || st == 3) ? 1.0f : 2.0f;
         const float Kf = (float)yi.K;
-        float k[3];
+        float k[C], Gk[C];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) k[i] = Kf * (n[i] + yi.d[i]);
+        for (int i = 0; i < C; ++i) {
+            k[i] = Kf * (n[i] + yi.d[i]);
+            Gk[i] = G[i] * k[i];
+        }
         const float s = (float)(eta0 - yi.eta);
         const float H = (float)Hc(cz, yi.eta), dH = (float)Hc.deriv(cz, yi.eta);
-        const float psi = G[0] * k[0] + G[1] * k[1] + G[2] * k[2];
-        float De, DK, Dx[3], Dk[3];
+        const float psi = Form::sum(Gk);
+        float De, DK, Dx[C], Dk[C];
         diff(y, yi, De, DK, Dx, Dk);
         // spatial derivative of the interpolated gradient: the t-derivatives
         // of the stencil's trilinear interpolant times 2^lvl / h0
-        const float tx = F.t[0], ty = F.t[1], tz = F.t[2];
+        float t[3];
+        F.offsets(t);
         const float sc = ldexpf(inv_h0, F.lvl);
-        float JG[3][3];
+        float JG[C][3];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const float4 lo = F.quad(j, 0), hi = F.quad(j, 1);
-            const float c1 = lo.y, c2 = lo.z, c3 = lo.w, c4 = hi.x, c5 = hi.y, c6 = hi.z, c7 = hi.w;
-            JG[j][0] = (c1 + ty * c4 + tz * c5 + ty * tz * c7) * sc;
-            JG[j][1] = (c2 + tx * c4 + tz * c6 + tx * tz * c7) * sc;
-            JG[j][2] = (c3 + tx * c5 + ty * c6 + tx * ty * c7) * sc;
+        for (int j = 0; j < C; ++j) {
+            float4 p, q;            // c0..c3, c4..c7
+            F.coefs(j, p, q);
+            JG[j][0] = fmaf(t[2], q.y, fmaf(t[1], fmaf(t[2], q.w, q.x), p.y));
+            JG[j][1] = fmaf(t[2], q.z, fmaf(t[0], fmaf(t[2], q.w, q.x), p.z));
+            JG[j][2] = fmaf(t[1], q.z, fmaf(t[0], fmaf(t[1], q.w, q.y), p.w));
         }
+        const float K2 = Kf + Kf;
+        const float hk = dH * K2;                         // 2 H' K
+        const float hk2 = hk * Kf;                        // 2 H' K^2
+        const float h2 = H + H;
+        const float cq = fmaf(h2, Kf, psi + psi);         // 2 H K + 2 psi
+        const float ck0 = fmaf(h2, K2, -(psi + psi));     // 4 H K - 2 psi
+        const float cg = -K2 * Kf, cK = -(K2 + K2);       // -2 K^2, -4 K
+        const float ce = (K2 + K2) * psi;                 // 4 psi K
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            float te = dEta[b], tK = dK[b], tX[3], tQ[3];
+            float te = dEta[b], tK = dK[b], tX[C], tQ[C];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { tX[i] = dX[b][i]; tQ[i] = dQ[b][i]; }
+            for (int i = 0; i < C; ++i) { tX[i] = dX[b][i]; tQ[i] = dQ[b][i]; }
             if (st > 0) {
-                te += cdl * fEta[b] + rho[b] * De;
-                tK += cdl * fK[b] + rho[b] * DK;
+                te = fmaf(rho[b], De, fmaf(cdl, fEta[b], te));
+                tK = fmaf(rho[b], DK, fmaf(cdl, fK[b], tK));
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    tX[i] += cdl * fX[b][i] + rho[b] * Dx[i];
-                    tQ[i] += cdl * fQ[b][i] + rho[b] * Dk[i];
+                for (int i = 0; i < C; ++i) {
+                    tX[i] = fmaf(rho[b], Dx[i], fmaf(cdl, fX[b][i], tX[i]));
+                    tQ[i] = fmaf(rho[b], Dk[i], fmaf(cdl, fQ[b][i], tQ[i]));
                 }
             }
-            float dxf[3], dG[3];
+            float dx[C], dxf[3], dG[C], pk[C];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) dxf[i] = s * e[b][i] + tX[i];
+            for (int i = 0; i < C; ++i) dx[i] = sc * fmaf(s, e[b][i], tX[i]);
+            Form::whole_vector(dx, dxf);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) dG[j] = JG[j][0] * dxf[0] + JG[j][1] * dxf[1] + JG[j][2] * dxf[2];
-            const float dpsi = (dG[0] * k[0] + dG[1] * k[1] + dG[2] * k[2]) +
-                               Kf * (G[0] * e[b][0] + G[1] * e[b][1] + G[2] * e[b][2]) +
-                               (G[0] * tQ[0] + G[1] * tQ[1] + G[2] * tQ[2]);
-            fEta[b] = -tK;
-            fK[b] = 2.0f * dH * Kf * Kf * te + (4.0f * H * Kf - 2.0f * psi) * tK - 2.0f * Kf * dpsi;
-            const float ck = 2.0f * dH * te * Kf + 2.0f * H * tK + 2.0f * dpsi;
-            const float cq = 2.0f * H * Kf + 2.0f * psi;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                fX[b][i] = tQ[i];
-                fQ[b][i] = ck * k[i] + cq * tQ[i] - 2.0f * Kf * Kf * dG[i] - 4.0f * Kf * tK * G[i] +
-                           4.0f * psi * Kf * e[b][i];
+            for (int j = 0; j < C; ++j) {
+                dG[j] = fmaf(JG[j][2], dxf[2], fmaf(JG[j][1], dxf[1], JG[j][0] * dxf[0]));
+                pk[j] = fmaf(G[j], fmaf(Kf, e[b][j], tQ[j]), dG[j] * k[j]);
             }
-            aEta[b] += w * fEta[b];
-            aK[b] += w * fK[b];
+            const float dpsi = Form::sum(pk);
+            fEta[b] = -tK;
+            fK[b] = fmaf(hk2, te, fmaf(ck0, tK, -K2 * dpsi));
+            const float ck = fmaf(hk, te, fmaf(h2, tK, dpsi + dpsi));
+            const float cG = cK * tK;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                aX[b][i] += w * fX[b][i];
-                aQ[b][i] += w * fQ[b][i];
+            for (int i = 0; i < C; ++i) {
+                fX[b][i] = tQ[i];
+                fQ[b][i] = fmaf(ck, k[i], fmaf(cq, tQ[i], fmaf(cg, dG[i], fmaf(cG, G[i], ce * e[b][i]))));
+            }
+            aEta[b] = fmaf(w, fEta[b], aEta[b]);
+            aK[b] = fmaf(w, fK[b], aK[b]);
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                aX[b][i] = fmaf(w, fX[b][i], aX[b][i]);
+                aQ[b][i] = fmaf(w, fQ[b][i], aQ[b][i]);
             }
         }
     }
 
     __device__ __forceinline__ void end_step(const GeoState& y, const GeoState& yn)
     {
-        float De, DK, Dx[3], Dk[3];
+        #pragma clang fp contract(off)
+        float De, DK, Dx[C], Dk[C];
         diff(y, yn, De, DK, Dx, Dk);
         const float h6 = dlf * (1.0f / 6.0f);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            dEta[b] += h6 * aEta[b] + rho[b] * De;
-            dK[b] += h6 * aK[b] + rho[b] * DK;
+            dEta[b] = fmaf(rho[b], De, fmaf(h6, aEta[b], dEta[b]));
+            dK[b] = fmaf(rho[b], DK, fmaf(h6, aK[b], dK[b]));
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                dX[b][i] += h6 * aX[b][i] + rho[b] * Dx[i];
-                dQ[b][i] += h6 * aQ[b][i] + rho[b] * Dk[i];
+            for (int i = 0; i < C; ++i) {
+                dX[b][i] = fmaf(rho[b], Dx[i], fmaf(h6, aX[b][i], dX[b][i]));
+                dQ[b][i] = fmaf(rho[b], Dk[i], fmaf(h6, aQ[b][i], dQ[b][i]));
             }
         }
     }
@@ -1105,17 +1137,19 @@ struct TangentPair {
 // The cast with the two tangents: the primal outputs of the plain cast (bit
 // for bit) and the tangent end states for tangent_observables_kernel.
 // The tangents take registers the plain cast has not: two waves per SIMD.
-template <bool AMR>
+// QUAD: four lanes per ray.
+template <bool AMR, bool QUAD>
 __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, TanEnd* te)
 {
     extern __shared__ float coef_lds[];
+    using FC = typename std::conditional<QUAD, QuadCache<AMR>, FieldCache<AMR>>::type;
     int64_t r;
-    if (!lane_ray(a, a.n_rays, r)) return;
-    RayRun<AMR> R;
-    R.F.bind(coef_lds);
+    if (!lane_ray<QUAD ? 4 : 1>(a, a.n_rays, r)) return;
+    RayRun<AMR, FC> R;
+    if constexpr (!QUAD) R.F.bind(coef_lds);
     R.start(a, r);
-    TangentPair T;
-    T.init(a, R.geo, R.phi_o);
+    TangentPair<FC> T;
+    T.init(a, a.dirs + 3 * r, R.phi_o);
     R.advance_recorded(a, T);
     R.finish(a);           // leaves the end point's stencil in R.F
     TanEnd e;
@@ -1123,11 +1157,9 @@ __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, Tan
     for (int b = 0; b < 2; ++b) {
         e.deta[b] = T.dEta[b];
         e.dK[b] = T.dK[b];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) e.dX[b][i] = T.dX[b][i];
+        FC::whole_vector(T.dX[b], e.dX[b]);
     }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) e.d[i] = R.y.d[i];
+    FC::whole_vector(R.y.d, e.d);
     e.phi_o = R.phi_o;
     e.K = R.y.K;
     e.base = R.F.base;
@@ -1262,10 +1294,12 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
 // waves) 2.02 and 1.66, 49,152 2.13 and 2.19; 64^3 + 5 levels: 3,072 1.44 and
 // 1.09, 32,768 2.33 and 1.76, 65,536 (four) 2.58 and 2.14, 98,304 2.51 and
 // 2.96.  With checkpoints the same.
-static bool by_quads(const CastArgs& a)
+static bool by_quads(const CastArgs& a, int waves)
 {
-    return a.n_rays <= (int64_t)(kWave / 4) * a.simds * (a.grid.max_level > 0 ? 4 : 2);
+    return a.n_rays <= (int64_t)(kWave / 4) * a.simds * waves;
 }
+
+static int quad_waves(const CastArgs& a) { return a.grid.max_level > 0 ? 4 : 2; }
 
 template <bool CKPT>
 static hipError_t launch_cast_quad(const CastArgs& args, hipStream_t s)
@@ -1282,7 +1316,7 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
     const bool amr = args.grid.max_level > 0, td = args.grid.tdual != nullptr;
-    if (!td && by_quads(args)) return launch_cast_quad<false>(args, s);
+    if (!td && by_quads(args, quad_waves(args))) return launch_cast_quad<false>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1);
     const size_t lds = (size_t)(td ? FieldCache<true, true>::kFloats : FieldCache<true>::kFloats) * kBlock *
                        sizeof(float);
@@ -1300,7 +1334,7 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    if (by_quads(args)) return launch_cast_quad<true>(args, s);
+    if (by_quads(args, quad_waves(args))) return launch_cast_quad<true>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
@@ -1326,12 +1360,21 @@ hipError_t launch_cast_infbeam(const CastArgs& args, float* A, hipStream_t s)
 hipError_t launch_cast_tangent(const CastArgs& args, TanEnd* te, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
-    const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
-    if (a.grid.max_level > 0)
-        hipLaunchKernelGGL(cast_tangent_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, te);
-    else
-        hipLaunchKernelGGL(cast_tangent_kernel<false>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a, te);
+    // four lanes a ray up to two waves per SIMD (registers admit no more):
+    // 12,288 rays 3.51 ms and 2.06, 32,768 3.68 and 3.25, 49,152 3.82 and 4.59
+    // (uniform); 2.85 and 1.93, 3.29 and 2.38, 3.34 and 3.60 (tree)
+    const bool quad = by_quads(args, 2);
+    const CastArgs a = quad ? spread_rays(args, args.n_rays, 1, kWave / 4) : spread_rays(args, args.n_rays, 1);
+    const bool amr = a.grid.max_level > 0;
+    const size_t lds = quad ? 0 : (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
+    const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
+    if (quad) {
+        if (amr) hipLaunchKernelGGL((cast_tangent_kernel<true, true>), grid, blk, lds, s, a, te);
+        else hipLaunchKernelGGL((cast_tangent_kernel<false, true>), grid, blk, lds, s, a, te);
+    } else {
+        if (amr) hipLaunchKernelGGL((cast_tangent_kernel<true, false>), grid, blk, lds, s, a, te);
+        else hipLaunchKernelGGL((cast_tangent_kernel<false, false>), grid, blk, lds, s, a, te);
+    }
     return hipGetLastError();
 }
 

@@ -252,6 +252,11 @@ struct WholeRay {
     {
         return fmaf(m[2], G[2], fmaf(m[1], G[1], m[0] * G[0]));
     }
+    static __device__ __forceinline__ float sum(const float v[3])
+    {
+        #pragma clang fp contract(off)
+        return v[0] + v[1] + v[2];
+    }
     static __device__ __forceinline__ void whole_vector(const float v[3], float all[3])
     {
         all[0] = v[0]; all[1] = v[1]; all[2] = v[2];
@@ -282,6 +287,11 @@ struct QuadRay {
     static __device__ __forceinline__ float dot(const float m[1], const float G[1])
     {
         return fmaf(of<2>(m[0]), of<2>(G[0]), fmaf(of<1>(m[0]), of<1>(G[0]), of<0>(m[0]) * of<0>(G[0])));
+    }
+    static __device__ __forceinline__ float sum(const float v[1])
+    {
+        #pragma clang fp contract(off)
+        return of<0>(v[0]) + of<1>(v[0]) + of<2>(v[0]);
     }
     static __device__ __forceinline__ void whole_vector(const float v[1], float all[3])
     {
@@ -369,6 +379,14 @@ struct FieldCache : WholeRay {
 
     // coefficient quad o (0: c0..c3, 1: c4..c7) of component f
     __device__ __forceinline__ float4 quad(int f, int o) const { return c[64 * (2 * f + o)]; }
+
+    // component i's coefficients, and the offsets along the three axes
+    __device__ __forceinline__ void coefs(int i, float4& p, float4& q) const
+    {
+        p = quad(i, 0);
+        q = quad(i, 1);
+    }
+    __device__ __forceinline__ void offsets(float o[3]) const { o[0] = t[0]; o[1] = t[1]; o[2] = t[2]; }
 
     __device__ __forceinline__ float tri(int f) const
     {
@@ -584,6 +602,13 @@ struct QuadCache : QuadRay {
         sc = 0.0;
         kd = __builtin_nan("");
     }
+
+    __device__ __forceinline__ void coefs(int, float4& a, float4& b) const
+    {
+        a = p;
+        b = q;
+    }
+    __device__ __forceinline__ void offsets(float o[3]) const { o[0] = of<0>(t); o[1] = of<1>(t); o[2] = of<2>(t); }
 
     __device__ __forceinline__ bool inside(double v, float& u) const
     {

@@ -14,11 +14,13 @@ COSMO = (0.3, 0.7, 0.7)
 
 def _equal(M, grid, n, tag, **kw):
     import torch
-    runs = [M.cast(grid, M.CastConfig(nside=128, pix_first=[0], pix_count=[n], schedule=s, **kw)) for s in (1, 2)]
-    for k, v in runs[0].items():
+    one, four = (M.cast(grid, M.CastConfig(nside=128, pix_first=[0], pix_count=[n], schedule=s, **kw)) for s in (2, 1))
+    with_tangents = M.jacobian(grid, M.CastConfig(nside=128, pix_first=[0], pix_count=[n], **kw))
+    for k, v in one.items():
         if not k.startswith("_"):
-            assert torch.equal(v.view(torch.uint8), runs[1][k].view(torch.uint8)), (tag, n, k)
-    return runs[0]
+            assert torch.equal(v.view(torch.uint8), four[k].view(torch.uint8)), (tag, n, k)
+            assert torch.equal(v.view(torch.uint8), with_tangents[k].view(torch.uint8)), (tag, n, k)
+    return four
 
 
 @pytest.mark.parametrize("levels", [0, 3])
