@@ -305,6 +305,16 @@ struct QuadRay {
 // the 8 cells holds it.
 constexpr int kWholeLeaf = -2;
 
+// A cached region that is the stencil's dual cell (FieldCache::off).
+constexpr uint32_t kDual = ~0u;
+
+// Interleaved coordinates m with `one` (0 or the axis's lowest bit) added to
+// the axis whose bits are `lanes`, wrapping.
+__device__ __forceinline__ uint32_t step_up(uint32_t m, uint32_t lanes, uint32_t one)
+{
+    return (m & ~lanes) | (((m | ~lanes) + one) & lanes);
+}
+
 // Field value interpolated at one point, with the lane's cache of the last
 // resolved 8-cell stencil (as trilinear coefficients) and of the region of
 // points that resolve to it.
@@ -349,7 +359,8 @@ struct FieldCache : WholeRay {
     int leafL;          // leaf level of the points of the cached region
     int lvl;            // level of the resolved stencil
     int base;           // id of its lowest corner cell
-    bool whole;         // the region is the stencil's dual cell (AMR)
+    uint32_t off, offz; // AMR, region a half-cell: its place in the stencil (see locate), x and y in
+                        // 16 bits each; kDual: the region is the stencil's dual cell
     double kd[3], sc;   // the region
     float t[3];         // offsets of the last evaluated point in that stencil
     float4* c;          // quad o of this lane at c[64 o]: per component (gx, gy, gz[, phi]
@@ -372,7 +383,7 @@ struct FieldCache : WholeRay {
         leafL = -1;
         lvl = 0;
         base = 0;
-        whole = true;
+        off = kDual;
         sc = 0.0;
         kd[0] = kd[1] = kd[2] = __builtin_nan("");      // no point is inside
     }
@@ -407,14 +418,16 @@ struct FieldCache : WholeRay {
     }
     __device__ __forceinline__ void wait() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-    // u of the point in the cached region; true when it lies inside
-    __device__ __forceinline__ bool inside(const double v[3], float u[3]) const
+    // u of the point in the cached region (w before its conversion); true when
+    // it lies inside
+    __device__ __forceinline__ bool inside(const double v[3], double w[3], float u[3]) const
     {
         #pragma clang fp contract(off)
         uint32_t m = 0u;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            u[d] = (float)(AMR ? fma(v[d], sc, -kd[d]) : fma(v[d], 0.5, -kd[d]));
+            w[d] = AMR ? fma(v[d], sc, -kd[d]) : fma(v[d], 0.5, -kd[d]);
+            u[d] = (float)w[d];
             const uint32_t b = __float_as_uint(u[d]);
             m = b > m ? b : m;
         }
@@ -456,22 +469,26 @@ struct FieldCache : WholeRay {
         bool w = true;
         if constexpr (AMR) w = ok && g.child[b] == kWholeLeaf;
         if (AMR && !w && L >= 0) {
-            const int Mf = M << Lm;
-            int J[3];
+            // the coarse cell: b, or the next one along the axes where the point is
+            // in its lower half
+            const uint32_t bits = (1u << (3 * __builtin_ctz((unsigned)M))) - 1u;
+            uint32_t id = (uint32_t)b;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) J[d] = (I[d] >> 1) & (Mf - 1);      // level max_level
-            int id = (int)morton3((uint32_t)(J[0] >> Lm), (uint32_t)(J[1] >> Lm), (uint32_t)(J[2] >> Lm));
-            for (int m = Lm - 1; m >= 0; --m) {
+            for (int d = 0; d < 3; ++d) {
+                const uint32_t lanes = (0x49249249u << d) & bits;
+                id = step_up(id, lanes, (uint32_t)(~(I[d] >> Lm) & 1) << d);
+            }
+            for (int m = Lm; m > 0; --m) {
                 const int ch = g.child[id];
                 if (ch < 0) break;
-                id = ch + (((J[0] >> m) & 1) | (((J[1] >> m) & 1) << 1) | (((J[2] >> m) & 1) << 2));
+                id = ch + (((I[0] >> m) & 1) | (((I[1] >> m) & 1) << 1) | (((I[2] >> m) & 1) << 2));
                 ++L;
             }
             // a point in a leaf of level 0 takes the level-0 stencil (or none at
             // the edge of a non-periodic box)
             if (L > 0) {
                 const int sh = Lm - L;
-                b = g.leafinfo[8 * (int64_t)(id - g.level_start[1]) +
+                b = g.leafinfo[8 * (int64_t)((int)id - g.level_start[1]) +
                                (((I[0] >> sh) & 1) | (((I[1] >> sh) & 1) << 1) | (((I[2] >> sh) & 1) << 2))];
                 ok = b >= 0;
                 if (ok) {
@@ -493,14 +510,29 @@ struct FieldCache : WholeRay {
         }
         if constexpr (AMR) {
             const int sh = w ? Lm - l : Lm - L;
-            // u = v 2^-sh - k in the half-cell k, u = v 2^-(sh + 1) - (b + 1/2) in the dual cell
+            // u = v 2^-sh - k in the half-cell k, u = v 2^-(sh + 1) - (b + 1/2)
+            // in the dual cell, b + 1/2 = ((k - 1) | 1) / 2
             sc = ldexp(1.0, w ? -sh - 1 : -sh);
+            int k[3];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int k = I[d] >> sh;
-                kd[d] = w ? (double)((k - 1) >> 1) + 0.5 : (double)k;
+            for (int d = 0; d < 3; ++d) k[d] = I[d] >> sh;
+            off = kDual;
+            if (w) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) kd[d] = 0.5 * (double)((k[d] - 1) | 1);
+            } else {
+                // half-cell k of the leaf's level L; the stencil's lowest centre is
+                // half-cell boundary 2^(s + 1) b + 2^s, b = ((k >> s) - 1) >> 1
+                const int s = L - l;
+                uint32_t o[3];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    kd[d] = (double)k[d];
+                    o[d] = (uint32_t)(k[d] - ((((k[d] >> s) - 1) | 1) << s));
+                }
+                off = o[0] | o[1] << 16;
+                offz = o[2];
             }
-            whole = w;
         } else {
 #pragma unroll
             for (int d = 0; d < 3; ++d) kd[d] = (double)bc[d] + 0.5;
@@ -519,24 +551,25 @@ struct FieldCache : WholeRay {
     __device__ __forceinline__ bool locate(const GridDev& g, const double v[3], int& leaf_level)
     {
         #pragma clang fp contract(off)
+        double w[3];
         float u[3];
         bool ok = true;
         leaf_level = leafL;
-        if (!inside(v, u)) {
+        if (!inside(v, w, u)) {
             ok = find(g, v, leaf_level);
-            if (ok) (void)inside(v, u);
+            if (ok) (void)inside(v, w, u);
             else u[0] = u[1] = u[2] = 0.0f;
         }
         t[0] = u[0]; t[1] = u[1]; t[2] = u[2];
         if constexpr (AMR) {
-            if (!whole) {
-                // offsets from the stencil's lowest corner at its own level
-                // (v 2^(lvl - Lm - 1) is exact; kd holds the half-cell)
-                const int s = leafL - lvl;
-                const double sl = ldexp(1.0, lvl - g.max_level - 1);
-#pragma unroll
-                for (int d = 0; d < 3; ++d)
-                    t[d] = (float)(v[d] * sl - 0.5 - (double)((((int)kd[d] >> s) - 1) >> 1));
+            if (off != kDual) {
+                // the half-cell's place counted from the stencil's lowest centre
+                // in half-cells, and the point's in it, in units of 2^(s + 1)
+                // half-cells (the sum in double precision: one rounding, to t)
+                const int e = lvl - leafL - 1;
+                t[0] = ldexpf((float)(w[0] + (double)(off & 0xffffu)), e);
+                t[1] = ldexpf((float)(w[1] + (double)(off >> 16)), e);
+                t[2] = ldexpf((float)(w[2] + (double)offz), e);
             }
         }
         return ok;
@@ -588,7 +621,7 @@ struct QuadCache : QuadRay {
     static constexpr bool kTime = false;
     static constexpr bool kUniform = !AMR;
     int leafL, lvl, base;   // as in FieldCache
-    bool whole;
+    uint32_t off;           // this axis's
     double kd, sc;
     float t;                // this axis
     float4 p, q;            // coefficients c0..c3, c4..c7 of this axis's component
@@ -598,7 +631,7 @@ struct QuadCache : QuadRay {
         leafL = -1;
         lvl = 0;
         base = 0;
-        whole = true;
+        off = kDual;
         sc = 0.0;
         kd = __builtin_nan("");
     }
@@ -610,10 +643,11 @@ struct QuadCache : QuadRay {
     }
     __device__ __forceinline__ void offsets(float o[3]) const { o[0] = of<0>(t); o[1] = of<1>(t); o[2] = of<2>(t); }
 
-    __device__ __forceinline__ bool inside(double v, float& u) const
+    __device__ __forceinline__ bool inside(double v, double& w, float& u) const
     {
         #pragma clang fp contract(off)
-        u = (float)(AMR ? fma(v, sc, -kd) : fma(v, 0.5, -kd));
+        w = AMR ? fma(v, sc, -kd) : fma(v, 0.5, -kd);
+        u = (float)w;
         uint32_t m = __float_as_uint(u);
         const uint32_t n = next(m);
         const uint32_t a = after(m);
@@ -654,12 +688,11 @@ struct QuadCache : QuadRay {
         bool w = true;
         if constexpr (AMR) w = ok && g.child[b] == kWholeLeaf;
         if (AMR && !w && L >= 0) {
-            const int J = (I >> 1) & ((M << Lm) - 1);
-            int id = (int)interleave((uint32_t)(J >> Lm));
-            for (int m = Lm - 1; m >= 0; --m) {
+            int id = (int)interleave((uint32_t)((I >> (Lm + 1)) & (M - 1)));
+            for (int m = Lm; m > 0; --m) {
                 const int ch = g.child[id];
                 if (ch < 0) break;
-                id = ch + (int)all_or((uint32_t)((J >> m) & 1) << own_axis(0));
+                id = ch + (int)all_or((uint32_t)((I >> m) & 1) << own_axis(0));
                 ++L;
             }
             if (L > 0) {
@@ -684,8 +717,9 @@ struct QuadCache : QuadRay {
             const int sh = w ? Lm - l : Lm - L;
             sc = ldexp(1.0, w ? -sh - 1 : -sh);
             const int k = I >> sh;
-            kd = w ? (double)((k - 1) >> 1) + 0.5 : (double)k;
-            whole = w;
+            const int s = L - l;
+            kd = w ? 0.5 * (double)((k - 1) | 1) : (double)k;
+            off = w ? kDual : (uint32_t)(k - ((((k >> s) - 1) | 1) << s));
         } else {
             kd = (double)bc + 0.5;
         }
@@ -700,17 +734,15 @@ struct QuadCache : QuadRay {
     {
         #pragma clang fp contract(off)
         bool ok = true;
+        double w;
         leaf_level = leafL;
-        if (!inside(v[0], t)) {
+        if (!inside(v[0], w, t)) {
             ok = find(g, v[0], leaf_level);
-            if (ok) (void)inside(v[0], t);
+            if (ok) (void)inside(v[0], w, t);
             else t = 0.0f;
         }
         if constexpr (AMR) {
-            if (!whole) {
-                const double sl = ldexp(1.0, lvl - g.max_level - 1);
-                t = (float)(v[0] * sl - 0.5 - (double)((((int)kd >> (leafL - lvl)) - 1) >> 1));
-            }
+            if (off != kDual) t = ldexpf((float)(w + (double)off), lvl - leafL - 1);
         }
         stencil_level = AMR ? lvl : 0;
         G[0] = trilinear_eval(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, of<0>(t), of<1>(t), of<2>(t));
