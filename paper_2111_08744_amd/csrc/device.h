@@ -197,17 +197,18 @@ __host__ __device__ __forceinline__ int lookup_cell(const GridDev& g, int l, int
     return id;
 }
 
-// Level of a cell id (ids are level-major).  The scan stops at the grid's
-// deepest level (a uniform branch), and the unrolled comparisons keep the
-// level table in scalar registers (a dynamically indexed array would be
-// copied to vector registers).
+// Level of a cell id (ids are level-major; the levels past the deepest start
+// past every id).  Unrolled in two parts, the second behind a uniform branch,
+// so that a part's comparisons wait once for the level table in scalar
+// registers.
 __device__ __forceinline__ int level_of(const GridDev& g, int id)
 {
     int l = 0;
 #pragma unroll
-    for (int k = 1; k < kMaxLevels; ++k) {
-        if (k > g.max_level) break;
-        l += (id >= g.level_start[k]) ? 1 : 0;
+    for (int k = 1; k <= 4; ++k) l += id >= g.level_start[k] ? 1 : 0;
+    if (g.max_level > 4) {
+#pragma unroll
+        for (int k = 5; k < kMaxLevels; ++k) l += id >= g.level_start[k] ? 1 : 0;
     }
     return l;
 }
