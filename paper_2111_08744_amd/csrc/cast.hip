@@ -1285,8 +1285,8 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
 
 }  // namespace
 
-// Whether a cast's rays take four lanes each: where that needs at most two
-// waves per SIMD on a uniform grid, four on a tree.  A quad's wave issues two
+// A cast's rays take four lanes each where that needs at most two waves per
+// SIMD on a uniform grid, four on a tree.  A quad's wave issues two
 // thirds of the instructions of a step, and waits for no coefficients from
 // LDS, but carries a quarter of the rays; on a tree it also gathers and
 // diverges for 16 rays and not for 64.  One lane against four, uniform 64^3,
@@ -1294,18 +1294,13 @@ __global__ __launch_bounds__(256) void tangent_observables_kernel(CastArgs a, co
 // waves) 2.02 and 1.66, 49,152 2.13 and 2.19; 64^3 + 5 levels: 3,072 1.44 and
 // 1.09, 32,768 2.33 and 1.76, 65,536 (four) 2.58 and 2.14, 98,304 2.51 and
 // 2.96.  With checkpoints the same.
-static bool by_quads(const CastArgs& a, int waves)
-{
-    return a.n_rays <= (int64_t)(kWave / 4) * a.simds * waves;
-}
-
 static int quad_waves(const CastArgs& a) { return a.grid.max_level > 0 ? 4 : 2; }
 
 template <bool CKPT>
 static hipError_t launch_cast_quad(const CastArgs& args, hipStream_t s)
 {
     const bool amr = args.grid.max_level > 0;
-    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1, 16);
+    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1, kWave / 4);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     if (amr) hipLaunchKernelGGL((cast_quad_kernel<true, CKPT>), grid, blk, 0, s, a);
     else hipLaunchKernelGGL((cast_quad_kernel<false, CKPT>), grid, blk, 0, s, a);
@@ -1316,7 +1311,7 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
     const bool amr = args.grid.max_level > 0, td = args.grid.tdual != nullptr;
-    if (!td && by_quads(args, quad_waves(args))) return launch_cast_quad<false>(args, s);
+    if (!td && by_quads(args, args.n_rays, quad_waves(args))) return launch_cast_quad<false>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1);
     const size_t lds = (size_t)(td ? FieldCache<true, true>::kFloats : FieldCache<true>::kFloats) * kBlock *
                        sizeof(float);
@@ -1334,7 +1329,7 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    if (by_quads(args, quad_waves(args))) return launch_cast_quad<true>(args, s);
+    if (by_quads(args, args.n_rays, quad_waves(args))) return launch_cast_quad<true>(args, s);
     const CastArgs a = spread_rays(args, args.n_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
@@ -1363,8 +1358,8 @@ hipError_t launch_cast_tangent(const CastArgs& args, TanEnd* te, hipStream_t s)
     // four lanes a ray up to two waves per SIMD (registers admit no more):
     // 12,288 rays 3.51 ms and 2.06, 32,768 3.68 and 3.25, 49,152 3.82 and 4.59
     // (uniform); 2.85 and 1.93, 3.29 and 2.38, 3.34 and 3.60 (tree)
-    const bool quad = by_quads(args, 2);
-    const CastArgs a = quad ? spread_rays(args, args.n_rays, 1, kWave / 4) : spread_rays(args, args.n_rays, 1);
+    const bool quad = by_quads(args, args.n_rays, 2);
+    const CastArgs a = spread_rays(args, args.n_rays, 1, quad ? kWave / 4 : kWave);
     const bool amr = a.grid.max_level > 0;
     const size_t lds = quad ? 0 : (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);

@@ -28,7 +28,7 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nblocks)
     return x < r ? x * (q + 1) + idx : r * (q + 1) + (x - r) * q + idx;
 }
 
-// Rays per wave of a launch of n rays: 64, or fewer where that leaves SIMDs without a
+// Rays per wave of a launch of n rays: `most` (64 lanes' worth), or fewer where that leaves SIMDs without a
 // wave: the smallest power of two that needs at most `waves` waves per SIMD.
 // A stage stalls the wave when any of its rays enters a new stencil, so waves
 // of fewer rays run a step sooner; beyond one wave per SIMD the additional
@@ -44,6 +44,10 @@ inline CastArgs spread_rays(const CastArgs& a, int64_t n, int waves, int most = 
     while (c.lanes > 1 && (n + c.lanes / 2 - 1) / (c.lanes / 2) <= (int64_t)waves * a.simds) c.lanes /= 2;
     return c;
 }
+
+// Whether n rays of four lanes each (QuadRay) need at most `waves` waves per
+// SIMD; the launchers say how many are worth it.
+inline bool by_quads(const CastArgs& a, int64_t n, int waves) { return n <= (int64_t)16 * a.simds * waves; }
 
 inline dim3 ray_grid(const CastArgs& a, int64_t n)
 {
@@ -730,8 +734,7 @@ struct QuadCache : QuadRay {
         return true;
     }
 
-    __device__ __forceinline__ int eval(const GridDev& g, const double v[1], float G[1], int& leaf_level,
-                                        int& stencil_level)
+    __device__ __forceinline__ bool locate(const GridDev& g, const double v[1], int& leaf_level)
     {
         #pragma clang fp contract(off)
         bool ok = true;
@@ -745,6 +748,13 @@ struct QuadCache : QuadRay {
         if constexpr (AMR) {
             if (off != kDual) t = ldexpf((float)(w + (double)off), lvl - leafL - 1);
         }
+        return ok;
+    }
+
+    __device__ __forceinline__ int eval(const GridDev& g, const double v[1], float G[1], int& leaf_level,
+                                        int& stencil_level)
+    {
+        const bool ok = locate(g, v, leaf_level);
         stencil_level = AMR ? lvl : 0;
         G[0] = trilinear_eval(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, of<0>(t), of<1>(t), of<2>(t));
         return ok ? 0 : 1;

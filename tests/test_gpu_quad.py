@@ -1,4 +1,4 @@
-"""Casts whose rays take four lanes each (by_quads in cast.hip) against the
+"""Casts whose rays take four lanes each (by_quads in device.h) against the
 persistent schedule, one lane per ray, bit for bit: rays that leave the box of
 a non-periodic grid through every face and edge, partly filled waves, and the
 numbers of rays on both sides of the rule's line."""
@@ -46,3 +46,35 @@ def test_four_lanes_a_ray(levels, periodic):
     line = 64 * torch.cuda.get_device_properties(0).multi_processor_count * (4 if levels else 2)
     for n in (line, line + 1):
         _equal(M, grid, n, "line", **{**kw, "stop": 0.05 * cells.box})
+
+
+@pytest.mark.parametrize("levels", [0, 3])
+def test_cell_gradient_of_four_lanes_a_ray(levels):
+    """The cell gradient is a sum over rays: of more rays than take four lanes
+    each, and of their parts, which do.  Single-precision sums of up to 1e4
+    terms a cell in another order: 1e2 roundings of 6e-8 of the norm."""
+    import torch
+
+    import paper_2111_08744_amd as M
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    cells = synth.random_amr_cells(16, 125.0, levels, seed=5) if levels else synth.make_cells("gauss32")
+    grid = M.Grid(cells, COSMO)
+    n = 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator("cuda").manual_seed(3)
+    ga = torch.randn(n + 3, 2, device="cuda", generator=gen)
+    gz = torch.randn(n + 3, device="cuda", generator=gen, dtype=torch.float64)
+
+    def gradient(lo, hi):
+        cfg = M.CastConfig([0.47 * cells.box, 0.5 * cells.box, 0.6 * cells.box], 0.3 * cells.box, 128, stop_kind="chi",
+                           pix_first=[lo], pix_count=[hi - lo], steps_per_cell=3, adaptive=levels > 0,
+                           checkpoint_every=8)
+        print(levels, lo, hi, flush=True)
+        res = M.adjoint(grid, cfg, M.cast(grid, cfg), dL_dalpha=ga[lo:hi].contiguous(), dL_dz=gz[lo:hi].contiguous(),
+                        jacobian=False, cells=True)
+        assert int((res["ray_status"] != 0).sum()) == 0
+        return res["dL_dvalues"].double()
+
+    whole = gradient(0, n + 3)
+    parts = gradient(0, 1) + gradient(1, 1030) + gradient(1030, n + 3)
+    assert float((whole - parts).norm()) <= 6e-6 * float(whole.norm())
