@@ -78,3 +78,33 @@ def test_cell_gradient_of_four_lanes_a_ray(levels):
     whole = gradient(0, n + 3)
     parts = gradient(0, 1) + gradient(1, 1030) + gradient(1030, n + 3)
     assert float((whole - parts).norm()) <= 6e-6 * float(whole.norm())
+
+
+def test_finder_steps_of_four_lanes_a_ray():
+    """The finder's Newton steps: the distortion matrices of more rays than
+    take four lanes each against the same sources in two calls, whose rays do.
+    The matrices are single-precision on both sides (1e-6 relative), and the
+    last step is below 1e-7 rad of the root (tol), so the roots agree to 1e-13
+    rad plus the rounding of double-precision directions."""
+    import numpy as np
+    import torch
+
+    import paper_2111_08744_amd as M
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    cells = synth.make_cells("gauss32")
+    grid = M.Grid(cells, COSMO)
+    n = 64 * torch.cuda.get_device_properties(0).multi_processor_count + 3
+    v = np.random.default_rng(9).standard_normal((n, 3))
+    obs = np.full(3, 0.5 * cells.box)
+    src = obs + v / np.linalg.norm(v, axis=1, keepdims=True) * 0.2 * cells.box
+
+    def find(s):
+        print(len(s), flush=True)
+        res = M.find_geodesics(grid, obs, s, steps_per_cell=3, identity_iters=0, tol=1e-9)
+        return {k: res[k].cpu() for k in ("theta", "n_iter", "status")}
+
+    whole, parts = find(src), [find(src[:n // 2]), find(src[n // 2:])]
+    both = {k: torch.cat([p[k] for p in parts]) for k in whole}
+    assert torch.equal(whole["status"], both["status"]) and torch.equal(whole["n_iter"], both["n_iter"])
+    assert float((whole["theta"] - both["theta"]).abs().max()) <= 1e-12
