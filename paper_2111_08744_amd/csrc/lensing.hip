@@ -26,25 +26,58 @@ __device__ inline void screen_basis(const double v[3], double e1[3], double e2[3
 // [-g2, 1 - kappa + g1]] (Sect. 2.3): A11 + A22 = 2 (1 - kappa) cos omega and
 // A21 - A12 = 2 (1 - kappa) sin omega give omega and 1 - kappa; the symmetric
 // factor S = R(-omega) A gives g1 = (S22 - S11) / 2 and g2 = -(S12 + S21) / 2;
-// mu = 1 / det A.  FP64 internally.
+// mu = 1 / det A.  FP64 internally; squares of single-precision values stay in
+// its range, so that the length needs no scaling and gives cos and sin omega.
+__device__ __forceinline__ void decompose(const float4 m, float o[5])
+{
+    const double a11 = m.x, a12 = m.y, a21 = m.z, a22 = m.w;
+    const double tr = a11 + a22, rot = a21 - a12;
+    const double omega = atan2(rot, tr);
+    double len = sqrt(tr * tr + rot * rot), s, c;
+    if (len > 0.0 && len < __builtin_inf()) {
+        const double inv = 1.0 / len;
+        s = rot * inv;
+        c = tr * inv;
+    } else {
+        len = hypot(tr, rot);
+        sincos(omega, &s, &c);
+    }
+    const double s11 = c * a11 + s * a21, s12 = c * a12 + s * a22;
+    const double s21 = -s * a11 + c * a21, s22 = -s * a12 + c * a22;
+    o[0] = (float)(1.0 - 0.5 * len);
+    o[1] = (float)(0.5 * (s22 - s11));
+    o[2] = (float)(-0.5 * (s12 + s21));
+    o[3] = (float)omega;
+    o[4] = (float)(1.0 / (a11 * a22 - a12 * a21));
+}
+
+// One matrix per lane.  Memory bounds it (36 bytes a matrix): the five values
+// go through LDS, so that a wave stores whole cache lines with 16 bytes a lane
+// instead of five times every fifth word, and sin and cos omega come from the
+// length instead of the library: 12.6 million matrices 102.7 -> 89.8 us (5,050
+// GB/s; a copy reaches 5,440).  ALIGNED: A and out on 16 bytes.
+template <bool ALIGNED>
 __global__ __launch_bounds__(256) void lensing_maps_kernel(const float* __restrict__ A, int64_t n,
                                                            float* __restrict__ out)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double a11 = A[4 * i], a12 = A[4 * i + 1], a21 = A[4 * i + 2], a22 = A[4 * i + 3];
-    const double tr = a11 + a22, rot = a21 - a12;
-    const double omega = atan2(rot, tr);
-    const double one_k = 0.5 * hypot(tr, rot);
-    double s, c;
-    sincos(omega, &s, &c);
-    const double s11 = c * a11 + s * a21, s12 = c * a12 + s * a22;
-    const double s21 = -s * a11 + c * a21, s22 = -s * a12 + c * a22;
-    out[5 * i] = (float)(1.0 - one_k);
-    out[5 * i + 1] = (float)(0.5 * (s22 - s11));
-    out[5 * i + 2] = (float)(-0.5 * (s12 + s21));
-    out[5 * i + 3] = (float)omega;
-    out[5 * i + 4] = (float)(1.0 / (a11 * a22 - a12 * a21));
+    __shared__ float4 st[5 * 256 / 4];
+    float* o = reinterpret_cast<float*>(st);
+    const int64_t first = (int64_t)blockIdx.x * 256, i = first + threadIdx.x;
+    if (i < n) {
+        float4 m;
+        if constexpr (ALIGNED) m = reinterpret_cast<const float4*>(A)[i];
+        else m = make_float4(A[4 * i], A[4 * i + 1], A[4 * i + 2], A[4 * i + 3]);
+        decompose(m, o + 5 * threadIdx.x);
+    }
+    __syncthreads();
+    if (ALIGNED && first + 256 <= n) {
+        float4* p = reinterpret_cast<float4*>(out + 5 * first);
+        p[threadIdx.x] = st[threadIdx.x];
+        if (threadIdx.x < 64) p[256 + threadIdx.x] = st[256 + threadIdx.x];
+    } else {
+        const int left = 5 * (int)(n - first < 256 ? n - first : 256);
+        for (int k = threadIdx.x; k < left; k += 256) out[5 * first + k] = o[k];
+    }
 }
 
 // Observer j of reference ray r (observers are few: scan from the end).
@@ -166,7 +199,9 @@ inline dim3 blocks_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 hipError_t launch_lensing_maps(const float* A, int64_t n, float* out, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(lensing_maps_kernel, blocks_for(n), dim3(256), 0, s, A, n, out);
+    if (((uintptr_t)A | (uintptr_t)out) % 16 == 0)
+        hipLaunchKernelGGL(lensing_maps_kernel<true>, blocks_for(n), dim3(256), 0, s, A, n, out);
+    else hipLaunchKernelGGL(lensing_maps_kernel<false>, blocks_for(n), dim3(256), 0, s, A, n, out);
     return hipGetLastError();
 }
 

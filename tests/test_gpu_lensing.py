@@ -238,3 +238,31 @@ def test_healpix_dirs_are_the_pixel_cast_directions(M, gauss64):
     for k in ("beta", "z5", "n_steps", "status", "hash"):
         assert np.array_equal(a[k], b[k]), k
     assert M.healpix_dirs(4, 0, 0).shape == (0, 3)
+
+
+@pytest.mark.parametrize("n", [1, 63, 255, 256, 257, 4099])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_lensing_maps_sizes_and_alignment(M, n, offset):
+    """Whole and partial blocks, matrices not on 16 bytes, and values without a
+    finite decomposition, against the formula in double precision."""
+    rng = np.random.default_rng(n)
+    flat = np.zeros(offset + 4 * n, np.float32)
+    A = flat[offset:].reshape(n, 2, 2)
+    A[:] = np.eye(2) + rng.normal(0, 0.1, (n, 2, 2))
+    odd = [[[0, 0], [0, 0]], [[np.inf, 0], [0, 1]], [[np.nan, 0], [0, 1]], [[1e38, 1], [-1, 1e38]], [[1, 2], [-2, -1]],
+           [[1e-40, 0], [0, 0]]]
+    A[:len(odd)] = np.asarray(odd, np.float32)[:n]
+    out = M.lensing_maps(_cuda(flat)[offset:].view(n, 2, 2)).cpu().numpy()
+    with np.errstate(all="ignore"):
+        a, b, c, d = A.astype(np.float64).reshape(n, 4).T
+        w = np.arctan2(c - b, a + d)
+        co, si = np.cos(w), np.sin(w)
+        s11, s12, s21, s22 = co * a + si * c, co * b + si * d, -si * a + co * c, -si * b + co * d
+        ref = np.stack([1 - 0.5 * np.hypot(a + d, c - b), 0.5 * (s22 - s11), -0.5 * (s12 + s21), w,
+                        1 / (a * d - b * c)], 1).astype(np.float32)
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(np.isinf(out), np.isinf(ref))
+    ok = np.isfinite(ref) & np.isfinite(out)
+    # one rounding to float32, and 4e-16 times the matrix in double precision
+    size = np.abs(A).reshape(n, 4).max(1)[:, None]
+    err = np.abs(out.astype(np.float64)[ok] - ref[ok])
+    assert (err <= 1.2e-7 * np.abs(ref[ok]) + 4e-15 * np.broadcast_to(size, ref.shape)[ok]).all()
