@@ -182,6 +182,13 @@ __device__ inline double scale_factor(const CosmoDev& c, double eta)
 // ray may leave the box) and wrapped only to address memory.
 // ---------------------------------------------------------------------------
 
+// Interleaved coordinates m with `one` (0 or the axis's lowest bit) added to
+// the axis whose bits are `lanes`, wrapping.
+__host__ __device__ __forceinline__ uint32_t step_up(uint32_t m, uint32_t lanes, uint32_t one)
+{
+    return (m & ~lanes) | (((m | ~lanes) + one) & lanes);
+}
+
 // Id of cell (l, J) or -1 if it does not exist: coarse ancestor by Morton
 // index, then one child link per level.
 __host__ __device__ __forceinline__ int lookup_cell(const GridDev& g, int l, int J0, int J1, int J2)
@@ -312,13 +319,6 @@ constexpr int kWholeLeaf = -2;
 
 // A cached region that is the stencil's dual cell (FieldCache::off).
 constexpr uint32_t kDual = ~0u;
-
-// Interleaved coordinates m with `one` (0 or the axis's lowest bit) added to
-// the axis whose bits are `lanes`, wrapping.
-__device__ __forceinline__ uint32_t step_up(uint32_t m, uint32_t lanes, uint32_t one)
-{
-    return (m & ~lanes) | (((m | ~lanes) + one) & lanes);
-}
 
 // Field value interpolated at one point, with the lane's cache of the last
 // resolved 8-cell stencil (as trilinear coefficients) and of the region of
@@ -898,8 +898,9 @@ struct TscCache : WholeRay {
 
     // Load the payloads of the 27 cells cc + {-1, 0, 1}^3 at level l when
     // all of them exist; false otherwise (nothing is loaded).  Level 0: the
-    // Morton id is the OR of one bit spread per axis, so 9 spreads give the
-    // 27 ids.  Refined level: the 27 cells have 2 x 2 x 2 parents (two per
+    // Morton id is the OR of one bit spread per axis, so 3 spreads, each with
+    // one added and one taken away on its bits, give the 27 ids (nine spreads
+    // were a third of the gather's instructions).  Refined level: the 27 cells have 2 x 2 x 2 parents (two per
     // axis, the parents of cc - 1 and cc + 1); each cell is its parent's
     // first child plus its octant, so 8 walks to level l - 1 replace 27
     // walks to level l.
@@ -907,16 +908,17 @@ struct TscCache : WholeRay {
     {
         if (!AMR || l == 0) {
             const int M = g.n0;
+            const uint32_t bits = (1u << (3 * __builtin_ctz((unsigned)M))) - 1u;
             uint32_t sp[3][3];
             bool all = true;
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const int J = cc[d] + a - 1;
-                    all &= g.periodic || (unsigned)J < (unsigned)M;
-                    sp[d][a] = part1by2((uint32_t)(J & (M - 1))) << d;
-                }
+            for (int d = 0; d < 3; ++d) {
+                all &= g.periodic || (cc[d] >= 1 && cc[d] + 1 < M);
+                const uint32_t lanes = (0x49249249u << d) & bits;
+                sp[d][1] = part1by2((uint32_t)(cc[d] & (M - 1))) << d;
+                sp[d][0] = (sp[d][1] - (1u << d)) & lanes;
+                sp[d][2] = step_up(sp[d][1], lanes, 1u << d) & lanes;
+            }
             if (!all) return false;
 #pragma unroll
             for (int q = 0; q < 27; ++q) p[q] = g.payload[sp[0][q % 3] | sp[1][(q / 3) % 3] | sp[2][q / 9]];
