@@ -863,7 +863,7 @@ template <int W, bool SCATTER>
 __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCtx& R, int end_base, int end_lvl,
                                                const ObsDev& ob, int64_t ray, bool owner, const GeoState& yf, double phio,
                                                const double e1[3], const double e2[3], Phys (&yb)[W],
-                                               double& phio_bar)
+                                               double& phio_bar, double& phis_bar)
 {
     constexpr bool HAS_JAC = W >= 3;
     const GridDev& g = A.c.grid;
@@ -896,7 +896,7 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
         }
         yb[2].k0 = -dz_dK;
     }
-    phio_bar = 0.0;
+    phio_bar = phis_bar = 0.0;
     if (SCATTER) {
         const float ga0 = A.dL_dalpha ? A.dL_dalpha[2 * ray] : 0.0f;
         const float ga1 = A.dL_dalpha ? A.dL_dalpha[2 * ray + 1] : 0.0f;
@@ -935,7 +935,8 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
 #pragma unroll
         for (int i = 0; i < 3; ++i) L.x[i] = (cb[0] * f1[i] + cb[1] * f2[i]) / chi + gz * dz_dphis * Jf.gphi[i];
         L.k0 = -gz * dz_dK;
-        if (owner) scatter_phi(A, end_base, Jf.t, gz * dz_dphis);
+        phis_bar = gz * dz_dphis;
+        if (owner) scatter_phi(A, end_base, Jf.t, phis_bar);
         phio_bar = gz * dz_dphio;
     }
 #pragma unroll
@@ -1055,7 +1056,8 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
                     }
                     double none;
                     w.locate(a.grid, y);
-                    end_cotangents<W, false>(A, w.R, w.F.base, w.F.lvl, *w.ob, ray, false, y, w.phio, w.e1, w.e2, yb, none);
+                    end_cotangents<W, false>(A, w.R, w.F.base, w.F.lvl, *w.ob, ray, false, y, w.phio, w.e1, w.e2, yb,
+                                             none, none);
                 }
             }
             const int jl = fwd ? it : len - 1 - (it - nf);
@@ -1176,7 +1178,9 @@ __global__ __launch_bounds__(kBlock, 2) void adjoint_loss_kernel(AdjointArgs A)
                 break;
             }
             w.locate(a.grid, y);
-            end_cotangents<1, true>(A, w.R, w.F.base, w.F.lvl, *w.ob, ray, owner, y, w.phio, w.e1, w.e2, yb, phio_bar);
+            double phis_bar;
+            end_cotangents<1, true>(A, w.R, w.F.base, w.F.lvl, *w.ob, ray, owner, y, w.phio, w.e1, w.e2, yb, phio_bar,
+                                    phis_bar);
         }
         for (int jl = len - 1; jl >= 0; --jl) {
             // the lanes still iterating empty the table when it is a quarter full
@@ -1399,8 +1403,9 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
     w.start(A, ray, n_steps, nullptr);
     const float nf = (float)w.R.geo.n[0], inv_h0 = (float)g.inv_h0;
     const int K = a.ckpt_every;
-    double yb_eta = 0.0, yb_k0 = 0.0, yb_x = 0.0, yb_k = 0.0, phio_bar = 0.0;     // LOSS: this component
-    Phys yb[1];                                                                  // else this column
+    double yb_eta = 0.0, yb_k0 = 0.0, yb_x = 0.0, yb_k = 0.0;     // LOSS: this component
+    Phys yb[1];                                                  // else this column
+    double phio_bar = 0.0, phis_bar = 0.0;
     QuadScatter S;
     S.cur = -1;
     if constexpr (LOSS) S.flush(A, T);
@@ -1445,8 +1450,8 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
             RayCtx R;
             w.whole(A, ray, R);
             if constexpr (LOSS) {
-                end_cotangents<1, true>(A, R, w.F.base, w.F.lvl, *w.ob, ray, owner && (threadIdx.x & 3) == 0, ye,
-                                        w.phio, w.e1, w.e2, yb, phio_bar);
+                end_cotangents<1, true>(A, R, w.F.base, w.F.lvl, *w.ob, ray, false, ye, w.phio, w.e1, w.e2, yb,
+                                        phio_bar, phis_bar);
                 yb_eta = yb[0].eta;
                 yb_k0 = yb[0].k0;
                 yb_x = ax == 0 ? yb[0].x[0] : ax == 1 ? yb[0].x[1] : yb[0].x[2];
@@ -1454,7 +1459,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
             } else {
                 Phys c[3];
                 end_cotangents<3, false>(A, R, w.F.base, w.F.lvl, *w.ob, ray, false, ye, w.phio, w.e1, w.e2, c,
-                                         phio_bar);
+                                         phio_bar, phis_bar);
                 yb[0] = ax == 0 ? c[0] : ax == 1 ? c[1] : c[2];
             }
         }
@@ -1519,7 +1524,24 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
         for (int i = 0; i < 3; ++i) { y0.d[i] = 0.0f; y0.dx[i] = 0.0f; }
         double t0[3];
         stage_offsets(g, R, y0, w.obs_lvl, t0);
-        if ((threadIdx.x & 3) == 0) scatter_phi(A, w.obs_base, t0, phio_bar);
+        // Phi at the end point: after the loops, since with one lane of a quad
+        // branching off inside them the compiler (ROCm 7.2) spilled a pointer
+        // before the other lanes were switched on again, and those then read
+        // from wherever their register pointed
+        GeoState ye;
+        const RayEnd e = a.ends[ray];
+        ye.eta = e.eta;
+        double te[3];
+        GeoState yo = ye;
+        yo.dx[0] = e.dx[ax];
+        w.locate(g, yo);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) ye.dx[i] = e.dx[i];
+        stage_offsets(g, R, ye, w.F.lvl, te);
+        if ((threadIdx.x & 3) == 0) {
+            scatter_phi(A, w.obs_base, t0, phio_bar);
+            scatter_phi(A, w.F.base, te, phis_bar);
+        }
     }
     T.evict(A);
 }
