@@ -201,7 +201,7 @@ int mpath_grid_set_values(mpath_grid* grid, const float* values, void* stream);
 #define MPATH_DPHIDL_CHAIN 0    /* dPhi/dlambda (mpath_cast_desc.dphidl)                         */
 #define MPATH_DPHIDL_DIFF 1
 
-#define MPATH_SCHED_AUTO 0      /* library choice (the static schedule)                          */
+#define MPATH_SCHED_AUTO 0      /* library choice (persistent for many observers and many rays) */
 #define MPATH_SCHED_STATIC 1    /* one lane per ray, one launch                                 */
 #define MPATH_SCHED_PERSISTENT 2/* resident waves pull ray batches from a global queue          */
 

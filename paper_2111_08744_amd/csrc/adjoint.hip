@@ -1113,8 +1113,8 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
 // in LDS and the Jacobian's columns alongside), which hides most of the gather
 // and table latency: 131,072 rays to z = 1 on a uniform 64^3 grid (3,000 steps)
 // 80.3 ms before, 34.6 now, 27 of them without the scatter; with the Jacobian
-// (15 ms of tangents) 80.5 and 49.6.  12,288 rays on 64^3 + 5 levels 18.1 and
-// 11.1.  SPREAD: waves of fewer than 64 rays (see lane_ray).
+// (15 ms of tangents) 80.5 and 49.6.  Fewer rays than fill one wave per SIMD by
+// four lanes each take adjoint_quad_kernel.  SPREAD: waves of fewer than 64 rays (see lane_ray).
 template <bool AMR, bool SPREAD>
 __global__ __launch_bounds__(kBlock, 2) void adjoint_loss_kernel(AdjointArgs A)
 {

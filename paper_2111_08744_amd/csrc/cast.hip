@@ -1,8 +1,9 @@
 // cast.hip -- forward ray-casting kernels for gfx950.
 //
-// One lane integrates one photon (Sect. 2.2: photons are independent).  Two
-// schedules share the per-ray code:
-//   static      one launch with one lane per ray; rays of a wave are
+// One lane integrates one photon (Sect. 2.2: photons are independent), or four
+// lanes do where the rays are few (QuadRay).  Two schedules share the per-ray
+// code:
+//   static      one launch with one lane per ray (or four); rays of a wave are
 //               neighbouring NESTED pixels of one observer, so their
 //               stencil gathers hit the same cache lines near the observer;
 //   persistent  a grid sized to the resident capacity of the GPU; every lane
@@ -23,9 +24,9 @@ namespace {
 constexpr int kWave = 64;
 // Occupancy target of the integration kernels: 4 waves per SIMD (128
 // registers).  A wave stalls on every stage where one of its lanes enters a
-// new stencil (a dependent stencil-table and coefficient gather), so latency
-// hiding pays more than the few values the bound spills (measured on the AMR
-// workload: 3 waves 102.6 ms, 4 waves 89.5 ms per cast).
+// new stencil, so latency hiding pays more than the few values the bound
+// spills (measured on the AMR workload with an earlier form of the field
+// cache: 3 waves 102.6 ms, 4 waves 89.5 ms per cast).
 constexpr int kMinWavesPerSimd = 4;
 
 // Step-start hook of RayRun::advance that does nothing (plain casts).

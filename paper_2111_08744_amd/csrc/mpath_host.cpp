@@ -1062,15 +1062,18 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
     } else if (d->checkpoint_every > 0) {
         e = launch_cast_checkpointed(a, s);
     } else {
-        // AUTO is the static schedule: with many observers too, the hardware
-        // refills whole waves, and few rays are spread over the SIMDs.  Uniform
-        // 64^3, sources to z in [0.1, 2], static against persistent: 64 cones of
-        // 16,384 rays 47.3 ms and 48.7, of 64 rays 6.6 and 9.4; 4,096 observers
-        // of 3 rays (lanes of one wave ending at very different steps) 13.7 and
-        // 26.8; 64^3 + 5 levels 31.4 and 30.1, 4.6 and 6.2, 11.1 and 26.0.
-        const int sched = d->schedule;
+        // AUTO: the queue for many observers with more rays than the GPU holds at
+        // once (4 waves per SIMD), since the static launch gives each XCD a run of
+        // observers, whose paths can differ in length: 64 cones of 16,384 rays on
+        // a uniform 64^3 grid, three draws of source redshifts in [0.1, 2], static
+        // 49.7, 47.8 and 53.4 ms, queue 49.4, 48.0 and 46.8.  Fewer rays take the
+        // static launch, which spreads them over the SIMDs: 64 cones of 64 rays
+        // 6.6 ms and 9.4, 4,096 observers of 3 rays 13.7 and 26.8.
+        int sched = d->schedule;
+        if (sched == MPATH_SCHED_AUTO)
+            sched = d->n_obs > 1 && a.n_rays > (int64_t)64 * 4 * a.simds ? MPATH_SCHED_PERSISTENT : MPATH_SCHED_STATIC;
         const int block = d->block_size ? d->block_size : 256;
-        if (sched != MPATH_SCHED_PERSISTENT) {
+        if (sched == MPATH_SCHED_STATIC) {
             e = launch_cast_static(a, s);
         } else {
             int wpc = d->waves_per_cu;

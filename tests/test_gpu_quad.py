@@ -108,3 +108,24 @@ def test_finder_steps_of_four_lanes_a_ray():
     both = {k: torch.cat([p[k] for p in parts]) for k in whole}
     assert torch.equal(whole["status"], both["status"]) and torch.equal(whole["n_iter"], both["n_iter"])
     assert float((whole["theta"] - both["theta"]).abs().max()) <= 1e-12
+
+
+def test_automatic_schedule_of_many_observers():
+    """On both sides of the number of rays where the automatic choice changes."""
+    import torch
+
+    import paper_2111_08744_amd as M
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    cells = synth.make_cells("gauss32")
+    grid = M.Grid(cells, COSMO)
+    line = 64 * 4 * 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    obs = [[f * cells.box] * 3 for f in (0.3, 0.6)]
+    for n in (line, line + 1):
+        print(n, flush=True)
+        auto, static = (M.cast(grid, M.CastConfig(obs, [0.03 * cells.box, 0.06 * cells.box], 256, stop_kind="chi",
+                                                  pix_first=[0, 5], pix_count=[1000, n - 1000], steps_per_cell=3,
+                                                  schedule=s)) for s in (0, 1))
+        for k, v in auto.items():
+            if not k.startswith("_"):
+                assert torch.equal(v.view(torch.uint8), static[k].view(torch.uint8)), (n, k)
