@@ -1186,8 +1186,8 @@ __device__ __forceinline__ double quotient(double a, double b)
 // fractions are constants: about 105 instructions a stage where the general
 // form took 145.  With the region check and the records' way through LDS (see
 // FieldCache): 725 -> 582 instructions per wave-step and 13.26 -> 9.34 ms for
-// 196,608 rays to z = 1 on a uniform 64^3 grid, 984 -> 842 and 71.3 -> 61.6 ms
-// for 786,432 rays on a 128^3 + 3 level tree (813 and 56.7 ms with the later
+// 196,608 rays to z = 1 on a uniform 64^3 grid, 71.3 -> 61.6 ms for 786,432 rays
+// on a 128^3 + 3 level tree (989 -> 843 instructions and 56.7 ms with the later
 // savings in its look-ups).
 template <class FC, class Rec, class DP, bool UNROLL>
 __device__ __forceinline__ int rk4_core(const GridDev& g, const CosmoDev& cz, FC& F,
