@@ -460,7 +460,8 @@ struct WaveTable {
     }
 
     // The same for component q of the eight cells alone, by the lane of a quad
-    // that holds it (`on`: not the lane that repeats another's).
+    // that holds it (`on`: not the lane that repeats another's, which goes the
+    // same way and adds zeros).
     __device__ __forceinline__ void add8(const AdjointArgs& A, const int ids[8], const float acc[8], int q, bool on)
     {
         int h[8], old[8];
@@ -476,14 +477,15 @@ struct WaveTable {
             const bool cell = ids[o] >= 0;
             const bool mine = cell && (old[o] == -1 || old[o] == ids[o]);
             claimed += (cell && old[o] == -1) ? 1 : 0;
-            conflict |= (cell && on && !mine) ? (1u << o) : 0u;
+            conflict |= (cell && !mine) ? (1u << o) : 0u;
             atomicAdd(&vals[q * kTab + h[o]], mine && on ? acc[o] : 0.0f);
         }
         if (claimed) atomicAdd(count, claimed);
         if (conflict) {
 #pragma unroll
             for (int o = 0; o < 8; ++o)
-                if (conflict & (1u << o)) unsafeAtomicAdd(A.grad + grad_slot(ids[o], 1 + q, A.n_cells), acc[o]);
+                if (conflict & (1u << o))
+                    unsafeAtomicAdd(A.grad + grad_slot(ids[o], 1 + q, A.n_cells), on ? acc[o] : 0.0f);
         }
     }
 };
@@ -1525,9 +1527,10 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
         double t0[3];
         stage_offsets(g, R, y0, w.obs_lvl, t0);
         // Phi at the end point: after the loops, since with one lane of a quad
-        // branching off inside them the compiler (ROCm 7.2) spilled a pointer
+        // branching off inside them the compiler (ROCm 7.2) once spilled a pointer
         // before the other lanes were switched on again, and those then read
-        // from wherever their register pointed
+        // from wherever their register pointed.  Any branch of some lanes can
+        // meet that; build.py searches every build's assembly for it.
         GeoState ye;
         const RayEnd e = a.ends[ray];
         ye.eta = e.eta;
