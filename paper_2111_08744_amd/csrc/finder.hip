@@ -38,35 +38,19 @@ __device__ inline double end_direction(const RayEnd& e, const double th[3], doub
     return atan2(sqrt(dot3(c, c)), dot3(b, t));
 }
 
-// The sources that finder_update_kernel will move: their rays' indices to
-// list (in any order) and their number to *active.
-__global__ __launch_bounds__(256) void finder_list_kernel(int64_t n, const RayEnd* __restrict__ ends,
-                                                          const double* __restrict__ target,
-                                                          const int32_t* __restrict__ status, double eta0, double tol,
-                                                          const double* __restrict__ theta,
-                                                          const int32_t* __restrict__ n_iter,
-                                                          int32_t* __restrict__ list,
-                                                          unsigned int* __restrict__ active)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || n_iter[i] != -1 || status[i] != MPATH_RAY_REACHED) return;
-    const double t[3] = {target[3 * i], target[3 * i + 1], target[3 * i + 2]};
-    const double th[3] = {theta[3 * i], theta[3 * i + 1], theta[3 * i + 2]};
-    double b[3];
-    if (!(end_direction(ends[i], th, eta0, t, b) < tol)) list[atomicAdd(active, 1u)] = (int32_t)i;
-}
-
-// One Newton step for every source still iterating (n_iter == -1): a ray
-// that did not reach its source stops the iteration (-2); a ray within tol
-// of its target converges at iteration it; the others move theta and are
-// counted in *active.  jac NULL: A = I.
-__global__ __launch_bounds__(256) void finder_update_kernel(int64_t n, const RayEnd* __restrict__ ends,
-                                                            const double* __restrict__ target,
-                                                            const int32_t* __restrict__ status,
-                                                            const float* __restrict__ jac, double eta0, double tol,
-                                                            int it, double* __restrict__ theta,
-                                                            int32_t* __restrict__ n_iter, double* __restrict__ sep,
-                                                            unsigned int* __restrict__ active)
+// The verdict of iteration `it` on every source still iterating (n_iter ==
+// -1): a ray that did not reach its source stops the iteration (-2); a ray
+// within tol of its target converges; the others have to move: their indices
+// go to list (in any order) and their number to *active.  The verdict is given
+// here alone: a second evaluation of the angle may round otherwise, and the
+// matrices of the sources not listed are never written.
+__global__ __launch_bounds__(256) void finder_check_kernel(int64_t n, const RayEnd* __restrict__ ends,
+                                                           const double* __restrict__ target,
+                                                           const int32_t* __restrict__ status, double eta0, double tol,
+                                                           int it, const double* __restrict__ theta,
+                                                           int32_t* __restrict__ n_iter, double* __restrict__ sep,
+                                                           int32_t* __restrict__ list,
+                                                           unsigned int* __restrict__ active)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n || n_iter[i] != -1) return;
@@ -75,7 +59,7 @@ __global__ __launch_bounds__(256) void finder_update_kernel(int64_t n, const Ray
         return;
     }
     const double t[3] = {target[3 * i], target[3 * i + 1], target[3 * i + 2]};
-    double th[3] = {theta[3 * i], theta[3 * i + 1], theta[3 * i + 2]};
+    const double th[3] = {theta[3 * i], theta[3 * i + 1], theta[3 * i + 2]};
     double b[3];
     const double s = end_direction(ends[i], th, eta0, t, b);
     sep[i] = s;
@@ -83,6 +67,23 @@ __global__ __launch_bounds__(256) void finder_update_kernel(int64_t n, const Ray
         n_iter[i] = it;
         return;
     }
+    list[atomicAdd(active, 1u)] = (int32_t)i;
+}
+
+// One Newton step for each of the m listed sources.  jac NULL: A = I.
+__global__ __launch_bounds__(256) void finder_move_kernel(int64_t m, const int32_t* __restrict__ list,
+                                                          const RayEnd* __restrict__ ends,
+                                                          const double* __restrict__ target,
+                                                          const float* __restrict__ jac, double eta0,
+                                                          double* __restrict__ theta)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= m) return;
+    const int64_t i = list[k];
+    const double t[3] = {target[3 * i], target[3 * i + 1], target[3 * i + 2]};
+    double th[3] = {theta[3 * i], theta[3 * i + 1], theta[3 * i + 2]};
+    double b[3];
+    (void)end_direction(ends[i], th, eta0, t, b);
     // residual beta - beta_i as screen components at beta_i (zero exactly at the root)
     double f1[3], f2[3];
     basis_at(b, f1, f2);
@@ -96,11 +97,10 @@ __global__ __launch_bounds__(256) void finder_update_kernel(int64_t n, const Ray
     double e1[3], e2[3];
     basis_at(th, e1, e2);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) th[k] += x0 * e1[k] + x1 * e2[k];
+    for (int q = 0; q < 3; ++q) th[q] += x0 * e1[q] + x1 * e2[q];
     const double inv = 1.0 / sqrt(dot3(th, th));
 #pragma unroll
-    for (int k = 0; k < 3; ++k) theta[3 * i + k] = th[k] * inv;
-    atomicAdd(active, 1u);
+    for (int q = 0; q < 3; ++q) theta[3 * i + q] = th[q] * inv;
 }
 
 // Angle between the end direction of the final cast and the target.
@@ -214,25 +214,22 @@ inline dim3 blocks_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
 }  // namespace
 
-hipError_t launch_finder_list(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
-                              double tol, const double* theta, const int32_t* n_iter, int32_t* list,
-                              unsigned int* active, hipStream_t s)
+hipError_t launch_finder_check(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
+                               double tol, int it, const double* theta, int32_t* n_iter, double* sep, int32_t* list,
+                               unsigned int* active, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(1), 0, s, active);
-    hipLaunchKernelGGL(finder_list_kernel, blocks_for(n), dim3(256), 0, s, n, ends, target, status, eta0, tol, theta,
-                       n_iter, list, active);
+    hipLaunchKernelGGL(finder_check_kernel, blocks_for(n), dim3(256), 0, s, n, ends, target, status, eta0, tol, it,
+                       theta, n_iter, sep, list, active);
     return hipGetLastError();
 }
 
-hipError_t launch_finder_update(int64_t n, const RayEnd* ends, const double* target, const int32_t* status,
-                                const float* jac, double eta0, double tol, int it, double* theta, int32_t* n_iter,
-                                double* sep, unsigned int* active, hipStream_t s)
+hipError_t launch_finder_move(int64_t m, const int32_t* list, const RayEnd* ends, const double* target,
+                              const float* jac, double eta0, double* theta, hipStream_t s)
 {
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(1), 0, s, active);
-    if (n > 0)
-        hipLaunchKernelGGL(finder_update_kernel, blocks_for(n), dim3(256), 0, s, n, ends, target, status, jac, eta0,
-                           tol, it, theta, n_iter, sep, active);
+    if (m == 0) return hipSuccess;
+    hipLaunchKernelGGL(finder_move_kernel, blocks_for(m), dim3(256), 0, s, m, list, ends, target, jac, eta0, theta);
     return hipGetLastError();
 }
 

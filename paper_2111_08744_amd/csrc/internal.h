@@ -215,12 +215,11 @@ hipError_t launch_beam_dirs(const BeamObs* obs, int n_obs, int nside, const doub
 hipError_t launch_finite_beam(const BeamObs* obs, int n_obs, const RayEnd* ends, const double* dirs5,
                               const int32_t* status5, double eta0, double tan_eps, int64_t n_rays, float* A,
                               int32_t* status, hipStream_t s);
-hipError_t launch_finder_list(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
-                              double tol, const double* theta, const int32_t* n_iter, int32_t* list,
-                              unsigned int* active, hipStream_t s);
-hipError_t launch_finder_update(int64_t n, const RayEnd* ends, const double* target, const int32_t* status,
-                                const float* jac, double eta0, double tol, int it, double* theta, int32_t* n_iter,
-                                double* sep, unsigned int* active, hipStream_t s);
+hipError_t launch_finder_check(int64_t n, const RayEnd* ends, const double* target, const int32_t* status, double eta0,
+                               double tol, int it, const double* theta, int32_t* n_iter, double* sep, int32_t* list,
+                               unsigned int* active, hipStream_t s);
+hipError_t launch_finder_move(int64_t m, const int32_t* list, const RayEnd* ends, const double* target,
+                              const float* jac, double eta0, double* theta, hipStream_t s);
 hipError_t launch_finder_sep(int64_t n, const RayEnd* ends, const double* target, const double* theta,
                              const int32_t* status, double eta0, double* sep, hipStream_t s);
 hipError_t launch_grid_init(int64_t m, const int64_t* idx, const double* sep, double* w, hipStream_t s);

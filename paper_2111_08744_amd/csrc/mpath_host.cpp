@@ -1756,27 +1756,20 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
         rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop);
         if (rc) return rc;
         unsigned int left = 0;
-        if (exact) {
-            e = launch_finder_list(P.n, ends, target, status, g->eta0, f->tol, theta, n_iter, list, active, s);
-            if (!e) e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
-            if (!e) e = hipStreamSynchronize(s);
-            if (e) return hip_fail(e, "finder iteration");
-            if (left > 0) {
-                mpath_adjoint_desc ad;
-                std::memset(&ad, 0, sizeof ad);
-                ad.jac = jac;
-                rc = adjoint_impl(g, &P.cd, &fo, cws, P.cast_bytes, &ad, aws, P.adj_bytes, stream, stop, list, left);
-                if (rc) return rc;
-            }
-        }
-        e = launch_finder_update(P.n, ends, target, status, exact ? jac : nullptr, g->eta0, f->tol, it, theta,
-                                 n_iter, sep, active, s);
-        if (!e && !exact) {
-            e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
-            if (!e) e = hipStreamSynchronize(s);
-        }
+        e = launch_finder_check(P.n, ends, target, status, g->eta0, f->tol, it, theta, n_iter, sep, list, active, s);
+        if (!e) e = hipMemcpyAsync(&left, active, sizeof left, hipMemcpyDeviceToHost, s);
+        if (!e) e = hipStreamSynchronize(s);
         if (e) return hip_fail(e, "finder iteration");
         if (left == 0) break;
+        if (exact) {
+            mpath_adjoint_desc ad;
+            std::memset(&ad, 0, sizeof ad);
+            ad.jac = jac;
+            rc = adjoint_impl(g, &P.cd, &fo, cws, P.cast_bytes, &ad, aws, P.adj_bytes, stream, stop, list, left);
+            if (rc) return rc;
+        }
+        e = launch_finder_move(left, list, ends, target, exact ? jac : nullptr, g->eta0, theta, s);
+        if (e) return hip_fail(e, "finder iteration");
     }
     if (f->grid_rounds > 0) {
         // the last-resort root finder for the sources still iterating
