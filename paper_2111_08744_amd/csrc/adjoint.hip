@@ -1201,7 +1201,7 @@ __global__ __launch_bounds__(kBlock, 2) void adjoint_loss_kernel(AdjointArgs A)
         }
     }
     if (!ok) write_nan_jacobian(A, ray);
-    if (A.ray_status) A.ray_status[ray] = ok ? 0 : 2;
+    if (A.ray_status && !(ok && A.checked)) A.ray_status[ray] = ok ? 0 : 2;
     if (ok && owner) {
         S.flush(A, T);
         // the initial state: k = kmag(Phi_o) n (theta), k0 = -1
@@ -1509,7 +1509,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
         }
         return;
     }
-    if (A.ray_status) A.ray_status[ray] = ok ? 0 : 2;
+    if (A.ray_status && !(ok && A.checked)) A.ray_status[ray] = ok ? 0 : 2;
     if (ok && owner) {
         S.flush(A, T);
         // the initial state: k = kmag(Phi_o) n (theta), k0 = -1
@@ -1549,9 +1549,11 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
     T.evict(A);
 }
 
-// The check of a Jacobian without a loss: `ends` are the end states of the
-// cast that carried the tangents.  A ray that did not reach the source has no
-// derivative; one that ended elsewhere than the forward cast is reported.
+// The check of a Jacobian: `ends` are the end states of the cast that carried
+// the tangents.  A ray that did not reach the source has no derivative; one that
+// ended elsewhere than the forward cast is reported.  A loss sweep after it
+// (AdjointArgs::checked) leaves that report: its own replay starts from the
+// stored checkpoints and misses values that changed before the last one.
 __global__ __launch_bounds__(256) void retrace_kernel(AdjointArgs A, const RayEnd* __restrict__ ends)
 {
     const int64_t ray = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -150,6 +150,7 @@ struct AdjointArgs {
     GeoState* tape;              // [ckpt_every][n_rays] step states of one segment
     const int32_t* list;         // the rays to sweep, or NULL: all
     int64_t n_list;              // their number
+    int32_t checked;             // ray_status holds the Jacobian's check already
     const int32_t* n_steps;      // forward outputs
     const int32_t* status;
     const float* dL_dalpha;      // [n_rays][2] or NULL

@@ -1302,14 +1302,15 @@ int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obse
         // The Jacobian comes from the forward-mode tangents of the same cast
         // (about twice a forward, where three reverse columns take ten), the
         // cell cotangents from the reverse sweep of the loss's one column;
-        // either finds out whether the rays retrace the forward's.
+        // each finds out whether its rays retrace the forward's.
         if (ad->jac || ad->dz_dtheta || !loss) {
             CastArgs t = A.c;
             t.ends = (RayEnd*)(ws + al.off_ends);
             TanEnd* te = (TanEnd*)(ws + al.off_tan);
             e = launch_cast_tangent(t, te, s);
             if (!e) e = launch_tangent_observables(t, te, ad->jac, ad->dz_dtheta, s);
-            if (!e && !loss) e = launch_retrace(A, t.ends, s);
+            if (!e) e = launch_retrace(A, t.ends, s);
+            A.checked = 1;
         }
         if (loss) {
             if (!e) e = launch_fill_zero(grad, grad_accumulator_floats(g->n_cells), s);
