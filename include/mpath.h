@@ -390,10 +390,10 @@ int mpath_cast_jacobian(const mpath_grid* grid, const mpath_cast_desc* desc, mpa
  * fallback, step length h_leaf / N, landing on the iso-eta surface): the cell
  * outputs by one reverse sweep per ray over the checkpointed forward path
  * (each segment of K steps is recomputed from its checkpoint, then traversed
- * backwards), the per-ray outputs by the tangents of mpath_cast_jacobian
- * carried through the same cast once more.  The discrete decisions (leaf
- * levels, stencils, landing) are those of the forward cast and carry no
- * derivative.
+ * backwards), the per-ray outputs by the tangents of mpath_cast_jacobian,
+ * summed over the steps in double precision, carried through the same cast
+ * once more.  The discrete decisions (leaf levels, stencils, landing) are
+ * those of the forward cast and carry no derivative.
  *
  * Per-ray outputs (DEVICE, length n_rays; NaN for rays whose status is not
  * MPATH_RAY_REACHED):
@@ -429,7 +429,7 @@ typedef struct {
 } mpath_adjoint_desc;
 
 /* Device workspace of mpath_adjoint for this desc (which needs
- * checkpoint_every > 0): K states per ray (40 B each), 104 B per ray, and
+ * checkpoint_every > 0): K states per ray (40 B each), 144 B per ray, and
  * 16 B per cell (rounded up to a multiple of 8 cells). */
 int mpath_adjoint_workspace_bytes(const mpath_grid* grid, const mpath_cast_desc* desc, size_t* bytes);
 
@@ -537,8 +537,8 @@ int mpath_infinitesimal_beam(const mpath_grid* grid, const mpath_cast_desc* desc
  * Jacobian sweep over the sources that have to move).  A source stops
  * iterating when the angle between beta_i and beta is below tol.  At the end
  * every source is cast once more along its theta and, when requested, its
- * exact A and dz5/dtheta there come from that cast's tangents
- * (mpath_cast_jacobian). */
+ * exact A and dz5/dtheta there come from that cast's tangents, as in
+ * mpath_adjoint. */
 typedef struct {
     const double* obs_pos;      /* HOST [3] observer position                            */
     int64_t n_src;
@@ -583,7 +583,7 @@ typedef struct {
     double* z1;                 /* z0 + (1 + z0)(Phi_o - Phi_s)                                      */
 } mpath_finder_out;
 
-/* Workspace: the checkpointed cast, Jacobian sweep and tangents (80 bytes per
+/* Workspace: the checkpointed cast, Jacobian sweep and tangents (120 bytes per
  * source) of n_src rays plus per-source tables (80 bytes per source). */
 int mpath_find_geodesics_workspace_bytes(const mpath_grid* grid, const mpath_finder_desc* desc, size_t* bytes);
 /* Synchronises the stream once per iteration and grid round (the count of

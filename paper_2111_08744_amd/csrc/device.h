@@ -271,7 +271,8 @@ struct WholeRay {
         #pragma clang fp contract(off)
         return v[0] + v[1] + v[2];
     }
-    static __device__ __forceinline__ void whole_vector(const float v[3], float all[3])
+    template <class T>
+    static __device__ __forceinline__ void whole_vector(const T v[3], T all[3])
     {
         all[0] = v[0]; all[1] = v[1]; all[2] = v[2];
     }
@@ -289,6 +290,11 @@ struct QuadRay {
     static __device__ __forceinline__ uint32_t of(uint32_t x) { return perm<K, K, K, K>(x); }
     template <int K>
     static __device__ __forceinline__ float of(float x) { return __uint_as_float(of<K>(__float_as_uint(x))); }
+    template <int K>
+    static __device__ __forceinline__ double of(double x)
+    {
+        return __hiloint2double((int)of<K>((uint32_t)__double2hiint(x)), (int)of<K>((uint32_t)__double2loint(x)));
+    }
     static __device__ __forceinline__ uint32_t next(uint32_t x) { return perm<1, 2, 0, 0>(x); }
     static __device__ __forceinline__ uint32_t after(uint32_t x) { return perm<2, 0, 1, 1>(x); }
     static __device__ __forceinline__ uint32_t all_or(uint32_t x) { return x | next(x) | after(x); }
@@ -307,7 +313,8 @@ struct QuadRay {
         #pragma clang fp contract(off)
         return of<0>(v[0]) + of<1>(v[0]) + of<2>(v[0]);
     }
-    static __device__ __forceinline__ void whole_vector(const float v[1], float all[3])
+    template <class T>
+    static __device__ __forceinline__ void whole_vector(const T v[1], T all[3])
     {
         all[0] = of<0>(v[0]); all[1] = of<1>(v[0]); all[2] = of<2>(v[0]);
     }

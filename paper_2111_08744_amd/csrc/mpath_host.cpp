@@ -929,7 +929,7 @@ AdjointLayout adjoint_layout(const mpath_grid* g, const mpath_cast_desc* d, int6
     L.off_tape = 0;
     L.off_grad = align_up((size_t)d->checkpoint_every * (size_t)n_rays * sizeof(GeoState), 256);
     L.off_tan = align_up(L.off_grad + (size_t)grad_accumulator_floats(g->n_cells) * 4, 256);
-    L.off_ends = align_up(L.off_tan + (size_t)n_rays * sizeof(TanEnd), 256);
+    L.off_ends = align_up(L.off_tan + (size_t)n_rays * sizeof(TanEnd64), 256);
     L.total = align_up(L.off_ends + (size_t)n_rays * sizeof(RayEnd), 256);
     return L;
 }
@@ -965,11 +965,13 @@ int mpath_cast_workspace_bytes(const mpath_grid* g, const mpath_cast_desc* d, si
 
 namespace {
 
-// Outputs of the forward-mode derivative (mpath_cast_jacobian).
+// Outputs of the forward-mode derivative: with ends64 summed in double
+// precision (the finder's matrices), else in single (mpath_cast_jacobian).
 struct TangentOut {
-    TanEnd* ends;
-    float* jac;
-    float* dz_dtheta;
+    TanEnd* ends = nullptr;
+    TanEnd64* ends64 = nullptr;
+    float* jac = nullptr;
+    float* dz_dtheta = nullptr;
 };
 
 // mpath_cast, or with inf set the cast that also integrates the
@@ -1046,9 +1048,11 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
         return MPATH_OK;
     }
     if (tg) {
-        e = launch_cast_tangent(a, tg->ends, s);
+        e = tg->ends64 ? launch_cast_tangent(a, tg->ends64, s) : launch_cast_tangent(a, tg->ends, s);
         if (!e) e = launch_observables(a, s);
-        if (!e) e = launch_tangent_observables(a, tg->ends, tg->jac, tg->dz_dtheta, s);
+        if (!e)
+            e = tg->ends64 ? launch_tangent_observables(a, tg->ends64, tg->jac, tg->dz_dtheta, s)
+                           : launch_tangent_observables(a, tg->ends, tg->jac, tg->dz_dtheta, s);
         return e ? hip_fail(e, "tangent cast launch") : MPATH_OK;
     }
     if (inf) {
@@ -1306,7 +1310,7 @@ int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obse
         if (ad->jac || ad->dz_dtheta || !loss) {
             CastArgs t = A.c;
             t.ends = (RayEnd*)(ws + al.off_ends);
-            TanEnd* te = (TanEnd*)(ws + al.off_tan);
+            TanEnd64* te = (TanEnd64*)(ws + al.off_tan);
             e = launch_cast_tangent(t, te, s);
             if (!e) e = launch_tangent_observables(t, te, ad->jac, ad->dz_dtheta, s);
             if (!e) e = launch_retrace(A, t.ends, s);
@@ -1673,7 +1677,7 @@ int finder_plan(const mpath_grid* g, const mpath_finder_desc* f, FinderPlan& P, 
     P.off_adj = align_up(P.off_cast + P.cast_bytes, 256);
     P.adj_bytes = adjoint_layout(g, &P.cd, P.n).total;
     P.off_tan = align_up(P.off_adj + P.adj_bytes, 256);
-    P.total = P.off_tan + n * sizeof(TanEnd);
+    P.total = P.off_tan + n * sizeof(TanEnd64);
     if (f->grid_rounds > 0 && P.n > 0) {
         P.g = f->grid_n;
         P.m_max = f->grid_max > 0 ? std::min<int64_t>(f->grid_max, P.n) : P.n;
@@ -1828,7 +1832,7 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
     fo.z1 = out->z1;
     fo.phi_src = out->phi_src;
     TangentOut tg;
-    tg.ends = reinterpret_cast<TanEnd*>(ws + P.off_tan);
+    tg.ends64 = reinterpret_cast<TanEnd64*>(ws + P.off_tan);
     tg.jac = out->A;
     tg.dz_dtheta = out->dz_dtheta;
     rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop,
