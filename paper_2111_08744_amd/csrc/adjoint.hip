@@ -783,8 +783,8 @@ __device__ __forceinline__ void reverse_loss_step(const AdjointArgs& A, const Ra
     reverse_loss_stage<3>(A, R, rec, dlf, v6, Fb, dlbar, dy);
     phys_axpy(yb, 1.0, dy);
     // a regular step has dl = ds / |k0| with ds fixed by the leaf level:
-    // k0bar += dlbar ds / k0^2 = (dlbar dl) / |k0|
-    if (ds_reg > 0.0) yb.k0 += (double)(dlbar * __builtin_amdgcn_rcpf((float)K));
+    // k0bar += dlbar ds / k0^2 = (dlbar dl) / |k0|, in double precision
+    if (ds_reg > 0.0) yb.k0 += quotient((double)dlbar, K);
 }
 
 // Rays without a derivative (not stopped on the source surface, or a replay
@@ -1492,7 +1492,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
             yb_k0 += (double)dy.k0;
             yb_x += (double)dy.x;
             yb_k += (double)dy.k;
-            if (!landing) yb_k0 += (double)(dlbar * __builtin_amdgcn_rcpf((float)ys.K));
+            if (!landing) yb_k0 += quotient((double)dlbar, ys.K);
             if (owner) S.add(A, T, rec);
         }
     }
