@@ -202,7 +202,7 @@ int mpath_grid_set_values(mpath_grid* grid, const float* values, void* stream);
 #define MPATH_DPHIDL_DIFF 1
 
 #define MPATH_SCHED_AUTO 0      /* library choice (persistent for many observers and many rays) */
-#define MPATH_SCHED_STATIC 1    /* one lane per ray, one launch                                 */
+#define MPATH_SCHED_STATIC 1    /* one launch, one lane per ray or, for few rays, four          */
 #define MPATH_SCHED_PERSISTENT 2/* resident waves pull ray batches from a global queue          */
 
 typedef struct {
@@ -446,8 +446,9 @@ int mpath_adjoint(const mpath_grid* grid, const mpath_cast_desc* desc, const mpa
 /* ---- launch autotuner ----
  * Times candidate launch shapes on a sample of the rays of desc (the first
  * ceil(count / sample_div) pixels of every observer, keeping the observers'
- * mix of source distances) and returns in *tuned a copy of desc with the
- * fastest schedule, waves_per_cu and batch.  Candidates: the static schedule
+ * mix of source distances; a static launch with as many lanes per ray and rays
+ * per wave as the whole cast would take) and returns in *tuned a copy of desc
+ * with the fastest schedule, waves_per_cu and batch.  Candidates: the static schedule
  * and the persistent one at the resident occupancy, half and twice that,
  * with queue refills every 8, 16, 32, 64 or 128 steps.  The launch shape
  * does not change any result.  Synchronises the stream; dev_ws (size from

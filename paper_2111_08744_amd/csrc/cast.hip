@@ -1320,7 +1320,7 @@ template <bool CKPT>
 static hipError_t launch_cast_quad(const CastArgs& args, hipStream_t s)
 {
     const bool amr = args.grid.max_level > 0;
-    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1, kWave / 4);
+    const CastArgs a = spread_rays(args, args.form_rays, amr ? 2 : 1, kWave / 4);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     if (amr) hipLaunchKernelGGL((cast_quad_kernel<true, CKPT>), grid, blk, 0, s, a);
     else hipLaunchKernelGGL((cast_quad_kernel<false, CKPT>), grid, blk, 0, s, a);
@@ -1331,8 +1331,8 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
     const bool amr = args.grid.max_level > 0, td = args.grid.tdual != nullptr;
-    if (!td && by_quads(args, args.n_rays, quad_waves(args))) return launch_cast_quad<false>(args, s);
-    const CastArgs a = spread_rays(args, args.n_rays, amr ? 2 : 1);
+    if (!td && by_quads(args, args.form_rays, quad_waves(args))) return launch_cast_quad<false>(args, s);
+    const CastArgs a = spread_rays(args, args.form_rays, amr ? 2 : 1);
     const size_t lds = (size_t)(td ? FieldCache<true, true>::kFloats : FieldCache<true>::kFloats) * kBlock *
                        sizeof(float);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
@@ -1349,8 +1349,8 @@ hipError_t launch_cast_static(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    if (by_quads(args, args.n_rays, quad_waves(args))) return launch_cast_quad<true>(args, s);
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    if (by_quads(args, args.form_rays, quad_waves(args))) return launch_cast_quad<true>(args, s);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0)
         hipLaunchKernelGGL(cast_ckpt_kernel<true>, ray_grid(a, a.n_rays), dim3(kBlock), lds, s, a);
@@ -1362,7 +1362,7 @@ hipError_t launch_cast_checkpointed(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_infbeam(const CastArgs& args, float* A, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const size_t lds = (size_t)(FieldCache<true>::kFloats + std::max(InfBeam<true>::kFloats, InfBeam<false>::kFloats)) *
                        kBlock * sizeof(float);
     if (a.grid.max_level > 0)
@@ -1379,8 +1379,8 @@ hipError_t launch_cast_tangent(const CastArgs& args, TanEndOf<T>* te, hipStream_
     // four lanes a ray up to two waves per SIMD (registers admit no more):
     // 12,288 rays 3.51 ms and 2.06, 32,768 3.68 and 3.25, 49,152 3.82 and 4.59
     // (uniform); 2.85 and 1.93, 3.29 and 2.38, 3.34 and 3.60 (tree)
-    const bool quad = by_quads(args, args.n_rays, 2);
-    const CastArgs a = spread_rays(args, args.n_rays, 1, quad ? kWave / 4 : kWave);
+    const bool quad = by_quads(args, args.form_rays, 2);
+    const CastArgs a = spread_rays(args, args.form_rays, 1, quad ? kWave / 4 : kWave);
     const bool amr = a.grid.max_level > 0;
     const size_t lds = quad ? 0 : (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
@@ -1412,7 +1412,7 @@ template hipError_t launch_tangent_observables(const CastArgs&, const TanEnd64*,
 hipError_t launch_cast_order(const CastArgs& args, int order, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, args.grid.max_level > 0 ? 2 : 1);
+    const CastArgs a = spread_rays(args, args.form_rays, args.grid.max_level > 0 ? 2 : 1);
     const size_t lds = 0;
     const dim3 grid = ray_grid(a, a.n_rays), block(kBlock);
     const bool amr = a.grid.max_level > 0;
@@ -1429,7 +1429,7 @@ hipError_t launch_cast_order(const CastArgs& args, int order, hipStream_t s)
 hipError_t launch_born_beam(const CastArgs& args, float* A, int32_t* status, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const size_t lds = (size_t)(FieldCache<true>::kFloats + std::max(InfBeam<true>::kFloats, InfBeam<false>::kFloats)) *
                        kBlock * sizeof(float);
     if (a.grid.max_level > 0)
@@ -1442,7 +1442,7 @@ hipError_t launch_born_beam(const CastArgs& args, float* A, int32_t* status, hip
 hipError_t launch_cast_surfaces(const CastArgs& args, const double2* surf, int n_extra, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     Surfaces S;
     S.surf = surf;
@@ -1458,7 +1458,7 @@ hipError_t launch_cast_surfaces(const CastArgs& args, const double2* surf, int n
 hipError_t launch_cast_stop(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     const size_t lds = (size_t)FieldCache<true>::kFloats * kBlock * sizeof(float);
     const bool amr = a.grid.max_level > 0;
@@ -1484,7 +1484,7 @@ hipError_t launch_cast_stop(const CastArgs& args, hipStream_t s)
 hipError_t launch_cast_diff(const CastArgs& args, hipStream_t s)
 {
     if (args.n_rays == 0) return hipSuccess;
-    const CastArgs a = spread_rays(args, args.n_rays, 1);
+    const CastArgs a = spread_rays(args, args.form_rays, 1);
     const dim3 grid = ray_grid(a, a.n_rays), blk(kBlock);
     const size_t lds = (size_t)FieldCache<true, false, true>::kFloats * kBlock * sizeof(float);
     if (a.grid.max_level > 0) hipLaunchKernelGGL(cast_diff_kernel<true>, grid, blk, lds, s, a);

@@ -133,6 +133,8 @@ struct CastArgs {
                                       // kernels read it through step_length()
     int64_t max_steps;
     int64_t n_rays;
+    int64_t form_rays;           // rays by whose number a launch takes its form (lanes a ray, rays a wave):
+                                 // n_rays, or for the autotuner's sample those of the launch it stands for
     int32_t simds;               // SIMDs of the GPU
     int32_t lanes;               // rays per wave of a launch (set by its launcher; see spread_rays)
     OutDev out;

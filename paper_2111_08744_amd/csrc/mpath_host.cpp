@@ -858,6 +858,7 @@ CastArgs make_cast_args(const mpath_grid* g, const mpath_cast_desc* d, const Cas
         a.ds_level[l] = (g->box / g->n0) / (double)(1 << (a.adaptive ? l : 0)) / (double)d->steps_per_cell;
     a.max_steps = std::min<int64_t>(d->max_steps, INT32_MAX);   // steps are counted in 32 bits
     a.n_rays = n_rays;
+    a.form_rays = n_rays;
     a.simds = 4 * (g->num_cus > 0 ? g->num_cus : 256);
     a.lanes = 64;
     a.queue = (unsigned long long*)(ws + lay.off_queue);
@@ -976,10 +977,11 @@ struct TangentOut {
 
 // mpath_cast, or with inf set the cast that also integrates the
 // infinitesimal-beam distortion matrix into inf_A (static schedule), or with
-// tg set the cast that carries the two tangents (static schedule).
+// tg set the cast that carries the two tangents (static schedule).  form_rays:
+// the rays of the launch that this one is a sample of (0: it is none).
 int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* out, void* dev_ws,
               size_t ws_bytes, void* stream, bool inf, float* inf_A, const double2* ray_stop = nullptr,
-              const TangentOut* tg = nullptr)
+              const TangentOut* tg = nullptr, int64_t form_rays = 0)
 {
     int64_t n_rays;
     std::vector<ObsDev> obs;
@@ -999,6 +1001,7 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
 
     CastArgs a = make_cast_args(g, d, lay, ws, n_rays);
     a.ray_stop = ray_stop;
+    if (form_rays > 0) a.form_rays = form_rays;
     a.out.beta = out->beta;
     a.out.alpha = out->alpha;
     a.out.z5 = out->z5;
@@ -1395,6 +1398,10 @@ int mpath_autotune(const mpath_grid* g, const mpath_cast_desc* d, int32_t sample
     if (rc) return rc;
     if (!dev_ws || ws_bytes < need) return fail(MPATH_ERR_WORKSPACE_TOO_SMALL, "autotune workspace too small");
     const TuneSample t = tune_sample(d, sample_div);
+    // the sample is cast in the form of the launch it stands for: fewer rays
+    // would take more lanes each on the static schedule, and not on the other
+    int64_t n_rays = 0;
+    if ((rc = mpath_cast_count_rays(d, &n_rays))) return rc;
     hipStream_t s = (hipStream_t)stream;
     // candidates: the static schedule, and the persistent one at the
     // resident occupancy, half and twice that, with refills every 8..128 steps
@@ -1422,7 +1429,7 @@ int mpath_autotune(const mpath_grid* g, const mpath_cast_desc* d, int32_t sample
         // the first candidate runs once more untimed (warm caches and code)
         for (int rep = (i == 0 ? -1 : 0); rep < 2 && rc == MPATH_OK; ++rep) {
             if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(MPATH_ERR_DEVICE, "autotune: event record"); break; }
-            rc = mpath_cast(g, &c, &none, dev_ws, ws_bytes, stream);
+            rc = cast_impl(g, &c, &none, dev_ws, ws_bytes, stream, false, nullptr, nullptr, nullptr, n_rays);
             if (rc) break;
             float m = 0.0f;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
