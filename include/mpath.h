@@ -429,8 +429,8 @@ typedef struct {
 } mpath_adjoint_desc;
 
 /* Device workspace of mpath_adjoint for this desc (which needs
- * checkpoint_every > 0): K states per ray (40 B each), 144 B per ray, and
- * 16 B per cell (rounded up to a multiple of 8 cells). */
+ * checkpoint_every > 0): K states per ray (40 B each; 144 B per ray for
+ * K < 4) and 16 B per cell (rounded up to a multiple of 8 cells). */
 int mpath_adjoint_workspace_bytes(const mpath_grid* grid, const mpath_cast_desc* desc, size_t* bytes);
 
 /* Derivatives after a checkpointed mpath_cast with the same grid (whose
@@ -584,8 +584,8 @@ typedef struct {
     double* z1;                 /* z0 + (1 + z0)(Phi_o - Phi_s)                                      */
 } mpath_finder_out;
 
-/* Workspace: the checkpointed cast, Jacobian sweep and tangents (120 bytes per
- * source) of n_src rays plus per-source tables (80 bytes per source). */
+/* Workspace: the checkpointed cast and Jacobian sweep of n_src rays plus
+ * per-source tables (80 bytes per source). */
 int mpath_find_geodesics_workspace_bytes(const mpath_grid* grid, const mpath_finder_desc* desc, size_t* bytes);
 /* Synchronises the stream once per iteration and grid round (the count of
  * sources still iterating decides whether to continue).  Errors:

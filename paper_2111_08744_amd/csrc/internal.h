@@ -104,6 +104,7 @@ struct TanEndOf {
 };
 using TanEnd = TanEndOf<float>;
 using TanEnd64 = TanEndOf<double>;
+static_assert(sizeof(TanEnd) == 80 && sizeof(TanEnd64) == 120 && sizeof(RayEnd) == 24, "sizes of the workspaces");
 
 struct OutDev {
     double* beta;

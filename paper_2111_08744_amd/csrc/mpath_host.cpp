@@ -918,20 +918,22 @@ int make_surface_table(const mpath_grid* g, const mpath_cast_desc* d, const std:
     return MPATH_OK;
 }
 
-// Adjoint workspace: one segment of step states per ray, the cell cotangents
-// in library order, and the tangents and end states of the Jacobian's pass.
+// Adjoint workspace: one segment of step states per ray, and the cell
+// cotangents in library order.  The tangents and end states of the Jacobian's
+// pass, which are read before the loss sweep begins, take the states' place.
 struct AdjointLayout {
-    size_t off_tape, off_grad, off_tan, off_ends, total;
+    size_t off_tape, off_tan, off_ends, off_grad, total;
 };
 
 AdjointLayout adjoint_layout(const mpath_grid* g, const mpath_cast_desc* d, int64_t n_rays)
 {
     AdjointLayout L;
-    L.off_tape = 0;
-    L.off_grad = align_up((size_t)d->checkpoint_every * (size_t)n_rays * sizeof(GeoState), 256);
-    L.off_tan = align_up(L.off_grad + (size_t)grad_accumulator_floats(g->n_cells) * 4, 256);
-    L.off_ends = align_up(L.off_tan + (size_t)n_rays * sizeof(TanEnd64), 256);
-    L.total = align_up(L.off_ends + (size_t)n_rays * sizeof(RayEnd), 256);
+    const size_t n = (size_t)n_rays;
+    L.off_tape = L.off_tan = 0;
+    L.off_ends = n * sizeof(TanEnd64);
+    L.off_grad = align_up(std::max((size_t)d->checkpoint_every * n * sizeof(GeoState),
+                                   L.off_ends + n * sizeof(RayEnd)), 256);
+    L.total = align_up(L.off_grad + (size_t)grad_accumulator_floats(g->n_cells) * 4, 256);
     return L;
 }
 
@@ -1592,7 +1594,7 @@ struct FinderPlan {
     int64_t count = 0;
     mpath_cast_desc cd;
     size_t off_stop = 0, off_target = 0, off_iter = 0, off_status = 0, off_sep = 0, off_jac = 0, off_nsteps = 0,
-           off_list = 0, off_active = 0, off_cast = 0, off_adj = 0, off_tan = 0, cast_bytes = 0, adj_bytes = 0,
+           off_list = 0, off_active = 0, off_cast = 0, off_adj = 0, cast_bytes = 0, adj_bytes = 0,
            total = 0;
     CastLayout lay;
     // grid search: at most m_max sources, g x g candidates each
@@ -1683,8 +1685,7 @@ int finder_plan(const mpath_grid* g, const mpath_finder_desc* f, FinderPlan& P, 
     P.cast_bytes = P.lay.total;
     P.off_adj = align_up(P.off_cast + P.cast_bytes, 256);
     P.adj_bytes = adjoint_layout(g, &P.cd, P.n).total;
-    P.off_tan = align_up(P.off_adj + P.adj_bytes, 256);
-    P.total = P.off_tan + n * sizeof(TanEnd64);
+    P.total = P.off_adj + P.adj_bytes;
     if (f->grid_rounds > 0 && P.n > 0) {
         P.g = f->grid_n;
         P.m_max = f->grid_max > 0 ? std::min<int64_t>(f->grid_max, P.n) : P.n;
@@ -1832,14 +1833,15 @@ int mpath_find_geodesics(const mpath_grid* g, const mpath_finder_desc* f, mpath_
             }
         }
     }
-    // final cast along theta, with its tangents for the distortion matrix there
+    // final cast along theta, with its tangents (in the sweeps' workspace) for
+    // the distortion matrix there
     P.cd.checkpoint_every = 0;
     fo.z5 = out->z5;
     fo.z0 = out->z0;
     fo.z1 = out->z1;
     fo.phi_src = out->phi_src;
     TangentOut tg;
-    tg.ends64 = reinterpret_cast<TanEnd64*>(ws + P.off_tan);
+    tg.ends64 = reinterpret_cast<TanEnd64*>(aws + adjoint_layout(g, &P.cd, P.n).off_tan);
     tg.jac = out->A;
     tg.dz_dtheta = out->dz_dtheta;
     rc = cast_impl(g, &P.cd, &fo, cws, P.cast_bytes, stream, false, nullptr, stop,
