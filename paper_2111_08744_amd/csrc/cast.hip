@@ -566,17 +566,23 @@ __device__ __forceinline__ double inv_sqrt(double x)
 // On a refined grid the six probes are evaluated through a second stencil
 // cache, so that the integration's own is left in place.  On a uniform grid
 // x +- h e_i lies at the same offsets in the neighbouring stencils b +- e_i,
-// so the six independent entries of H are trilinear with the differences of
-// those records' coefficients: 48 words a lane, formed when x enters a new
-// stencil and evaluated with 42 FMAs a step, where six probes, each almost
-// always in another stencil than the last, were six resolutions and gathers:
-// 49,152 rays to z = 1 on a 64^3 grid 23.3 -> 13.0 ms, the Born beam 16.2 ->
-// 8.1.
+// so the six independent entries of H are the trilinear interpolants of the
+// differences of the cells' gradients one cell to either side of x's own
+// stencil cells: 48 words a lane, formed from 32 cells when x enters a new
+// stencil and evaluated with 84 instructions a step, where six probes, each
+// almost always in another stencil than the last, were six resolutions and
+// gathers: 49,152 rays to z = 1 on a 64^3 grid 23.3 -> 12.2 ms, the Born beam
+// 16.2 -> 8.2.  The differences are taken in double precision, as the probes'
+// were, and the eight values interpolated, whose weights are convex: float32
+// differences of the records' trilinear coefficients gave A's mixed entry 1.5
+// to 1.7 times the error (3,072 rays to z = 0.1, against 64 bits: six probes
+// 9.8e-12, the coefficients 1.66e-11, this 9.3e-12; with float32 differences of
+// the cells 9.9e-12, at 11.1 ms where double takes 12.2).
 template <bool AMR>
 struct InfBeam {
     static constexpr int kFloats = AMR ? FieldCache<AMR>::kFloats : 48;   // LDS words per lane
     FieldCache<AMR> P;           // AMR: the probes' stencils
-    float4* c;                   // uniform: coefficients of H, quad o of entry p (00, 01, 02, 11, 12, 22) at c[64 (2 p + o)]
+    float4* c;                   // uniform: entry p of H (00, 01, 02, 11, 12, 22) at the stencil's cells 0..3 at c[64 2 p], 4..7 after it
     int base;                    // uniform: the stencil they belong to
     double chi_p, Tp[3], Up[3];  // previous sample: chi T and chi^2 T (T11, T12, T22)
     double J1[3], J2[3];         // trapezoid sums of chi T and chi^2 T
@@ -597,45 +603,72 @@ struct InfBeam {
         for (int k = 0; k < 3; ++k) J1[k] = J2[k] = 0.0;
     }
 
-    // Uniform grid: coefficients of H (times 2 h; the mixed entries times 4 h)
-    // in the stencil of F.  A probe without a complete stencil (the edge of a
-    // non-periodic box) leaves a zero row.
+    // Uniform grid: H (times 2 h; the mixed entries times 4 h) at the 8 cells of
+    // F's stencil.  A probe without a complete stencil (the edge of a
+    // non-periodic box) leaves a zero row, a point without one a zero H.
     __device__ __forceinline__ void load(const GridDev& g, const FieldCache<AMR>& F)
     {
         const uint32_t bits = (1u << (3 * __builtin_ctz((unsigned)g.n0))) - 1u;
-        float4 q[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) q[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // per axis the interleaved coordinates of the cells -1, 0, 1, 2 (wrapping)
+        uint32_t at[3][4];
+        bool ok[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            // the dilated coordinate of axis i plus and minus one (wrapping)
-            const uint32_t md = (0x49249249u << i) & bits, m = (uint32_t)F.base;
-            const uint32_t up = (m & ~md) | (((m | ~md) + (1u << i)) & md);
-            const uint32_t dn = (m & ~md) | (((m & md) - (1u << i)) & md);
-            bool ok = true;
-            if (!g.periodic) {
+            const uint32_t lanes = (0x49249249u << i) & bits, m = (uint32_t)F.base & lanes;
+            at[i][0] = (m - (1u << i)) & lanes;
+            at[i][1] = m;
+            at[i][2] = step_up(m, lanes, 1u << i) & lanes;
+            at[i][3] = step_up(at[i][2], lanes, 1u << i) & lanes;
+            ok[i] = F.leafL >= 0;
+            if (ok[i] && !g.periodic) {
                 const int b = (int)F.kd[i];
-                ok = b >= 1 && b + 2 < g.n0;
+                ok[i] = b >= 1 && b + 2 < g.n0;
             }
-            if (ok) {
-                const float4* rp = g.dual + 8 * (int64_t)up;
-                const float4* rm = g.dual + 8 * (int64_t)dn;
+        }
+        auto cell = [&](int x, int y, int z, float G[3]) {      // its gradient
+            const float4 q = g.payload[at[0][x] | at[1][y] | at[2][z]];
+            G[0] = q.y; G[1] = q.z; G[2] = q.w;
+        };
+        float in[8][3];
+        double H[6][8];
+#pragma unroll
+        for (int o = 0; o < 8; ++o) cell(1 + (o & 1), 1 + ((o >> 1) & 1), 1 + (o >> 2), in[o]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                // the cell beyond corner o along axis i, and the corner on its other side
+                const int up = (o >> i) & 1;
+                int k[3] = {1 + (o & 1), 1 + ((o >> 1) & 1), 1 + (o >> 2)};
+                k[i] = up ? 3 : 0;
+                float out[3];
+                cell(k[0], k[1], k[2], out);
 #pragma unroll
                 for (int j = 0; j < 3; ++j) {
+                    const double b = in[o ^ (1 << i)][j], d = up ? (double)out[j] - b : b - (double)out[j];
                     const int a0 = i < j ? i : j, a1 = i < j ? j : i;
-                    const int p = a0 == 0 ? a1 : a0 + a1 + 1;      // 00 01 02 11 12 22
-#pragma unroll
-                    for (int o = 0; o < 2; ++o) {
-                        const float4 u = rp[2 * j + o], w = rm[2 * j + o];
-                        float4& t = q[2 * p + o];
-                        t.x += u.x - w.x; t.y += u.y - w.y; t.z += u.z - w.z; t.w += u.w - w.w;
-                    }
+                    double& h = H[a0 == 0 ? a1 : a0 + a1 + 1][o];     // 00 01 02 11 12 22
+                    const double r = ok[i] ? d : 0.0;
+                    h = i <= j ? r : h + r;
                 }
             }
         }
 #pragma unroll
-        for (int k = 0; k < 12; ++k) c[64 * k] = q[k];
+        for (int p = 0; p < 6; ++p) {
+            c[64 * 2 * p] = make_float4((float)H[p][0], (float)H[p][1], (float)H[p][2], (float)H[p][3]);
+            c[64 * (2 * p + 1)] = make_float4((float)H[p][4], (float)H[p][5], (float)H[p][6], (float)H[p][7]);
+        }
         base = F.base;
+    }
+
+    // Trilinear interpolant of the values a (cells 0..3) and b (4..7).
+    static __device__ __forceinline__ float interpolate(const float4 a, const float4 b, const float t[3])
+    {
+        #pragma clang fp contract(off)
+        const float x0 = fmaf(t[0], a.y - a.x, a.x), x1 = fmaf(t[0], a.w - a.z, a.z);
+        const float x2 = fmaf(t[0], b.y - b.x, b.x), x3 = fmaf(t[0], b.w - b.z, b.z);
+        const float y0 = fmaf(t[1], x1 - x0, x0), y1 = fmaf(t[1], x3 - x2, x2);
+        return fmaf(t[2], y1 - y0, y0);
     }
 
     // The Hessian's entries (00, 01, 02, 11, 12, 22) at the point v, F's last
@@ -668,8 +701,7 @@ struct InfBeam {
             const double i2h = 0.5 * g.inv_h0;
 #pragma unroll
             for (int p = 0; p < 6; ++p) {
-                const float4 a = c[64 * 2 * p], b = c[64 * (2 * p + 1)];
-                const float f = trilinear_eval(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, F.t[0], F.t[1], F.t[2]);
+                const float f = interpolate(c[64 * 2 * p], c[64 * (2 * p + 1)], F.t);
                 H[p] = (double)f * (p == 0 || p == 3 || p == 5 ? i2h : 0.5 * i2h);
             }
         }
