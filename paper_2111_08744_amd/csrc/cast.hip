@@ -990,18 +990,18 @@ __global__ void permute_values_kernel(float4* payload, const int64_t* perm, cons
 // Every operation is written out (no contraction), so that one and four lanes
 // a ray (Form) give the same bits.
 //
-// T: the precision of the tangents at the step starts.  A step's increments are
-// formed in float32 either way; summed in float32 over the 3,000 steps of 8,192
-// rays to z = 1 (uniform 64^3) they leave dz5/dtheta a median error of 1.3e-8
-// against 64 bits (rms of the values 2.6e-2) and A one of 1.0e-8, summed in
-// double 2.6e-9 and 2.4e-9, the reverse sweep's columns 3.0e-9 and 3.8e-9.  The
-// time is the same (131,072 rays, 49,152 and 4,096: within 0.4 per cent).
-template <class Form, class T>
+// A step's increments are formed in float32 and summed over the steps in double
+// precision.  Summed in float32 over the 3,000 steps of 8,192 rays to z = 1
+// (uniform 64^3) they left dz5/dtheta a median error of 1.3e-8 against 64 bits
+// (rms of the values 2.6e-2) and A one of 1.0e-8, in double 2.6e-9 and 2.4e-9, a
+// reverse sweep of three columns 3.0e-9 and 3.8e-9.  The time is the same
+// (131,072 rays, 49,152 and 4,096: within 0.5 per cent).
+template <class Form>
 struct TangentPair {
     static constexpr int C = Form::kComp;
     float n[C];                                   // initial direction
     float e[2][C];                                // e_b
-    T dEta[2], dK[2], dX[2][C], dQ[2][C];         // tangents at the step start
+    double dEta[2], dK[2], dX[2][C], dQ[2][C];    // tangents at the step start
     float fEta[2], fK[2], fX[2][C], fQ[2][C];     // their derivative at the previous stage
     float aEta[2], aK[2], aX[2][C], aQ[2][C];     // sum of w_i times it over the stages
     float rho[2];                                  // d(dl)/dl of the recorded pass
@@ -1030,12 +1030,12 @@ struct TangentPair {
         for (int i = 0; i < C; ++i) n[i] = own(v, i);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            dEta[b] = T(0);
-            dK[b] = T(0);
+            dEta[b] = 0.0;
+            dK[b] = 0.0;
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 e[b][i] = own(eb[b], i);
-                dX[b][i] = T(0);
+                dX[b][i] = 0.0;
                 dQ[b][i] = km1 * e[b][i];
             }
         }
@@ -1156,10 +1156,6 @@ struct TangentPair {
     }
 
     // t + (rho D + h6 sum), the increment in float32
-    static __device__ __forceinline__ float advanced(float t, float rho, float D, float h6, float sum)
-    {
-        return fmaf(rho, D, fmaf(h6, sum, t));
-    }
     static __device__ __forceinline__ double advanced(double t, float rho, float D, float h6, float sum)
     {
         #pragma clang fp contract(off)
@@ -1188,7 +1184,7 @@ struct TangentPair {
 // The cast with the two tangents: the primal outputs of the plain cast (bit
 // for bit) and the tangent end states for tangent_observables_kernel.
 // The tangents take registers the plain cast has not: two waves per SIMD.
-// QUAD: four lanes per ray.  S: the precision of the tangents' sums.
+// QUAD: four lanes per ray.  S: the precision the end states are kept in.
 template <bool AMR, bool QUAD, class S>
 __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, TanEndOf<S>* te)
 {
@@ -1199,16 +1195,19 @@ __global__ __launch_bounds__(kBlock, 2) void cast_tangent_kernel(CastArgs a, Tan
     RayRun<AMR, FC> R;
     if constexpr (!QUAD) R.F.bind(coef_lds);
     R.start(a, r);
-    TangentPair<FC, S> T;
+    TangentPair<FC> T;
     T.init(a, a.dirs + 3 * r, R.phi_o);
     R.advance_recorded(a, T);
     R.finish(a);           // leaves the end point's stencil in R.F
     TanEndOf<S> e;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-        e.deta[b] = T.dEta[b];
-        e.dK[b] = T.dK[b];
-        FC::whole_vector(T.dX[b], e.dX[b]);
+        double dX[3];
+        FC::whole_vector(T.dX[b], dX);
+        e.deta[b] = (S)T.dEta[b];
+        e.dK[b] = (S)T.dK[b];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) e.dX[b][i] = (S)dX[i];
     }
     FC::whole_vector(R.y.d, e.d);
     e.phi_o = R.phi_o;

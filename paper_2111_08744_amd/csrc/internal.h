@@ -90,8 +90,8 @@ struct RayEnd {
 // length, e_b the direction the initial n moves along) at the end point before
 // the landing step's length is differentiated; the end state's d and K, Phi at
 // the observer, and the stencil (lowest corner, level) of the end point.
-// T: the precision the tangents are summed in over the steps, float for
-// mpath_cast_jacobian, double for mpath_adjoint and the finder.
+// T: the precision the tangents are kept in, float for mpath_cast_jacobian,
+// double for mpath_adjoint and the finder.
 template <class T>
 struct TanEndOf {
     T deta[2], dK[2], dX[2][3];

@@ -968,8 +968,8 @@ int mpath_cast_workspace_bytes(const mpath_grid* g, const mpath_cast_desc* d, si
 
 namespace {
 
-// Outputs of the forward-mode derivative: with ends64 summed in double
-// precision (the finder's matrices), else in single (mpath_cast_jacobian).
+// Outputs of the forward-mode derivative: with ends64 the end states are kept in
+// double precision (the finder's matrices), else in single (mpath_cast_jacobian).
 struct TangentOut {
     TanEnd* ends = nullptr;
     TanEnd64* ends64 = nullptr;

@@ -1,4 +1,4 @@
-"""The per-ray derivatives of mpath_adjoint and of the finder over a long path:
+"""The per-ray derivatives of mpath_adjoint, mpath_cast_jacobian and the finder over a long path:
 3,000 steps to z = 1 on a uniform grid, against the oracle's complex step.
 Stage quantities are float32 on both the tangents' and the reverse sweep's
 way, one rounding (6e-8 relative) each; what a step adds is summed in double
@@ -28,11 +28,16 @@ def case():
     return M, cells, M.Grid(cells, COSMO), [0.5 * cells.box] * 3
 
 
-def test_redshift_derivative_of_a_long_path(case):
+@pytest.mark.parametrize("call", ["adjoint", "jacobian"])
+def test_redshift_derivative_of_a_long_path(case, call):
     M, cells, grid, obs = case
-    cfg = M.CastConfig(obs, 1.0, 4, [0], [96], steps_per_cell=10, checkpoint_every=32)
-    out = M.cast(grid, cfg)
-    dz = M.adjoint(grid, cfg, out, jacobian=True)["dz_dtheta"].cpu().numpy().astype(np.float64)
+    if call == "adjoint":
+        cfg = M.CastConfig(obs, 1.0, 4, [0], [96], steps_per_cell=10, checkpoint_every=32)
+        out = M.cast(grid, cfg)
+        res = M.adjoint(grid, cfg, out, jacobian=True)
+    else:
+        out = res = M.jacobian(grid, M.CastConfig(obs, 1.0, 4, [0], [96], steps_per_cell=10))
+    dz = res["dz_dtheta"].cpu().numpy().astype(np.float64)
     assert (out["n_steps"].cpu().numpy() > 2500).all()
     p = O.params(obs, z_src=1.0, steps_per_cell=10, adaptive=False)
     field, c = O.Field.grid(cells), O.cosmo(*COSMO)
