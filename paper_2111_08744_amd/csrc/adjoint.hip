@@ -25,13 +25,12 @@
 //                    interpolated (Phi, grad Phi) at every sub-step are
 //                    scattered to the cells with the CIC weights (dL/d cell
 //                    values)
-//   beta_1, beta_2, z   adjoint_kernel: e~_a(beta) . x / |x_s - x_obs| and the
-//                    redshift z5 (Sect. 2.5); their values at the observer,
-//                    contracted with d k / d theta_b, give the distortion
-//                    matrix A_ab = d beta_a / d theta_b (Sect. 2.3) and
-//                    d z5 / d theta_b.  Only the finder's Newton steps take
-//                    them so: three reverse columns cost ten forwards, the
-//                    two tangents of cast_tangent_kernel two.
+//   beta_1, beta_2   adjoint_kernel: e~_a(beta) . x / |x_s - x_obs|; their
+//                    values at the observer, contracted with d k / d theta_b,
+//                    give the distortion matrix A_ab = d beta_a / d theta_b
+//                    (Sect. 2.3).  Only the finder's Newton steps take it so:
+//                    the two tangents of cast_tangent_kernel, which cost two
+//                    forwards, give the other products.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -105,7 +104,7 @@ struct Jet32 {
     int base, lvl;
 };
 
-// The four stages of one RK4 step for the Jacobian sweep (three columns),
+// The four stages of one RK4 step for the Jacobian sweep (two columns),
 // kept in this lane's LDS slots.  Word w of stage i is at p[(i * kWords + w) kBlock].
 struct LdsRecord {
     static constexpr int kWords = 18;
@@ -857,7 +856,7 @@ __device__ __forceinline__ void point_jet(const AdjointArgs& A, const RayCtx& R,
 }
 
 // Cotangents of the state at the end point yf (on the source surface):
-// beta_a and z columns, and the loss column from dL/dalpha and dL/dz5; the
+// the beta_a columns, or the loss column from dL/dalpha and dL/dz5; the
 // direct Phi_s term of the loss is scattered to the end point's stencil (end_base) and
 // the Phi_o term returned.  The landing step has its length set by
 // eta(y_f) = eta_s, so the cotangent along the flow F(y_f) is removed.
@@ -867,7 +866,6 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
                                                const double e1[3], const double e2[3], Phys (&yb)[W],
                                                double& phio_bar, double& phis_bar)
 {
-    constexpr bool HAS_JAC = W >= 3;
     const GridDev& g = A.c.grid;
     HubbleCubic Hf;
     Hf.init(A.c.cosmo, yf.eta);
@@ -889,14 +887,12 @@ __device__ __forceinline__ void end_cotangents(const AdjointArgs& A, const RayCt
     const double dz_dphio = -a_s * yf.K * (1.0 + phis) / ((1.0 + phio) * (1.0 + phio));
 #pragma unroll
     for (int c = 0; c < W; ++c) phys_zero(yb[c]);
-    if (HAS_JAC) {
+    if constexpr (W == 2) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             yb[0].x[i] = f1[i] / chi;
             yb[1].x[i] = f2[i] / chi;
-            yb[2].x[i] = dz_dphis * Jf.gphi[i];
         }
-        yb[2].k0 = -dz_dK;
     }
     phio_bar = phis_bar = 0.0;
     if (SCATTER) {
@@ -1007,10 +1003,10 @@ __device__ __forceinline__ bool retraced(const RayEnd& e, const GeoState& y)
     return y.eta == e.eta && y.dx[0] == e.dx[0] && y.dx[1] == e.dx[1] && y.dx[2] == e.dx[2];
 }
 
-// The distortion matrix by the reverse sweep: the three columns beta_1,
-// beta_2 and z of the rays A.list (the finder's Newton steps; the other
-// products take the tangents of cast_tangent_kernel), for more rays than
-// adjoint_quad_kernel takes.
+// The distortion matrix by the reverse sweep: the two columns beta_1 and
+// beta_2 of the rays A.list (the finder's Newton steps; the other products take
+// the tangents of cast_tangent_kernel), for more rays than adjoint_quad_kernel
+// takes.
 template <bool AMR>
 __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
 {
@@ -1020,7 +1016,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
     int64_t at;
     if (!lane_ray(a, A.n_list, at)) return;
     const int64_t ray = A.list[at];
-    constexpr int W = 3;
+    constexpr int W = 2;
     if (A.status[ray] != MPATH_RAY_REACHED || A.n_steps[ray] <= 0) {
         write_nan_jacobian(A, ray);
         return;
@@ -1100,12 +1096,8 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
     for (int bb = 0; bb < 2; ++bb) {
         const double db0 = w.kmag * (yb[0].k[0] * eb[bb][0] + yb[0].k[1] * eb[bb][1] + yb[0].k[2] * eb[bb][2]);
         const double db1 = w.kmag * (yb[1].k[0] * eb[bb][0] + yb[1].k[1] * eb[bb][1] + yb[1].k[2] * eb[bb][2]);
-        const double dz = w.kmag * (yb[2].k[0] * eb[bb][0] + yb[2].k[1] * eb[bb][1] + yb[2].k[2] * eb[bb][2]);
-        if (A.jac) {
-            A.jac[4 * ray + bb] = (float)db0;          // row beta_1
-            A.jac[4 * ray + 2 + bb] = (float)db1;      // row beta_2
-        }
-        if (A.dz_dtheta) A.dz_dtheta[2 * ray + bb] = (float)dz;
+        A.jac[4 * ray + bb] = (float)db0;          // row beta_1
+        A.jac[4 * ray + 2 + bb] = (float)db1;      // row beta_2
     }
 }
 
@@ -1228,8 +1220,9 @@ __global__ __launch_bounds__(kBlock, 2) void adjoint_loss_kernel(AdjointArgs A)
 // the stages' coefficients kept from the replay and the scatter sums of its
 // component in registers, and shares the scalars.  The start and the end of a
 // ray run on whole vectors in all four lanes alike.  Without LOSS, the
-// Jacobian's columns of the rays A.list: the replay likewise, then each lane
-// reverses one column on whole vectors, with the operations of adjoint_kernel.
+// matrix's columns of the rays A.list: the replay likewise, then each lane
+// reverses one column (the first lane beta_1, the others beta_2) on whole
+// vectors, with the operations of adjoint_kernel.
 // ---------------------------------------------------------------------------
 struct QuadRecord {
     float K[4], H[4], dH[4], d[4], G[4], t[4];
@@ -1459,10 +1452,10 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
                 yb_x = ax == 0 ? yb[0].x[0] : ax == 1 ? yb[0].x[1] : yb[0].x[2];
                 yb_k = ax == 0 ? yb[0].k[0] : ax == 1 ? yb[0].k[1] : yb[0].k[2];
             } else {
-                Phys c[3];
-                end_cotangents<3, false>(A, R, w.F.base, w.F.lvl, *w.ob, ray, false, ye, w.phio, w.e1, w.e2, c,
+                Phys c[2];
+                end_cotangents<2, false>(A, R, w.F.base, w.F.lvl, *w.ob, ray, false, ye, w.phio, w.e1, w.e2, c,
                                          phio_bar, phis_bar);
-                yb[0] = ax == 0 ? c[0] : ax == 1 ? c[1] : c[2];
+                yb[0] = ax == 0 ? c[0] : c[1];
             }
         }
         for (int jl = len - 1; jl >= 0; --jl) {
@@ -1504,8 +1497,7 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_quad_kernel(AdjointArgs A)
 #pragma unroll
         for (int bb = 0; bb < 2; ++bb) {
             const double v = w.kmag * (yb[0].k[0] * eb[bb][0] + yb[0].k[1] * eb[bb][1] + yb[0].k[2] * eb[bb][2]);
-            if (ax < 2 && A.jac) A.jac[4 * ray + 2 * ax + bb] = (float)v;         // row beta_1 or beta_2
-            if (ax == 2 && A.dz_dtheta) A.dz_dtheta[2 * ray + bb] = (float)v;
+            A.jac[4 * ray + (ax == 0 ? 0 : 2) + bb] = (float)v;         // row beta_1 or beta_2
         }
         return;
     }

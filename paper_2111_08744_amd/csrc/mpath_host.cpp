@@ -1305,11 +1305,11 @@ int adjoint_impl(const mpath_grid* g, const mpath_cast_desc* d, const mpath_obse
     A.n_cells = g->n_cells;
     hipError_t e = hipSuccess;
     if (list) {
-        // the finder's Newton steps: the three columns of the listed rays
+        // the finder's Newton steps: the matrix's two columns of the listed rays
         e = launch_adjoint(A, s);
     } else {
         // The Jacobian comes from the forward-mode tangents of the same cast
-        // (about twice a forward, where three reverse columns take ten), the
+        // (about twice a forward, where reverse columns take ten), the
         // cell cotangents from the reverse sweep of the loss's one column;
         // each finds out whether its rays retrace the forward's.
         if (ad->jac || ad->dz_dtheta || !loss) {
