@@ -185,9 +185,10 @@ struct LdsRecord {
     __device__ __forceinline__ void gradient(const GridDev& g, Jet32& J) const;
 };
 
-// The same for the loss sweep (one column), kept in registers: 13 or 14 words
-// a stage.  With the stages unrolled every index is a constant; without the
-// records in LDS two waves fit a SIMD.
+// The same for the loss sweep (one column), in local variables: 13 or 14 words
+// a stage.  With the stages unrolled every index is a constant, and without the
+// records in LDS two waves fit a SIMD.  They do not all stay in registers: see
+// adjoint_loss_kernel.
 struct RegRecord {
     float K[4], H[4], dH[4], k[4][3], G[4][3], t[4][3];
     int base[4], lvl[4];
@@ -1102,10 +1103,12 @@ __global__ __launch_bounds__(kBlock, 1) void adjoint_kernel(AdjointArgs A)
 }
 
 // The cell cotangents of the loss L by the reverse sweep of its one column.
-// One column's stage records fit in registers and the scatter sums take 96
-// bytes of LDS a lane, so that two waves fit a SIMD (one did with the records
-// in LDS and the Jacobian's columns alongside), which hides most of the gather
-// and table latency: 131,072 rays to z = 1 on a uniform 64^3 grid (3,000 steps)
+// The stage records are not in LDS and the scatter sums take 96 bytes of it a
+// lane, so that two waves fit a SIMD (one did with the records in LDS and the
+// Jacobian's columns alongside), which hides most of the gather and table
+// latency, and the traffic of what the 256 registers do not hold: the compiler
+// spills 105 (uniform) or 120 (tree) registers, 143 and 171 with SPREAD, 396 to
+// 516 bytes a lane.  131,072 rays to z = 1 on a uniform 64^3 grid (3,000 steps)
 // 80.3 ms before, 34.6 now, 27 of them without the scatter; with the Jacobian
 // (15 ms of tangents) 80.5 and 49.6.  Fewer rays than fill one wave per SIMD by
 // four lanes each take adjoint_quad_kernel.  SPREAD: waves of fewer than 64 rays (see lane_ray).

@@ -820,7 +820,11 @@ __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_diff_kernel(Cas
     R.finish(a);
 }
 
-// One lane per ray to an iso-chi, iso-lambda or iso-z surface (SURF).
+// One lane per ray to an iso-chi, iso-lambda or iso-z surface (SURF).  At four
+// waves per SIMD the iso-chi and iso-z kernels spill 32 to 60 of the 128
+// registers, which gained them less from the unrolled stages than the plain
+// cast: 196,608 rays to z = 1 on a uniform 64^3 grid 14.9 -> 13.8 and 15.3 ->
+// 12.5 ms, iso-lambda without spills 13.5 -> 10.4.
 template <bool AMR, int SURF>
 __global__ __launch_bounds__(kBlock, kMinWavesPerSimd) void cast_stop_kernel(CastArgs a)
 {

@@ -869,8 +869,9 @@ struct NgpCache : WholeRay {
 // weights and 108 multiply-adds, with no memory access.  It is bound by
 // instruction issue; the check by the leaf's region, which also gives f where
 // the stencil is at the leaf's level, in place of integer coordinates and
-// keys: 49,152 rays to z = 1 on a uniform 64^3 grid 10.8 -> 9.8 ms.  Per axis, with f
-// the position in the centre cell (in [0, 1)), the weights of the cells at
+// keys: 49,152 rays to z = 1 on a uniform 64^3 grid 10.8 -> 9.8 ms.  On a tree
+// the resolution's walks and the payloads do not fit the 256 registers: 112 are
+// spilled.  Per axis, with f the position in the centre cell (in [0, 1)), the weights of the cells at
 // -1, 0, +1 are (1 - f)^2 / 2, 3/4 - (f - 1/2)^2 and f^2 / 2.
 template <bool AMR>
 struct TscCache : WholeRay {

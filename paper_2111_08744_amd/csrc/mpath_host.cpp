@@ -1073,11 +1073,18 @@ int cast_impl(const mpath_grid* g, const mpath_cast_desc* d, mpath_observables* 
     } else {
         // AUTO: the queue for many observers with more rays than the GPU holds at
         // once (4 waves per SIMD), since the static launch gives each XCD a run of
-        // observers, whose paths can differ in length: 64 cones of 16,384 rays on
-        // a uniform 64^3 grid, three draws of source redshifts in [0.1, 2], static
-        // 49.7, 47.8 and 53.4 ms, queue 49.4, 48.0 and 46.8.  Fewer rays take the
-        // static launch, which spreads them over the SIMDs: 64 cones of 64 rays
-        // 6.6 ms and 9.4, 4,096 observers of 3 rays 13.7 and 26.8.
+        // observers, whose paths can differ in length.  Fewer rays take the static
+        // launch, which spreads them over the SIMDs.  Queue over static, three
+        // draws each of source redshifts in [0.1, 1] (uniform 64^3; 64^3 + 3
+        // levels) or [0.1, 0.7] (32^3 + 5 levels), 262,144 rays being the line:
+        //   64 cones of    64 rays   2.15-2.18   1.99-2.15   2.30-2.36
+        //   64 cones of 1,024        1.26-1.43   1.21-1.28   1.19-1.30
+        //   64 cones of 4,096        1.08-1.24   1.02-1.11   1.02-1.10
+        //   16 cones of 16,384       0.98-1.17   0.90-1.01   0.90-1.11
+        //   24 cones of 16,384       0.90-1.12   0.80-0.89   0.78-0.93
+        //   64 cones of 16,384       0.94-0.98   0.88-0.93   0.81-0.87
+        //    8 cones of 65,536       0.77-0.83   0.69-0.80   0.69-0.83
+        //    2 cones of 262,144      0.79-0.94   0.75-1.03   0.77-0.98
         int sched = d->schedule;
         if (sched == MPATH_SCHED_AUTO)
             sched = d->n_obs > 1 && a.n_rays > (int64_t)64 * 4 * a.simds ? MPATH_SCHED_PERSISTENT : MPATH_SCHED_STATIC;
