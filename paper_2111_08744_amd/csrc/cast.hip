@@ -582,7 +582,8 @@ template <bool AMR>
 struct InfBeam {
     static constexpr int kFloats = AMR ? FieldCache<AMR>::kFloats : 48;   // LDS words per lane
     FieldCache<AMR> P;           // AMR: the probes' stencils
-    float4* c;                   // uniform: entry p of H (00, 01, 02, 11, 12, 22) at the stencil's cells 0..3 at c[64 2 p], 4..7 after it
+    float4* c;                   // uniform: entry p of H (00, 01, 02, 11, 12, 22) at the stencil's cells 0..3 at
+                                 // c[64 2 p] and 4..7 at c[64 (2 p + 1)]
     int base;                    // uniform: the stencil they belong to
     double chi_p, Tp[3], Up[3];  // previous sample: chi T and chi^2 T (T11, T12, T22)
     double J1[3], J2[3];         // trapezoid sums of chi T and chi^2 T
@@ -998,8 +999,9 @@ __global__ void permute_values_kernel(float4* payload, const int64_t* perm, cons
 // precision.  Summed in float32 over the 3,000 steps of 8,192 rays to z = 1
 // (uniform 64^3) they left dz5/dtheta a median error of 1.3e-8 against 64 bits
 // (rms of the values 2.6e-2) and A one of 1.0e-8, in double 2.6e-9 and 2.4e-9, a
-// reverse sweep of three columns 3.0e-9 and 3.8e-9.  The time is the same
-// (131,072 rays, 49,152 and 4,096: within 0.5 per cent).
+// reverse sweep of three columns 3.0e-9 and 3.8e-9.  It takes no more time for
+// 4,096 to 131,072 rays (within 0.5 per cent) and 1.5 to 2 per cent more for
+// 2^20 and 2^25.6 (101.0 -> 102.5 ms, 7.12 -> 7.26 s).
 template <class Form>
 struct TangentPair {
     static constexpr int C = Form::kComp;
