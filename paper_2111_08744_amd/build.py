@@ -10,9 +10,9 @@ from __future__ import annotations
 
 import os
 import re
+import shutil
 import subprocess
 import sys
-import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -123,7 +123,10 @@ def _compile(src, extra, verbose):
     """Object file of one source; its kernels' assembly is searched."""
     stem = os.path.splitext(src)[0]
     obj = os.path.join(HERE, "_build", stem + ".o")
-    with tempfile.TemporaryDirectory(dir=os.path.join(HERE, "_build")) as tmp:
+    tmp = os.path.join(HERE, "_build", stem + ".tmp")     # a fixed name, which the object may hold
+    shutil.rmtree(tmp, ignore_errors=True)
+    os.mkdir(tmp)
+    try:
         out = os.path.join(tmp, stem + ".o")
         cmd = [HIPCC, "-x", "hip", *flags(), *extra, "-save-temps=obj", "-c", os.path.join(CSRC, src), "-o", out]
         if verbose:
@@ -138,6 +141,8 @@ def _compile(src, extra, verbose):
             if bad:
                 raise RuntimeError(f"{src}: spills before their lanes are switched on: {bad[:5]}")
         os.replace(out, obj)
+    finally:
+        shutil.rmtree(tmp, ignore_errors=True)
     return obj
 
 
