@@ -571,14 +571,15 @@ __device__ __forceinline__ double inv_sqrt(double x)
 // stencil cells: 48 words a lane, formed from 32 cells when x enters a new
 // stencil and evaluated with 84 instructions a step, where six probes, each
 // almost always in another stencil than the last, were six resolutions and
-// gathers: 49,152 rays to z = 1 on a 64^3 grid 23.3 -> 12.2 ms, the Born beam
-// 16.2 -> 8.2.  The differences are taken in double precision, as the probes'
-// were, and the eight values interpolated, whose weights are convex: float32
-// differences of the records' trilinear coefficients gave A's mixed entry 1.5
-// to 1.7 times the error (3,072 rays to z = 0.1, against 64 bits: six probes
-// 9.8e-12, the coefficients 1.66e-11, this 9.3e-12; with float32 differences of
-// the cells 9.9e-12, at 11.1 ms where double takes 12.2).
-template <bool AMR>
+// gathers: 49,152 rays to z = 1 on a 64^3 grid 23.3 -> 10.9 ms, the Born beam
+// 16.2 -> 7.2.  The differences are rounded once, as the probes' were (the mixed
+// entries' sums are formed in double precision), and the eight values
+// interpolated, whose weights are convex: float32 differences of the records'
+// trilinear coefficients (13.0 and 8.0 ms) gave A's mixed entry 1.5 to 1.7 times
+// the error (3,072 rays to z = 0.1, against 64 bits: six probes 9.8e-12, the
+// coefficients 1.66e-11, this 9.3e-12).
+// ALONE: no integration beside it (the Born beam).
+template <bool AMR, bool ALONE = false>
 struct InfBeam {
     static constexpr int kFloats = AMR ? FieldCache<AMR>::kFloats : 48;   // LDS words per lane
     FieldCache<AMR> P;           // AMR: the probes' stencils
@@ -609,57 +610,83 @@ struct InfBeam {
     // non-periodic box) leaves a zero row, a point without one a zero H.
     __device__ __forceinline__ void load(const GridDev& g, const FieldCache<AMR>& F)
     {
+        bool ok[3] = {true, true, true};
+        if (!g.periodic) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                ok[i] = F.leafL >= 0;
+                if (ok[i]) {
+                    const int b = (int)F.kd[i];
+                    ok[i] = b >= 1 && b + 2 < g.n0;
+                }
+            }
+        }
+        if (ok[0] && ok[1] && ok[2]) form<false>(g, (uint32_t)F.base, ok);
+        else form<true>(g, (uint32_t)F.base, ok);
+        base = F.base;
+    }
+
+    // The same with (EDGE) or without rows left out.
+    template <bool EDGE>
+    __device__ __forceinline__ void form(const GridDev& g, uint32_t from, const bool (&ok)[3])
+    {
         const uint32_t bits = (1u << (3 * __builtin_ctz((unsigned)g.n0))) - 1u;
         // per axis the interleaved coordinates of the cells -1, 0, 1, 2 (wrapping)
         uint32_t at[3][4];
-        bool ok[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const uint32_t lanes = (0x49249249u << i) & bits, m = (uint32_t)F.base & lanes;
+            const uint32_t lanes = (0x49249249u << i) & bits, m = from & lanes;
             at[i][0] = (m - (1u << i)) & lanes;
             at[i][1] = m;
             at[i][2] = step_up(m, lanes, 1u << i) & lanes;
             at[i][3] = step_up(at[i][2], lanes, 1u << i) & lanes;
-            ok[i] = F.leafL >= 0;
-            if (ok[i] && !g.periodic) {
-                const int b = (int)F.kd[i];
-                ok[i] = b >= 1 && b + 2 < g.n0;
-            }
         }
         auto cell = [&](int x, int y, int z, float G[3]) {      // its gradient
             const float4 q = g.payload[at[0][x] | at[1][y] | at[2][z]];
             G[0] = q.y; G[1] = q.z; G[2] = q.w;
         };
-        float in[8][3];
-        double H[6][8];
+        auto put = [&](int p, const auto* h) {
+            c[64 * 2 * p] = make_float4((float)h[0], (float)h[1], (float)h[2], (float)h[3]);
+            c[64 * (2 * p + 1)] = make_float4((float)h[4], (float)h[5], (float)h[6], (float)h[7]);
+        };
+        // the corners, and the cells beyond them along axis i.  The Born kernel
+        // needs the barriers to have the eight in flight together (it waits for
+        // each load without them: 8.2 -> 13.7 ms, with them 7.2); in the cast
+        // the compiler requests 24 at once, and barriers make it spill 39
+        // registers (10.9 -> 15.0 ms).
+        float in[8][3], out[8][3];
 #pragma unroll
         for (int o = 0; o < 8; ++o) cell(1 + (o & 1), 1 + ((o >> 1) & 1), 1 + (o >> 2), in[o]);
+        double X[3][8];                 // the mixed entries 01, 02, 12, rounded once
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
 #pragma unroll
             for (int o = 0; o < 8; ++o) {
-                // the cell beyond corner o along axis i, and the corner on its other side
-                const int up = (o >> i) & 1;
                 int k[3] = {1 + (o & 1), 1 + ((o >> 1) & 1), 1 + (o >> 2)};
-                k[i] = up ? 3 : 0;
-                float out[3];
-                cell(k[0], k[1], k[2], out);
+                k[i] = (o >> i) & 1 ? 3 : 0;
+                cell(k[0], k[1], k[2], out[o]);
+            }
+            if constexpr (ALONE) asm volatile("" ::: "memory");
+            float D[8];
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                const int up = (o >> i) & 1;
+                const float* hi = up ? out[o] : in[o ^ (1 << i)];
+                const float* lo = up ? in[o ^ (1 << i)] : out[o];
+                D[o] = !EDGE || ok[i] ? hi[i] - lo[i] : 0.0f;
 #pragma unroll
                 for (int j = 0; j < 3; ++j) {
-                    const double b = in[o ^ (1 << i)][j], d = up ? (double)out[j] - b : b - (double)out[j];
-                    const int a0 = i < j ? i : j, a1 = i < j ? j : i;
-                    double& h = H[a0 == 0 ? a1 : a0 + a1 + 1][o];     // 00 01 02 11 12 22
-                    const double r = ok[i] ? d : 0.0;
-                    h = i <= j ? r : h + r;
+                    if (j == i) continue;
+                    const double d = !EDGE || ok[i] ? (double)hi[j] - (double)lo[j] : 0.0;
+                    double& x = X[i + j - 1][o];
+                    x = i < j ? d : x + d;
                 }
             }
+            put(i == 0 ? 0 : 2 * i + 1, D);      // 00, 11, 22
+            if (i == 1) put(1, X[0]);
         }
-#pragma unroll
-        for (int p = 0; p < 6; ++p) {
-            c[64 * 2 * p] = make_float4((float)H[p][0], (float)H[p][1], (float)H[p][2], (float)H[p][3]);
-            c[64 * (2 * p + 1)] = make_float4((float)H[p][4], (float)H[p][5], (float)H[p][6], (float)H[p][7]);
-        }
-        base = F.base;
+        put(2, X[1]);
+        put(4, X[2]);
     }
 
     // Trilinear interpolant of the values a (cells 0..3) and b (4..7).
@@ -913,7 +940,7 @@ __global__ __launch_bounds__(kBlock, 2) void born_beam_kernel(CastArgs a, float*
     }
     const double eta_s = a.ray_stop ? a.ray_stop[r].x : ob.eta_s;
     const double chis = a.cosmo_eta0 - eta_s;
-    InfBeam<AMR> B;
+    InfBeam<AMR, true> B;
     FieldCache<AMR> F;
     B.init(born_lds);
     F.bind(born_lds + InfBeam<AMR>::kFloats * kBlock);
